@@ -22,8 +22,8 @@
 // uses), and accumulates nine per-record sums: e = dL/do_eff of each unclamped fragment,
 // its moments e w1, e w2, e w1^2, e w1 w2, e w2^2 in the exponent's factors (Staged; the exponent's
 // gradient is o_eff e, so the projection backward turns them into the mean and conic gradients once
-// per record), and the colour gradient. They are summed over the wave's pixels with a transposed butterfly of
-// permlane swaps and DPP adds and added to the record's slot with nine lanes of one hardware
+// per record), and the colour gradient. They are summed over the wave's pixels (the per-tile kernels with a
+// transposed butterfly of permlane swaps and DPP adds, the sub-tile kernel through LDS rows) and added to the record's slot with nine lanes of one hardware
 // float atomic, only when some lane of the wave contributed.
 #include "megs_internal.hpp"
 
@@ -91,10 +91,16 @@ struct Layout {
 // sqrt(k C) for the covariance Q^-1 = [[A, B], [B, C]], which the factors give without cancellation as
 // A = (r / l22)^2 + 1 / l11^2 and C = 1 / l22^2; widened by 1e-3 relative and 1e-2 px, far more than
 // FP32 rounding moves them, so every pixel with alpha >= 1/255 lies inside.
-__device__ __forceinline__ void stage(const BlendArgs& a, uint32_t g, double x0, double y0, Staged* dst,
-                                      bool box = true) {
-    const float4* q = reinterpret_cast<const float4*>(a.rec + g);  // the record's three vectors
-    const float4 q0 = q[0], q1 = q[1], q2 = q[2];
+struct RecVecs {  // a record's three vectors
+    float4 q0, q1, q2;
+};
+__device__ __forceinline__ RecVecs gather(const BlendArgs& a, uint32_t g) {
+    const float4* q = reinterpret_cast<const float4*>(a.rec + g);
+    return RecVecs{q[0], q[1], q[2]};
+}
+
+__device__ __forceinline__ Staged staged_of(const RecVecs& v, double x0, double y0, bool box) {
+    const float4 &q0 = v.q0, &q1 = v.q1, &q2 = v.q2;
     const double mx = __hiloint2double(__float_as_int(q0.y), __float_as_int(q0.x));
     const double my = __hiloint2double(__float_as_int(q0.w), __float_as_int(q0.z));
     const double r = __hiloint2double(__float_as_int(q1.y), __float_as_int(q1.x));
@@ -113,7 +119,12 @@ __device__ __forceinline__ void stage(const BlendArgs& a, uint32_t g, double x0,
         const float ry = __builtin_amdgcn_sqrtf(cut) * il22 * 1.001f + 0.01f;
         s.box = make_float4(-dxf - rx, -dxf + rx, -dyf - ry, -dyf + ry);
     }
-    *dst = s;
+    return s;
+}
+
+__device__ __forceinline__ void stage(const BlendArgs& a, uint32_t g, double x0, double y0, Staged* dst,
+                                      bool box = true) {
+    *dst = staged_of(gather(a, g), x0, y0, box);
 }
 
 // Does the pixel block [x0, x1] x [y0, y1] (tile-relative, centres at +0.5) meet the staged
@@ -748,14 +759,46 @@ __global__ __launch_bounds__(64) void k_blend_fwd_sub(BlendArgs a, int tile, int
     }
 }
 
+// The sub-tile backward. Reducing an entry's nine sums over the wave as soon as it is replayed takes a
+// butterfly per entry (24 VALU instructions, beside the eight products that form the summands: together
+// more than half of the kernel). Instead the replay, one pixel per lane, leaves only the two scalars that
+// everything is linear in, e and the blending weight, in a row of LDS per entry (one 8-byte store). After
+// kGroup entries the wave turns round: lane (entry, pixel row) takes its entry's eight pixels of one row,
+// forms the moments in registers (an entry's second factor w2 is constant along a row), and the eight rows'
+// partial sums go through LDS to the lane that adds them: lane 9 k + c ends with sum c of entry k, so the
+// kGroup records leave through one atomic instruction, nine consecutive lanes per record (kGroup = 7: 63
+// lanes). That is about 12 VALU instructions an entry: on eight 1080p views of 1 M Gaussians, 937 M VALU
+// instructions per launch instead of 1,369 M, and 2.17 ms instead of 2.42 ms (one 1080p view of 0.96 M:
+// 0.35 instead of 0.42 ms). VALU issue is then 74% of the time; the float atomics' completion is another
+// 0.29 ms (a copy without them ran 1.88 ms), and the rest is latency at four waves per SIMD. The kernel is
+// compiled for four: at five (96 registers) it spills, and since memory operations complete in order, each
+// reload from scratch memory waits for the atomics before it (2.69 ms).
+constexpr int kGroup = 7;
+
 template <bool FLAGS>  // as in k_blend_fwd_sub
-__global__ __launch_bounds__(64) void k_blend_bwd_sub(BlendArgs a, int tile, int persistent) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_blend_bwd_sub(BlendArgs a, int tile,
+                                                                                              int persistent) {
     constexpr int SUB = 8;
-    __shared__ Kept lds[64];
+    // the kept entries of a chunk behind up to kGroup - 1 carried over from the chunk before
+    __shared__ Kept lds[64 + kGroup - 1];
+    // rows[entry][pixel row][pixel]: a row's 64 bytes are four 16-byte pieces, stored in an order that
+    // depends on the row and the entry, so that the 16 lanes of a 16-byte read (two entries' eight rows)
+    // touch every LDS bank once
+    __shared__ __align__(16) float2 rows[kGroup * 64];
+    __shared__ __align__(16) float dlr[3][64];  // the pixels' colour gradients
     const int lane = __lane_id();
-    // the 9 sums leave through one 9-lane atomic: lanes 0, 8, .., 56 hold sums 0..7, lane 63 sum 8
-    const bool adds = (lane & 7) == 0 || lane == kLaneSum8;
-    const int comp = lane == kLaneSum8 ? 8 : lane >> 3;
+    // as replaying lane: pixel (lane & 7, lane >> 3); as summing lane: entry lane >> 3, pixel row lane & 7
+    const int sum_entry = min(lane >> 3, kGroup - 1), sum_row = lane & 7;
+    const int turn = (sum_row >> 2) | ((lane >> 3 & 1) << 1);  // piece h of the summing lane's row is h ^ turn
+    // the replaying lane's place in an even entry's row; an odd entry's is the same with piece bit 1 flipped
+    const int piece = ((lane & 7) >> 1) ^ (lane >> 5);
+    float2* const put0 = rows + (lane >> 3) * 8 + piece * 2 + (lane & 1);
+    float2* const put1 = rows + (lane >> 3) * 8 + (piece ^ 2) * 2 + (lane & 1);
+    const float4* const get = reinterpret_cast<const float4*>(rows + sum_entry * 64 + sum_row * 8);
+    float* const sums = reinterpret_cast<float*>(rows);  // [kGroup * 9][8] by row, once the rows are read
+    // as adding lane: sum lane % 9 of entry lane / 9 (lane 63 adds nothing)
+    const int add_entry = min(lane / 9, kGroup - 1), add_comp = lane % 9;
+    const float4* const fin = reinterpret_cast<const float4*>(sums + min(lane, 9 * kGroup - 1) * 8);
     const int64_t n_items = a.n_tiles * (int64_t)(tile / SUB) * (tile / SUB);
     Pull pull;
     for (int64_t w = next_item(a, -1, persistent, n_items, pull, false); w < n_items;
@@ -784,80 +827,154 @@ __global__ __launch_bounds__(64) void k_blend_bwd_sub(BlendArgs a, int tile, int
         uint32_t wave_last = lst;
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) wave_last = max(wave_last, (uint32_t)__shfl_xor((int)wave_last, d));
+        wave_last = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_last);  // into a scalar register
         if (wave_last == 0) continue;  // wave-uniform: no pixel of the sub-tile blended anything
+        wave_sync();
+        dlr[0][lane] = dl0;
+        dlr[1][lane] = dl1;
+        dlr[2][lane] = dl2;
         const uint2 rg = a.ranges[q.t];
         const float px = (lane & 7) + 0.5f, py = (lane >> 3) + 0.5f;  // relative to the sub-tile
+        const float row_y = sum_row + 0.5f;
         const double fx0 = (double)(c.x0 + q.sx), fy0 = (double)(c.y0 + q.sy);
-        // tile keys and record ids loaded one chunk ahead, as in the forward
-        uint32_t key_n = 0, id_n = 0;
-        if ((uint32_t)lane < wave_last) {
-            const uint32_t i0 = rg.x + wave_last - 1u - (uint32_t)lane;
-            id_n = a.vals[i0];
-            key_n = FLAGS ? a.tkeys[i0] : 0u;
-        }
-        for (uint32_t end = rg.x + wave_last; end > rg.x;) {
-            const uint32_t beg = end - rg.x > 64u ? end - 64u : rg.x;
-            const uint32_t cnt = end - beg;
-            const uint32_t idx = end - 1u - (uint32_t)lane;  // descending list positions
-            const uint32_t key = key_n, gid = id_n;
-            bool hit = false;
-            Staged st;
-            uint32_t g = 0;
-            if ((uint32_t)lane < cnt) {
-                g = gid;
-                const bool flagged = !FLAGS || ((key >> (16 + q.sidx)) & 1u);
-                if (flagged) {
-                    stage(a, g, fx0, fy0, &st, !FLAGS);
-                    // the flags already test the ellipse against the sub-tile; without them, its box
-                    hit = FLAGS ? true : box_meets(st.box, 0, SUB - 1, 0, SUB - 1);
-                }
+        // The list is walked in chunks of 64 from position wave_last - 1 downwards, pipelined: a chunk's
+        // tile keys and record ids are loaded two chunks ahead, and its records are gathered while the
+        // chunk before it is replayed, and taken over before that chunk's first atomics leave (memory
+        // operations complete in order, so a load waited for behind them would wait for them too).
+        const uint32_t first = rg.x + wave_last;  // one past the first chunk's first position
+        uint32_t key_n = 0, id_n = 0, g = 0;
+        bool flagged = false, hit = false;
+        RecVecs raw;
+        Staged st;
+        auto load_ids = [&](uint32_t end) {  // ids and keys of the chunk that ends below `end`
+            if ((uint32_t)lane < end - rg.x) {
+                id_n = a.vals[end - 1u - (uint32_t)lane];
+                key_n = FLAGS ? a.tkeys[end - 1u - (uint32_t)lane] : 0u;
             }
+        };
+        auto issue = [&](uint32_t end) {  // the records of that chunk, from its ids
+            flagged = (uint32_t)lane < end - rg.x && (!FLAGS || ((key_n >> (16 + q.sidx)) & 1u));
+            g = id_n;
+            if (flagged) raw = gather(a, g);
+        };
+        auto take = [&]() {
+            hit = false;
+            if (flagged) {
+                st = staged_of(raw, fx0, fy0, !FLAGS);
+                // the flags already test the ellipse against the sub-tile; without them, its box
+                hit = FLAGS ? true : box_meets(st.box, 0, SUB - 1, 0, SUB - 1);
+            }
+        };
+        load_ids(first);
+        issue(first);
+        uint32_t end = first;
+        uint32_t next = end - rg.x > 64u ? end - 64u : rg.x;
+        load_ids(next);
+        take();
+        int carried = 0;
+        for (;;) {
             const uint64_t m = __ballot(hit);
-            const int nhit = __popcll(m);
+            const int n = carried + __popcll(m);
             if (hit) {
-                const int slot = lane_rank(m);
-                lds[slot] = Kept{st.p0, st.p1, st.b, idx - rg.x + 1u, (uint64_t)grad2d_index(g, 0)};
+                const int slot = carried + lane_rank(m);
+                lds[slot] = Kept{st.p0, st.p1, st.b, end - (uint32_t)lane - rg.x, (uint64_t)grad2d_index(g, 0)};
             }
-            if ((uint32_t)lane < beg - rg.x) {  // the next chunk: positions beg - 1 - lane downwards
-                id_n = a.vals[beg - 1u - (uint32_t)lane];
-                key_n = FLAGS ? a.tkeys[beg - 1u - (uint32_t)lane] : 0u;
-            }
+            issue(next);
+            const uint32_t after = next - rg.x > 64u ? next - 64u : rg.x;
+            load_ids(after);
             wave_sync();
-            for (int k = 0; k < nhit; ++k) {
-                const Kept s = *kept_at(lds, k);
-                float alpha, G, w1, w2;
-                bool clamped;
-                const bool incl = frag(s, px, py, w1, w2, G, alpha, clamped) & (s.pos1 <= lst);
-                if (!__any(incl)) continue;
+            const bool last = next == rg.x;
+            // whole groups; what is left waits for the next chunk, and after the last chunk it is a group too
+            const int todo = last ? n : n - n % kGroup;
+            for (int k0 = 0; k0 < todo; k0 += kGroup) {
+                const Kept* kp = kept_at(lds, k0);
+                uint32_t included = 0;  // entries that some pixel includes
+                Kept ahead = kp[0];
+#pragma unroll
+                for (int kk = 0; kk < kGroup; ++kk) {
+                    if (k0 + kk >= todo) break;  // wave-uniform: the last group's end
+                    const Kept s = ahead;        // (each entry is read from LDS one entry ahead)
+                    if (kk + 1 < kGroup) ahead = kp[kk + 1];
+                    float alpha, G, w1, w2;
+                    bool clamped;
+                    const bool incl = frag(s, px, py, w1, w2, G, alpha, clamped) & (s.pos1 <= lst);
+                    if (!__any(incl)) continue;
+                    included |= 1u << kk;
+                    // a lane the entry does not include takes alpha = 0: its T is then multiplied by the
+                    // reciprocal of 1.0, which is exactly 1.0, and its P by nothing, so it needs no select
+                    const float al = incl ? alpha : 0.0f;
+                    const float Ti = T * __builtin_amdgcn_rcpf(1.0f - al);
+                    // (c - S) . dL/dC, from c . dL/dC and the carried P
+                    const float dcs = __fmaf_rn(s.p1.z, dl0, __fmaf_rn(s.p1.w, dl1, __fmaf_rn(s.b, dl2, -P)));
+                    const float dal = Ti * dcs;
+                    P = __fmaf_rn(al, dcs, P);
+                    T = Ti;
+                    const bool live = incl & !clamped;
+                    // dL/do_eff (the exponent gradient is o_eff times this) and the blending weight
+                    (kk & 1 ? put1 : put0)[kk * 64] = make_float2(live ? G * dal : 0.0f, al * Ti);
+                }
+                if (k0 == 0) take();
+                if (!included) continue;  // wave-uniform
+                wave_sync();
                 float acc[9];
-                // a lane the entry does not include takes alpha = 0: its T is then multiplied by the
-                // reciprocal of 1.0, which is exactly 1.0, and its P by nothing, so it needs no select
-                const float al = incl ? alpha : 0.0f;
-                const float Ti = T * __builtin_amdgcn_rcpf(1.0f - al);
-                const float wgt = al * Ti;
-                // (c - S) . dL/dC, from c . dL/dC and the carried P
-                const float dcs = __fmaf_rn(s.p1.z, dl0, __fmaf_rn(s.p1.w, dl1, __fmaf_rn(s.b, dl2, -P)));
-                acc[6] = wgt * dl0;
-                acc[7] = wgt * dl1;
-                acc[8] = wgt * dl2;
-                const float dal = Ti * dcs;
-                P = __fmaf_rn(al, dcs, P);
-                T = Ti;
-                const bool live = incl & !clamped;
-                acc[5] = live ? G * dal : 0.0f;  // dL/do_eff; the exponent gradient is o_eff times this
-                acc[0] = acc[5] * w1;
-                acc[1] = acc[5] * w2;
-                acc[2] = acc[0] * w1;
-                acc[3] = acc[0] * w2;
-                acc[4] = acc[1] * w2;
-                // (the sums' last add is a volatile statement, so their DPP adds stay in front of the
-                // branch: sunk into it, where only the adding lanes run, each would split into a DPP
-                // move and a separate add)
-                const float val = wave_sum9(acc);
-                if (adds) unsafeAtomicAdd(a.grad2d + (s.slot + comp), val);
+                {
+                    int tn = turn;  // (formed again for each group: the addresses would hold four registers)
+                    asm volatile("" : "+v"(tn));
+                    // rows of entries past the group's end or that no pixel includes hold older values:
+                    // they are summed like the others and not added
+                    const Kept& s = lds[min(k0 + sum_entry, todo - 1)];
+                    const float ax = s.p0.x, by = s.p1.x;
+                    const float wr = __fmaf_rn(s.p0.y, row_y, s.p0.z), w2 = __fmaf_rn(by, row_y, s.p1.y);
+                    float r0 = 0.f, r1 = 0.f;
+                    acc[2] = 0.f; acc[6] = 0.f; acc[7] = 0.f; acc[8] = 0.f;
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {
+                        if (h == 2) __builtin_amdgcn_sched_barrier(0);
+                        const float4 v = get[h ^ tn];  // e, weight of pixels 2 h and 2 h + 1
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) {
+                            const int j = 2 * h + u;
+                            const float e = u ? v.z : v.x, wg = u ? v.w : v.y;
+                            const float w1 = __fmaf_rn(ax, j + 0.5f, wr);
+                            const float m1 = e * w1;
+                            r0 += e;
+                            r1 += m1;
+                            acc[2] = __fmaf_rn(m1, w1, acc[2]);
+                            acc[6] = __fmaf_rn(wg, dlr[0][sum_row * 8 + j], acc[6]);
+                            acc[7] = __fmaf_rn(wg, dlr[1][sum_row * 8 + j], acc[7]);
+                            acc[8] = __fmaf_rn(wg, dlr[2][sum_row * 8 + j], acc[8]);
+                        }
+                    }
+                    acc[0] = r1;
+                    acc[1] = r0 * w2;
+                    acc[3] = r1 * w2;
+                    acc[4] = acc[1] * w2;
+                    acc[5] = r0;
+                }
+                wave_sync();
+                if (lane < 8 * kGroup) {
+                    float* o = sums + sum_entry * 72 + sum_row;
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) o[8 * i] = acc[i];
+                }
+                wave_sync();
+                const float4 f0 = fin[(lane >> 3) & 1], f1 = fin[((lane >> 3) & 1) ^ 1];
+                const float val = ((f0.x + f0.y) + (f0.z + f0.w)) + ((f1.x + f1.y) + (f1.z + f1.w));
+                if (lane < 9 * kGroup && ((included >> add_entry) & 1u))
+                    unsafeAtomicAdd(a.grad2d + (lds[k0 + add_entry].slot + add_comp), val);
+                wave_sync();
+            }
+            if (todo == 0) take();
+            if (last) break;
+            // carry the rest to the front (at most kGroup - 1 entries, and only past whole groups)
+            carried = n - todo;
+            if (todo && lane < 3 * carried) {
+                const float4 v = reinterpret_cast<const float4*>(lds + todo)[lane];
+                reinterpret_cast<float4*>(lds)[lane] = v;
             }
             wave_sync();
-            end = beg;
+            end = next;
+            next = after;
         }
     }
 }
