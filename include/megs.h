@@ -137,8 +137,10 @@ typedef struct {
     int32_t tile;          /* tile edge in pixels: 8, 16 or 32 */
     int32_t batch;         /* records staged in LDS per batch: 32, 64, 128 or 256 */
     uint32_t flags;        /* MEGS_FLAG_* */
-    int32_t waves;         /* wave64s per tile workgroup: 1, 2 or 4 (1 for 8x8 tiles); 0: default
-                              (1 for 8x8 tiles, 4 otherwise) */
+    int32_t waves;         /* wave64s per tile workgroup: 1, 2 or 4 (1 for 8x8 tiles); 0: the
+                              library's choice (one wave per 8x8 tile; 16x16 and 32x32 tiles blend
+                              per 8x8 sub-tile, one independent wave each, with the results of the
+                              per-tile kernels) */
     int64_t pair_capacity; /* 0: size the pair table from the counted pairs (one host sync per
                               forward); > 0: fixed capacity, no host sync, overflow reported
                               as MEGS_ERR_CAPACITY by megs_state_status */

@@ -100,8 +100,6 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // a misaligned pointer is an allocation error, reported before anything is launched.
 bool bad_alloc(const void* p) { return !p || (reinterpret_cast<uintptr_t>(p) & 255u) != 0; }
 
-int waves_of(const megs_config* cfg) { return cfg->waves ? cfg->waves : (cfg->tile == 8 ? 1 : 4); }
-
 // Bump allocator over one caller-provided block.
 struct Carver {
     char* base;
@@ -544,7 +542,7 @@ megs_status enqueue_back(const megs_scene* sc, const Layout& L, const megs_confi
     if (persistent) HIP_TRY(launch_fill_u32(f.queue, 0u, kQueueWords, s));
     {
         StageTimer t(MEGS_STAGE_BLEND_FWD, s);
-        HIP_TRY(launch_blend_fwd(a, L.tile, waves_of(cfg), cfg->batch, persistent, s, cfg->subtile));
+        HIP_TRY(launch_blend_fwd(a, L.tile, cfg->waves, cfg->batch, persistent, s, cfg->subtile));
     }
 
     state->n_records = L.nr;
@@ -614,7 +612,7 @@ megs_status enqueue_backward(const megs_scene* sc, const Layout& L, const megs_c
     if (persistent) HIP_TRY(launch_fill_u32(queue, 0u, kQueueWords, s));
     {
         StageTimer t(MEGS_STAGE_BLEND_BWD, s);
-        HIP_TRY(launch_blend_bwd(a, L.tile, waves_of(cfg), cfg->batch, persistent, s, cfg->subtile));
+        HIP_TRY(launch_blend_bwd(a, L.tile, cfg->waves, cfg->batch, persistent, s, cfg->subtile));
         if (grad_pair)
             HIP_TRY(launch_pair_reduce(static_cast<const uint32_t*>(st->det_order),
                                        static_cast<const uint32_t*>(st->det_offsets),

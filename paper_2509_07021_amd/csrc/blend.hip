@@ -328,6 +328,7 @@ __device__ __forceinline__ float dpp(float v) {  // lanes whose source lane is i
 }
 constexpr int kQuadXor1 = 0xb1, kQuadXor2 = 0x4e, kRowMirror = 0x140, kRowHalfMirror = 0x141;
 constexpr int kRowBcast15 = 0x142;  // lane 15 of the previous 16-lane row (rows 1-3)
+constexpr int kRowBcast31 = 0x143;  // lane 31 (rows 2-3)
 constexpr int kLaneSum8 = 63;       // the lane that ends with the wave total of v[8] in wave_sum9
 
 // Sum over one 8-lane group (every lane of the group ends with the total).
@@ -335,6 +336,15 @@ __device__ __forceinline__ float sum8(float y) {
     y += dpp<kQuadXor1>(y);
     y += dpp<kQuadXor2>(y);
     y += dpp<kRowHalfMirror>(y);
+    return y;
+}
+
+// Sum over the wave, in lane 63: within each 16-lane row, then across rows with the two row broadcasts.
+__device__ __forceinline__ float wave_sum(float y) {
+    y = sum8(y);
+    y += dpp<kRowMirror>(y);
+    y += dpp<kRowBcast15>(y);
+    y += dpp<kRowBcast31>(y);
     return y;
 }
 
@@ -632,15 +642,37 @@ __device__ __forceinline__ SubCtx sub_ctx(const BlendArgs& a, int64_t w, int til
     return q;
 }
 
-// FLAGS: the tile keys carry sub-tile flags (a.tkeys non-null), which decide which entries a
-// sub-tile keeps; without them each entry's footprint box is tested instead. A template argument, so
-// the flagged form (the default) carries no box code and no runtime test of the key pointer.
-template <bool STATS, bool IMP, bool FLAGS>
+// How a sub-tile kernel frames its entries and chooses the ones it keeps; a template argument, so each
+// form carries only its own tests.
+enum SubMode {
+    kSubFlags,   // the tile keys carry sub-tile flags (a.tkeys non-null), which decide; staged relative to
+                 // the sub-tile's corner
+    kSubReach,   // no flags: `reaches` decides; staged relative to the sub-tile's corner
+    kSubInTile,  // no flags: `reaches` decides; staged relative to the tile's corner, the frame of the
+                 // per-tile kernels, so that every alpha and every decision is bit for bit theirs (the
+                 // default launch of 16 x 16 and 32 x 32 tiles)
+};
+
+// May the staged entry reach a pixel centre of the 8 x 8 block whose corner is (bx, by) in its frame? No
+// when the cutoff ellipse's box misses the block, or when w1^2 + w2^2 exceeds log2(255 o) over the whole
+// block taking each factor's least size over it (exact for an upright ellipse). The limit is widened by
+// 0.2% and 0.01, far more than FP32 rounding moves w1 and w2 near it, so no entry with a pixel of alpha
+// >= 1/255 is dropped.
+__device__ __forceinline__ bool reaches(const Staged& s, int bx, int by) {
+    const float cx = bx + 4.0f, cy = by + 4.0f;
+    const float w1 = __fmaf_rn(s.p0.x, cx, __fmaf_rn(s.p0.y, cy, s.p0.z)), w2 = __fmaf_rn(s.p1.x, cy, s.p1.y);
+    const float m1 = fmaxf(fabsf(w1) - 3.5f * (fabsf(s.p0.x) + fabsf(s.p0.y)), 0.0f);
+    const float m2 = fmaxf(fabsf(w2) - 3.5f * fabsf(s.p1.x), 0.0f);
+    const float lim = __fmaf_rn(cutoff_of(s.p0.w), 0.5f * kLog2e, 0.01f);
+    return box_meets(s.box, bx, bx + 7, by, by + 7) & !(__fmaf_rn(m1, m1, m2 * m2) > lim);
+}
+
+template <bool STATS, bool IMP, SubMode MODE>
 __global__ __launch_bounds__(64) void k_blend_fwd_sub(BlendArgs a, int tile, int persistent) {
-    constexpr int SUB = 8;
+    constexpr bool FLAGS = MODE == kSubFlags;
     __shared__ Kept lds[64];
     const int lane = __lane_id();
-    const int64_t n_items = a.n_tiles * (int64_t)(tile / SUB) * (tile / SUB);
+    const int64_t n_items = a.n_tiles * (int64_t)(tile / 8) * (tile / 8);
     uint32_t n_blended = 0, n_evaluated = 0;
     Pull pull;
     for (int64_t w = next_item(a, -1, persistent, n_items, pull, true); w < n_items;
@@ -653,9 +685,11 @@ __global__ __launch_bounds__(64) void k_blend_fwd_sub(BlendArgs a, int tile, int
         float T = inside ? 1.0f : -1.0f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
         uint32_t last = 0;
         const uint2 rg = a.ranges[q.t];
-        // pixel centre relative to the sub-tile, the frame the entries are staged in
-        const float px = (lane & 7) + 0.5f, py = (lane >> 3) + 0.5f;
-        const double fx0 = (double)(c.x0 + q.sx), fy0 = (double)(c.y0 + q.sy);
+        // the frame the entries are staged in (the tile or the sub-tile): its corner, the sub-tile's corner
+        // in it, and the pixel centre in it
+        const int bx = MODE == kSubInTile ? q.sx : 0, by = MODE == kSubInTile ? q.sy : 0;
+        const double fx0 = (double)(c.x0 + q.sx - bx), fy0 = (double)(c.y0 + q.sy - by);
+        const float px = bx + (lane & 7) + 0.5f, py = by + (lane >> 3) + 0.5f;
         // each chunk's tile keys and record ids are loaded one chunk ahead, while the previous
         // chunk's entries are blended
         uint32_t key_n = 0, id_n = 0;
@@ -676,8 +710,7 @@ __global__ __launch_bounds__(64) void k_blend_fwd_sub(BlendArgs a, int tile, int
                 const bool flagged = !FLAGS || ((key >> (16 + q.sidx)) & 1u);
                 if (flagged) {
                     stage(a, g, fx0, fy0, &st, !FLAGS);
-                    // the flags already test the ellipse against the sub-tile; without them, its box
-                    hit = FLAGS ? true : box_meets(st.box, 0, SUB - 1, 0, SUB - 1);
+                    hit = FLAGS || reaches(st, bx, by);  // the flags already tested the ellipse
                 }
             }
             const uint64_t m = __ballot(hit);
@@ -720,10 +753,8 @@ __global__ __launch_bounds__(64) void k_blend_fwd_sub(BlendArgs a, int tile, int
                             last = incl ? s.pos1 : last;
                             if (STATS) n_blended += incl;
                             if (IMP) {
-                                float wsum = wgt;
-#pragma unroll
-                                for (int d = 32; d >= 1; d >>= 1) wsum += __shfl_xor(wsum, d);
-                                if (lane == 0 && wsum != 0.0f)
+                                const float wsum = wave_sum(wgt);
+                                if (lane == kWave - 1 && wsum != 0.0f)
                                     unsafeAtomicAdd(a.importance + ((int64_t)s.slot - (int64_t)c.view * a.n), wsum);
                             }
                         }
@@ -775,10 +806,10 @@ __global__ __launch_bounds__(64) void k_blend_fwd_sub(BlendArgs a, int tile, int
 // reload from scratch memory waits for the atomics before it (2.69 ms).
 constexpr int kGroup = 7;
 
-template <bool FLAGS>  // as in k_blend_fwd_sub
+template <SubMode MODE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_blend_bwd_sub(BlendArgs a, int tile,
                                                                                               int persistent) {
-    constexpr int SUB = 8;
+    constexpr bool FLAGS = MODE == kSubFlags;
     // the kept entries of a chunk behind up to kGroup - 1 carried over from the chunk before
     __shared__ Kept lds[64 + kGroup - 1];
     // rows[entry][pixel row][pixel]: a row's 64 bytes are four 16-byte pieces, stored in an order that
@@ -799,7 +830,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     // as adding lane: sum lane % 9 of entry lane / 9 (lane 63 adds nothing)
     const int add_entry = min(lane / 9, kGroup - 1), add_comp = lane % 9;
     const float4* const fin = reinterpret_cast<const float4*>(sums + min(lane, 9 * kGroup - 1) * 8);
-    const int64_t n_items = a.n_tiles * (int64_t)(tile / SUB) * (tile / SUB);
+    const int64_t n_items = a.n_tiles * (int64_t)(tile / 8) * (tile / 8);
     Pull pull;
     for (int64_t w = next_item(a, -1, persistent, n_items, pull, false); w < n_items;
          w = next_item(a, w, persistent, n_items, pull, false)) {
@@ -834,9 +865,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         dlr[1][lane] = dl1;
         dlr[2][lane] = dl2;
         const uint2 rg = a.ranges[q.t];
-        const float px = (lane & 7) + 0.5f, py = (lane >> 3) + 0.5f;  // relative to the sub-tile
-        const float row_y = sum_row + 0.5f;
-        const double fx0 = (double)(c.x0 + q.sx), fy0 = (double)(c.y0 + q.sy);
+        // the frame, as in the forward; the summing lane's pixel row in it
+        const int bx = MODE == kSubInTile ? q.sx : 0, by = MODE == kSubInTile ? q.sy : 0;
+        const double fx0 = (double)(c.x0 + q.sx - bx), fy0 = (double)(c.y0 + q.sy - by);
+        const float px = bx + (lane & 7) + 0.5f, py = by + (lane >> 3) + 0.5f;
+        const float row_y = by + sum_row + 0.5f;
         // The list is walked in chunks of 64 from position wave_last - 1 downwards, pipelined: a chunk's
         // tile keys and record ids are loaded two chunks ahead, and its records are gathered while the
         // chunk before it is replayed, and taken over before that chunk's first atomics leave (memory
@@ -861,8 +894,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
             hit = false;
             if (flagged) {
                 st = staged_of(raw, fx0, fy0, !FLAGS);
-                // the flags already test the ellipse against the sub-tile; without them, its box
-                hit = FLAGS ? true : box_meets(st.box, 0, SUB - 1, 0, SUB - 1);
+                hit = FLAGS || reaches(st, bx, by);  // the flags already tested the ellipse
             }
         };
         load_ids(first);
@@ -923,8 +955,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                     // rows of entries past the group's end or that no pixel includes hold older values:
                     // they are summed like the others and not added
                     const Kept& s = lds[min(k0 + sum_entry, todo - 1)];
-                    const float ax = s.p0.x, by = s.p1.x;
-                    const float wr = __fmaf_rn(s.p0.y, row_y, s.p0.z), w2 = __fmaf_rn(by, row_y, s.p1.y);
+                    const float ax = s.p0.x;
+                    float wr = __fmaf_rn(s.p0.y, row_y, s.p0.z);
+                    if (MODE == kSubInTile) wr = __fmaf_rn(ax, (float)bx, wr);
+                    const float w2 = __fmaf_rn(s.p1.x, row_y, s.p1.y);
                     float r0 = 0.f, r1 = 0.f;
                     acc[2] = 0.f; acc[6] = 0.f; acc[7] = 0.f; acc[8] = 0.f;
 #pragma unroll
@@ -1014,47 +1048,62 @@ hipError_t launch_bwd_t(const BlendArgs& a, int batch, bool persistent, hipStrea
     return hipGetLastError();
 }
 
-// The sub-tile flags' presence is a template argument, so the flagged form (the default) carries no
-// footprint-box code.
 template <bool STATS, bool IMP>
-void launch_fwd_sub_t(const BlendArgs& a, unsigned grid, int tile, bool persistent, hipStream_t stream) {
-    if (a.tkeys)
-        hipLaunchKernelGGL((k_blend_fwd_sub<STATS, IMP, true>), dim3(grid), dim3(64), 0, stream, a, tile, (int)persistent);
-    else
-        hipLaunchKernelGGL((k_blend_fwd_sub<STATS, IMP, false>), dim3(grid), dim3(64), 0, stream, a, tile,
-                           (int)persistent);
+void launch_fwd_sub_t(const BlendArgs& a, unsigned grid, int tile, SubMode mode, bool persistent, hipStream_t stream) {
+    if (mode == kSubFlags)
+        hipLaunchKernelGGL((k_blend_fwd_sub<STATS, IMP, kSubFlags>), dim3(grid), dim3(64), 0, stream, a, tile, (int)persistent);
+    else if (mode == kSubReach)
+        hipLaunchKernelGGL((k_blend_fwd_sub<STATS, IMP, kSubReach>), dim3(grid), dim3(64), 0, stream, a, tile, (int)persistent);
+    else if constexpr (!STATS)
+        hipLaunchKernelGGL((k_blend_fwd_sub<false, IMP, kSubInTile>), dim3(grid), dim3(64), 0, stream, a, tile, (int)persistent);
 }
 
-hipError_t launch_fwd_sub(const BlendArgs& a, int tile, bool persistent, hipStream_t stream) {
+hipError_t launch_fwd_sub(const BlendArgs& a, int tile, SubMode mode, bool persistent, hipStream_t stream) {
     const int64_t items = a.n_tiles * (int64_t)(tile / 8) * (tile / 8);
     const int64_t groups = persistent ? kPersistentGroups : items;
     const unsigned grid = (unsigned)(groups < items ? groups : items);
     if (a.importance)
-        launch_fwd_sub_t<false, true>(a, grid, tile, persistent, stream);
+        launch_fwd_sub_t<false, true>(a, grid, tile, mode, persistent, stream);
     else if (a.stats)
-        launch_fwd_sub_t<true, false>(a, grid, tile, persistent, stream);
+        launch_fwd_sub_t<true, false>(a, grid, tile, mode, persistent, stream);
     else
-        launch_fwd_sub_t<false, false>(a, grid, tile, persistent, stream);
+        launch_fwd_sub_t<false, false>(a, grid, tile, mode, persistent, stream);
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_sub(const BlendArgs& a, int tile, bool persistent, hipStream_t stream) {
+hipError_t launch_bwd_sub(const BlendArgs& a, int tile, SubMode mode, bool persistent, hipStream_t stream) {
     const int64_t items = a.n_tiles * (int64_t)(tile / 8) * (tile / 8);
     const int64_t groups = persistent ? kPersistentGroups : items;
     const unsigned grid = (unsigned)(groups < items ? groups : items);
-    if (a.tkeys)
-        hipLaunchKernelGGL((k_blend_bwd_sub<true>), dim3(grid), dim3(64), 0, stream, a, tile, (int)persistent);
+    if (mode == kSubFlags)
+        hipLaunchKernelGGL((k_blend_bwd_sub<kSubFlags>), dim3(grid), dim3(64), 0, stream, a, tile, (int)persistent);
+    else if (mode == kSubReach)
+        hipLaunchKernelGGL((k_blend_bwd_sub<kSubReach>), dim3(grid), dim3(64), 0, stream, a, tile, (int)persistent);
     else
-        hipLaunchKernelGGL((k_blend_bwd_sub<false>), dim3(grid), dim3(64), 0, stream, a, tile, (int)persistent);
+        hipLaunchKernelGGL((k_blend_bwd_sub<kSubInTile>), dim3(grid), dim3(64), 0, stream, a, tile, (int)persistent);
     return hipGetLastError();
 }
+
+// 16 x 16 and 32 x 32 tiles launched with waves = 0 (the library's choice) blend per sub-tile, in the
+// tile's frame, so that their results are those of the per-tile kernels (the forward's bit for bit): a wave
+// then walks only the entries that reach its 8 x 8 pixels, and no wave waits for another. The per-tile
+// kernels serve the wave counts a caller names, 8 x 8 tiles, the fragment statistics (they count tested
+// fragments) and the deterministic backward (one slot of sums per tile and entry).
+bool sub_in_tile(const BlendArgs& a, int tile, int waves) {
+    return waves == 0 && tile > 8 && !a.stats && !a.grad_pair;
+}
+
+int waves_or_default(int waves, int tile) { return waves ? waves : (tile == 8 ? 1 : 4); }
 
 }  // namespace
 
 hipError_t launch_blend_fwd(const BlendArgs& a, int tile, int waves, int batch, bool persistent, hipStream_t stream,
                             int subtile) {
     if (a.n_tiles <= 0) return hipSuccess;
-    if (subtile == 8 && tile > 8) return launch_fwd_sub(a, tile, persistent, stream);
+    if (subtile == 8 && tile > 8)
+        return launch_fwd_sub(a, tile, a.tkeys ? kSubFlags : kSubReach, persistent, stream);
+    if (sub_in_tile(a, tile, waves)) return launch_fwd_sub(a, tile, kSubInTile, persistent, stream);
+    waves = waves_or_default(waves, tile);
     if (tile == 8 && waves == 1) return launch_fwd_t<8, 1>(a, batch, persistent, stream);
     if (tile == 16 && waves == 1) return launch_fwd_t<16, 1>(a, batch, persistent, stream);
     if (tile == 16 && waves == 2) return launch_fwd_t<16, 2>(a, batch, persistent, stream);
@@ -1068,7 +1117,10 @@ hipError_t launch_blend_fwd(const BlendArgs& a, int tile, int waves, int batch, 
 hipError_t launch_blend_bwd(const BlendArgs& a, int tile, int waves, int batch, bool persistent, hipStream_t stream,
                             int subtile) {
     if (a.n_tiles <= 0) return hipSuccess;
-    if (subtile == 8 && tile > 8 && !a.grad_pair) return launch_bwd_sub(a, tile, persistent, stream);
+    if (subtile == 8 && tile > 8 && !a.grad_pair)
+        return launch_bwd_sub(a, tile, a.tkeys ? kSubFlags : kSubReach, persistent, stream);
+    if (sub_in_tile(a, tile, waves)) return launch_bwd_sub(a, tile, kSubInTile, persistent, stream);
+    waves = waves_or_default(waves, tile);
     if (tile == 8 && waves == 1) return launch_bwd_t<8, 1>(a, batch, persistent, stream);
     if (tile == 16 && waves == 1) return launch_bwd_t<16, 1>(a, batch, persistent, stream);
     if (tile == 16 && waves == 2) return launch_bwd_t<16, 2>(a, batch, persistent, stream);

@@ -405,7 +405,7 @@ struct BlendArgs {
     int64_t n;                  // Gaussians per view (record r of view v is Gaussian r - v n)
 };
 // subtile 8 (with 16 x 16 or 32 x 32 tiles): one independent wave per 8 x 8 sub-tile walking its
-// tile's list (the deterministic backward keeps the per-tile kernels).
+// tile's list (the deterministic backward keeps the per-tile kernels). waves 0: the library's choice.
 hipError_t launch_blend_fwd(const BlendArgs& a, int tile, int waves, int batch, bool persistent, hipStream_t stream,
                             int subtile);
 hipError_t launch_blend_bwd(const BlendArgs& a, int tile, int waves, int batch, bool persistent, hipStream_t stream,

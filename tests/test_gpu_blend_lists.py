@@ -1,10 +1,13 @@
 """Blending of short and odd lists: list lengths around the sub-tile backward's group of seven entries and
-the blends' chunks of 64 list positions, every stage against the oracle on a ragged image."""
+the blends' chunks of 64 list positions, every stage against the oracle on a ragged image; and the default
+launch (blended per sub-tile in the tile's frame) against the per-tile kernels, bit for bit."""
 import dataclasses
 
 import numpy as np
 import pytest
 
+from paper_2509_07021_amd import _lib as L
+from paper_2509_07021_amd import prune as P
 from paper_2509_07021_amd import render as R
 from paper_2509_07021_amd import scenes as S
 
@@ -24,8 +27,40 @@ def _faint_scene(n):
     return dataclasses.replace(sc, op_logit=(0.5 * sc.op_logit - 3.0 - 0.4 * np.log2(n)).clip(-4.5, None).astype(np.float32))
 
 
-@pytest.mark.parametrize("tile", [16, 32])
+@pytest.mark.parametrize("tile,subtile", [(16, 0), (32, 0), (16, 8), (32, 8)])
 @pytest.mark.parametrize("n", [1, 6, 7, 8, 14, 15, 63, 64, 65, 70, 71, 128, 134, 300])
-def test_list_lengths_at_group_and_chunk_edges(n, tile):
+def test_list_lengths_at_group_and_chunk_edges(n, tile, subtile):
     cams = [S.look_at((0.0, -4.0, 0.3), 21, 13, bg=(0.3, 0.1, 0.2))]
-    _run_all_stages(_faint_scene(n), cams, R.Config(tile, 64, subtile=8))
+    _run_all_stages(_faint_scene(n), cams, R.Config(tile, 64, subtile=subtile))
+
+
+@pytest.mark.parametrize("tile", [16, 32])
+@pytest.mark.parametrize("flags", [0, L.MEGS_FLAG_PERSISTENT, L.MEGS_FLAG_ONE_STAGE_SORT])
+def test_default_launch_matches_the_per_tile_kernels(tile, flags):
+    """waves = 0 against waves = 4 on uneven ragged views: images, final transmittances and last indices are
+    the same bits (the same decisions over the same lists); importance sums and gradients add the same
+    FP32 terms in another order, so each errs by at most a few roundings of its terms' absolute sum."""
+    scene, cams = S.make_workload("small_2k_128px")
+    cams = cams + [S.look_at((2.0, -3.0, 1.5), 101, 67, bg=(0.2, 0.3, 0.1)), S.look_at((0.2, -1.2, 0.1), 37, 41)]
+    ds = R.DeviceScene.from_scene(scene)
+    npix = sum(c.width * c.height for c in cams)
+    dl = torch.rand(3 * npix, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    out = []
+    for waves in (0, 4):
+        cfg = R.Config(tile, 64, flags=flags, waves=waves)
+        fr = R.forward(ds, cams, cfg)
+        imgs = [fr.images.clone(), fr.buffer("T_final", npix, torch.float32).clone(),
+                fr.buffer("last", npix, torch.int32).clone()]
+        grads = R.backward(ds, fr, dl)
+        imp_img, imp = P.importance(ds, cams, cfg)
+        out.append((imgs, grads, imp_img, imp))
+    (a, ga, ia, ma), (b, gb, ib, mb) = out
+    for x, y in zip(a, b):
+        assert torch.equal(x, y)
+    assert torch.equal(a[0], ia) and torch.equal(b[0], ib)
+    # weights are positive, so a sum of m of them in any order errs by less than m ulps of itself; a score
+    # adds at most a few thousand pixels, in partial sums of 64
+    assert torch.allclose(ma, mb, rtol=2e-5, atol=1e-7)
+    for p, g in ga.items():
+        if g is not None and g.numel():
+            assert float((g - gb[p]).norm() / gb[p].norm()) <= 1e-5, p
