@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <mutex>
 #include <new>
 #include <utility>
@@ -83,15 +84,104 @@ megs_status fail(megs_status s, const char* fmt, ...) {
         if (e_ != hipSuccess) return fail(MEGS_ERR_HIP, "%s failed: %s", #call, hipGetErrorString(e_));   \
     } while (0)
 
-constexpr int kViewChunk = 8;
+constexpr int kViewChunk = 16;
 struct ViewChunk {
     ViewInfo v[kViewChunk];
     int count;
 };
+static_assert(sizeof(ViewChunk) <= 3072, "a chunk travels as kernel arguments");
+
+// The first views of a forward, and its counters: [0] and [1] zero, [2] the record count; status zero.
+__global__ void k_begin(ViewInfo* dst, ViewChunk c, uint32_t* counters, int32_t* status, uint32_t n_records) {
+    const int t = threadIdx.x;
+    if (t < c.count) dst[t] = c.v[t];
+    if (t < 8) {
+        counters[t] = t == 2 ? n_records : 0u;
+        status[t] = 0;
+    }
+}
 
 __global__ void k_set_views(ViewInfo* dst, ViewChunk c) {
     if ((int)threadIdx.x < c.count) dst[threadIdx.x] = c.v[threadIdx.x];
 }
+
+// Slots of pinned host memory through which a kernel hands a counted total to the host that waits for it
+// (HostCount). One 4 KiB block for the process, portable over devices, its 64 slots lent to one call each;
+// a call that finds none, or whose stream is being captured, copies the words with the stream instead.
+// Measured on the eager forward of 2,000 Gaussians: two copies to pageable memory and the
+// synchronisation left the GPU idle for 100 us; the polled slot for 20 us.
+class HostSlots {
+public:
+    HostCount* take(uint32_t* seq) {
+        std::lock_guard<std::mutex> lock(mu_);
+        if (!base_ && !tried_) {
+            tried_ = true;
+            void* p = nullptr;
+            if (hipHostMalloc(&p, sizeof(HostCount) * kSlots, hipHostMallocPortable | hipHostMallocMapped |
+                                                                  hipHostMallocCoherent) == hipSuccess) {
+                memset(p, 0, sizeof(HostCount) * kSlots);
+                base_ = static_cast<HostCount*>(p);
+                for (int i = 0; i < kSlots; ++i) free_.push_back(i);
+            } else {
+                (void)hipGetLastError();
+            }
+        }
+        if (free_.empty()) return nullptr;
+        HostCount* s = base_ + free_.back();
+        free_.pop_back();
+        if (++seq_ == 0) ++seq_;
+        *seq = seq_;
+        return s;
+    }
+    void give(HostCount* s) {
+        std::lock_guard<std::mutex> lock(mu_);
+        free_.push_back((int)(s - base_));
+    }
+
+private:
+    static constexpr int kSlots = 64;
+    std::mutex mu_;
+    HostCount* base_ = nullptr;
+    bool tried_ = false;
+    std::vector<int> free_;
+    uint32_t seq_ = 0;
+};
+HostSlots g_slots;
+
+// One call's use of a slot: taken before the launches, waited for after them. A slot that was waited for
+// in vain is not lent again (a kernel might still write it).
+struct SlotUse {
+    HostCount* slot = nullptr;
+    uint32_t seq = 0;
+    hipStream_t stream;
+    explicit SlotUse(hipStream_t s) : stream(s) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        if (cap == hipStreamCaptureStatusNone) slot = g_slots.take(&seq);
+    }
+    // Polls for a while (the wait is normally tens of microseconds), then waits for the stream.
+    hipError_t wait(uint32_t* total, int32_t* bad_lobes) {
+        const auto t0 = std::chrono::steady_clock::now();
+        bool there = false;
+        while (!(there = __atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) == seq)) {
+            for (int i = 0; i < 32; ++i) __builtin_ia32_pause();
+            if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) break;
+        }
+        if (!there) {
+            const hipError_t e = hipStreamSynchronize(stream);
+            if (e != hipSuccess) return e;
+            if (__atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) != seq) return hipErrorUnknown;
+        }
+        *total = slot->total;
+        *bad_lobes = slot->bad_lobes;
+        g_slots.give(slot);
+        slot = nullptr;
+        return hipSuccess;
+    }
+};
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -418,25 +508,36 @@ Pairs carve_pairs(void* mem, int64_t cap, bool one_stage, bool det, char* alt) {
     return p;
 }
 
-megs_status upload_views(const Layout& L, ViewInfo* dst, hipStream_t s) {
+// The views and the counters' start values.
+megs_status begin(const Layout& L, Frame& f, hipStream_t s) {
     for (int v0 = 0; v0 < L.nv; v0 += kViewChunk) {
         ViewChunk ch;
         memset(&ch, 0, sizeof(ch));
         ch.count = L.nv - v0 < kViewChunk ? L.nv - v0 : kViewChunk;
         for (int i = 0; i < ch.count; ++i) ch.v[i] = L.views[v0 + i];
-        hipLaunchKernelGGL(k_set_views, dim3(1), dim3(kViewChunk), 0, s, dst + v0, ch);
+        if (v0 == 0)
+            hipLaunchKernelGGL(k_begin, dim3(1), dim3(64), 0, s, f.views, ch, f.counters, f.status, (uint32_t)L.nr);
+        else
+            hipLaunchKernelGGL(k_set_views, dim3(1), dim3(64), 0, s, f.views + v0, ch);
         HIP_TRY(hipGetLastError());
     }
     return MEGS_OK;
 }
 
-// Projection, depth pre-sort and tile-count scan (the part before the pair count is known).
-megs_status enqueue_front(const megs_scene* sc, const Layout& L, const megs_config* cfg, Frame& f, hipStream_t s) {
+// Projection, depth pre-sort and tile-count scan (the part before the pair count is known). slot: where the
+// host waits for the count, or null.
+megs_status enqueue_front(const megs_scene* sc, const Layout& L, const megs_config* cfg, Frame& f, hipStream_t s,
+                          const SlotUse* slot = nullptr) {
     const bool one_stage = cfg->flags & MEGS_FLAG_ONE_STAGE_SORT;
-    megs_status st = upload_views(L, f.views, s);
+    megs_status st = begin(L, f, s);
     if (st != MEGS_OK) return st;
-    HIP_TRY(launch_fill_u32(f.counters, 0u, 8, s));
-    HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(f.status), 0u, 8, s));
+    ScanTotal total;
+    total.total = f.counters + 0;
+    if (slot && slot->slot) {
+        total.host = slot->slot;
+        total.status = f.status;
+        total.seq = slot->seq;
+    }
     // Two-stage sort: the projection writes the depth sort's initial values with each record's tile
     // count above its id (when the id leaves at least 4 bits), so the scan after the sort reads the
     // counts in depth order without gathering them.
@@ -452,28 +553,25 @@ megs_status enqueue_front(const megs_scene* sc, const Layout& L, const megs_conf
     f.rec.order0 = nullptr;
     if (one_stage) {
         StageTimer t(MEGS_STAGE_SCAN, s);
-        HIP_TRY(launch_scan(f.rec.ntiles, nullptr, L.nr, f.offs, f.counters + 0, f.scan_scratch, s));
+        HIP_TRY(launch_scan(f.rec.ntiles, nullptr, L.nr, f.offs, total, f.scan_scratch, s));
+        return MEGS_OK;
+    }
+    if (packed) {
+        HIP_TRY(launch_sort_scan(f.rec.dkey, f.order, f.dkey_alt, f.order_alt, f.counters + 2, L.nr, f.rec.ntiles, idb,
+                                 f.offs, total, f.rs_scratch, f.scan_scratch, s));
         return MEGS_OK;
     }
     {
         StageTimer t(MEGS_STAGE_DEPTH_SORT, s);
-        if (!packed) HIP_TRY(launch_iota(f.order, L.nr, s));
-        HIP_TRY(launch_fill_u32(f.counters + 2, (uint32_t)L.nr, 1, s));
+        HIP_TRY(launch_iota(f.order, L.nr, s));
         bool alt = false;
         HIP_TRY(launch_radix_sort_u32(f.rec.dkey, f.order, f.dkey_alt, f.order_alt, f.counters + 2, L.nr, 0, 32,
                                       f.rs_scratch, s, &alt));
         if (alt) return fail(MEGS_ERR_HIP, "depth sort ended in the alternate buffer");
     }
-    {
-        StageTimer t(MEGS_STAGE_SCAN, s);
-        if (packed) {
-            HIP_TRY(launch_scan_packed(f.order, f.rec.ntiles, L.nr, idb, f.offs, f.counters + 0, f.scan_scratch, s));
-        } else {
-            // the depth keys' ping-pong buffer is free after the sort: it takes the gathered counts
-            HIP_TRY(launch_scan(f.rec.ntiles, f.order, L.nr, f.offs, f.counters + 0, f.scan_scratch, s,
-                                f.dkey_alt));
-        }
-    }
+    StageTimer t(MEGS_STAGE_SCAN, s);
+    // the depth keys' ping-pong buffer is free after the sort: it takes the gathered counts
+    HIP_TRY(launch_scan(f.rec.ntiles, f.order, L.nr, f.offs, total, f.scan_scratch, s, f.dkey_alt));
     return MEGS_OK;
 }
 
@@ -484,10 +582,9 @@ megs_status enqueue_back(const megs_scene* sc, const Layout& L, const megs_confi
     const bool persistent = cfg->flags & MEGS_FLAG_PERSISTENT;
     {
         StageTimer t(MEGS_STAGE_EMIT, s);
-        HIP_TRY(launch_clamp_count(f.counters + 0, p.capacity, f.counters + 1, f.status, s));
         HIP_TRY(launch_emit(f.rec, f.views, L.nv, L.n, L.tile, one_stage ? nullptr : f.order, f.offs, f.counters + 0,
-                            L.nr, p.tkeys,
-                            p.k64, p.vals, p.capacity, f.status, s, sub_masks(cfg, L) ? 8 : 0));
+                            L.nr, p.tkeys, p.k64, p.vals, p.capacity, f.status, f.counters + 1, f.ranges, L.n_tiles, s,
+                            sub_masks(cfg, L) ? 8 : 0));
     }
     const bool det = cfg->flags & MEGS_FLAG_DETERMINISTIC;
     if (det) {  // sort emission positions; the record ids are gathered back after the sort
@@ -521,7 +618,6 @@ megs_status enqueue_back(const megs_scene* sc, const Layout& L, const megs_confi
     }
     {
         StageTimer t(MEGS_STAGE_RANGES, s);
-        HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(f.ranges), 0u, 2 * L.n_tiles, s));
         if (one_stage)
             HIP_TRY(launch_ranges_u64(sorted_k, f.counters + 1, p.capacity, f.ranges, s));
         else
@@ -649,6 +745,29 @@ bool backward_reuses(const megs_config* cfg, const megs_state* st, size_t gbytes
     return work_reusable(cfg) && st->work && st->work_bytes >= (int64_t)gbytes;
 }
 
+// enqueue_front, then the host's wait for what it counted.
+megs_status front_and_count(const megs_scene* sc, const Layout& L, const megs_config* cfg, Frame& f, hipStream_t s,
+                            uint32_t* total, int32_t* bad_lobes) {
+    SlotUse slot(s);
+    const bool polled = slot.slot && L.nr > 0;  // (without records no scan runs)
+    if (slot.slot && !polled) {
+        g_slots.give(slot.slot);
+        slot.slot = nullptr;
+    }
+    const megs_status st = enqueue_front(sc, L, cfg, f, s, polled ? &slot : nullptr);
+    if (st != MEGS_OK) return st;
+    if (polled) {
+        HIP_TRY(slot.wait(total, bad_lobes));
+        return MEGS_OK;
+    }
+    int32_t flags[4] = {0, 0, 0, 0};
+    HIP_TRY(hipMemcpyAsync(total, f.counters, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(flags, f.status, sizeof(flags), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    *bad_lobes = flags[kStatusBadLobes];
+    return MEGS_OK;
+}
+
 // reserve_backward: size the frame's work space to take the backward's scratch as well (a backward
 // may follow); the pair sort's alternate buffers then also go there when they fit.
 megs_status forward_impl(const megs_scene* sc, const megs_camera* cams, int32_t nv, const megs_config* cfg,
@@ -666,17 +785,17 @@ megs_status forward_impl(const megs_scene* sc, const megs_camera* cams, int32_t 
     if (bad_alloc(fm))
         return fail(MEGS_ERR_ALLOC, "allocation of %zu bytes failed or not 256-byte aligned", frame_bytes(L, work));
     Frame f = carve_frame(fm, L, work);
-    st = enqueue_front(sc, L, cfg, f, s);
-    if (st != MEGS_OK) return st;
     int64_t cap = cfg->pair_capacity;
     int64_t counted = -1;
-    if (cap == 0) {
+    if (cap > 0) {
+        st = enqueue_front(sc, L, cfg, f, s);
+        if (st != MEGS_OK) return st;
+    } else {
         uint32_t total = 0;
-        int32_t flags[4] = {0, 0, 0, 0};
-        HIP_TRY(hipMemcpyAsync(&total, f.counters, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipMemcpyAsync(flags, f.status, sizeof(flags), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        if (flags[kStatusBadLobes]) return fail(MEGS_ERR_ARG, "malformed lobe_off (compressed-row lobes)");
+        int32_t bad_lobes = 0;
+        st = front_and_count(sc, L, cfg, f, s, &total, &bad_lobes);
+        if (st != MEGS_OK) return st;
+        if (bad_lobes) return fail(MEGS_ERR_ARG, "malformed lobe_off (compressed-row lobes)");
         if (total > kMaxPairs)
             return fail(MEGS_ERR_CAPACITY, "the records list %s%u tile pairs; a key table holds at most %u",
                         total == 0xffffffffu ? "at least " : "", total, kMaxPairs);
@@ -962,8 +1081,8 @@ megs_status megs_compact(const megs_scene* scene, double opacity_min, double sha
     HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(status), 0u, 8, s));
     HIP_TRY(launch_compact_mark(a, s));
     if (n > 0) {
-        HIP_TRY(launch_scan(a.keep, nullptr, n, a.new_idx, totals + 0, scan_scratch, s));
-        HIP_TRY(launch_scan(a.count, nullptr, n, a.lobe_pos, totals + 1, scan_scratch, s));
+        HIP_TRY(launch_scan(a.keep, nullptr, n, a.new_idx, ScanTotal{totals + 0}, scan_scratch, s));
+        HIP_TRY(launch_scan(a.count, nullptr, n, a.lobe_pos, ScanTotal{totals + 1}, scan_scratch, s));
     }
     uint32_t ht[2] = {0, 0};
     int32_t hs[4] = {0, 0, 0, 0};

@@ -343,17 +343,37 @@ hipError_t launch_project_bwd(const SceneDev& sc, const ViewInfo* views, int nv,
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t count, hipStream_t stream);
 hipError_t launch_iota(uint32_t* p, int64_t count, hipStream_t stream);
 
-// Exclusive scan of x[idx[i]] (idx may be null) for i < n (n given on host), writing out[i];
-// total written to *total (device). scratch: scan_scratch_bytes(n). With idx, `gathered` (n
-// entries, optional) receives the gathered values, which saves the second pass a gather.
+// A scan's grand total: to device memory, and, for a forward that waits for it, to host memory as well
+// (pinned, coherent): a slot whose sequence number the host gives out, written last.
+struct HostCount {
+    uint32_t total;
+    int32_t bad_lobes;
+    uint32_t seq;
+    uint32_t pad[13];  // one slot per 64 bytes
+};
+struct ScanTotal {
+    uint32_t* total = nullptr;
+    HostCount* host = nullptr;  // null: no host copy
+    const int32_t* status = nullptr;
+    uint32_t seq = 0;
+};
+
+// Exclusive scan of x[idx[i]] (idx may be null) for i < n (n given on host), writing out[i]; the grand
+// total as `total` asks (with n = 0 to device memory only). scratch: scan_scratch_bytes(n). With idx,
+// `gathered` (n entries, optional) receives the gathered values, which saves the second pass a gather.
 size_t scan_scratch_bytes(int64_t n);
+hipError_t launch_scan(const uint32_t* x, const uint32_t* idx, int64_t n, uint32_t* out, const ScanTotal& total,
+                       void* scratch, hipStream_t stream, uint32_t* gathered = nullptr);
 // The same scan over depth-sorted values that carry the tile count above the record id (see
 // Records::order0): counts come from the values themselves (ntiles[id] only for the escape value),
 // and the values are rewritten in place as bare record ids.
 hipError_t launch_scan_packed(uint32_t* order, const uint32_t* ntiles, int64_t n, int idb, uint32_t* out,
-                              uint32_t* total, void* scratch, hipStream_t stream);
-hipError_t launch_scan(const uint32_t* x, const uint32_t* idx, int64_t n, uint32_t* out, uint32_t* total,
-                       void* scratch, hipStream_t stream, uint32_t* gathered = nullptr);
+                              const ScanTotal& total, void* scratch, hipStream_t stream);
+// The depth sort of such values (n of them, *d_count = n) followed by that scan; the sorted keys are not
+// part of the result. One launch for few records.
+hipError_t launch_sort_scan(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
+                            const uint32_t* d_count, int64_t n, const uint32_t* ntiles, int idb, uint32_t* out,
+                            const ScanTotal& total, void* sort_scratch, void* scan_scratch, hipStream_t stream);
 
 // Stable LSD radix sort of (key, value) pairs on bits [begin_bit, end_bit). The element count is
 // read on device from *d_count (capped at max_count). Sorted output ends in keys/vals when
@@ -369,18 +389,17 @@ hipError_t launch_radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_
 
 // Key emission: for every record (in `order`, or index order when order is null) write its
 // tiles' keys at offsets[pos]; total: the scan's grand total (device). Two-stage: u32 global tile ids;
-// one-stage: u64 tile|depth keys. sub = 8: the upper 16 bits of each 32-bit tile key flag the 8 x 8
+// one-stage: u64 tile|depth keys. Also sets *count (the total clamped to the capacity), the status words of
+// the pair count, and every tile's range to empty. sub = 8: the upper 16 bits of each 32-bit tile key flag the 8 x 8
 // sub-tiles the record reaches (two-stage sort, tile ids below 2^16); sub = 0: plain tile ids.
 hipError_t launch_emit(const Records& rec, const ViewInfo* views, int nv, int64_t n, int tile,
                        const uint32_t* order, const uint32_t* offsets, const uint32_t* total, int64_t n_records,
                        uint32_t* tile_keys, uint64_t* keys64, uint32_t* vals, int64_t capacity,
-                       int32_t* status, hipStream_t stream, int sub);
+                       int32_t* status, uint32_t* count, uint2* ranges, int64_t n_tiles, hipStream_t stream, int sub);
 hipError_t launch_ranges_u32(const uint32_t* tile_keys, const uint32_t* d_count, int64_t max_count,
                              uint2* ranges, hipStream_t stream, uint32_t tmask);
 hipError_t launch_ranges_u64(const uint64_t* keys, const uint32_t* d_count, int64_t max_count,
                              uint2* ranges, hipStream_t stream);
-hipError_t launch_clamp_count(const uint32_t* total, int64_t capacity, uint32_t* count, int32_t* status,
-                              hipStream_t stream);
 
 struct BlendArgs {
     const ViewInfo* views;

@@ -147,7 +147,7 @@ hipError_t launch_select_topk(const float* score, int64_t n, int64_t kappa, void
         hipLaunchKernelGGL(k_select_pick, dim3(1), dim3(1), 0, stream, st, hist, shift);
     }
     hipLaunchKernelGGL(k_select_eq, dim3(grid_of(n)), dim3(256), 0, stream, score, n, st, eq);
-    hipError_t e = launch_scan(eq, nullptr, n, rank, hist, scan_scratch, stream);
+    hipError_t e = launch_scan(eq, nullptr, n, rank, ScanTotal{hist}, scan_scratch, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_select_keep, dim3(grid_of(n)), dim3(256), 0, stream, score, n, st, rank, keep);
     return hipGetLastError();

@@ -8,6 +8,12 @@
 // found with one 64-bit ballot per digit bit, and per-wave running counts live in LDS. There are no
 // inter-workgroup waits, so no pass depends on forward progress of other workgroups. The element
 // count is read on device, which lets the same launches run inside a captured graph.
+//
+// Small problems are bound by launches, not by bytes (a dependent launch costs 3 to 5 us between kernels
+// that run for 2): a sort of at most kSmallMax items is one workgroup and one launch, with the scan of
+// the tile counts in it; up to kFewBlocks workgroups a radix pass sums its count table itself instead of
+// launching the scan of its rows; and a scan of at most kFoldBlocks workgroups sums the workgroup totals
+// in its second pass.
 #include "megs_internal.hpp"
 
 namespace megs {
@@ -23,6 +29,13 @@ constexpr int kRsIpt = 16;
 constexpr int kRsTile = kRsThreads * kRsIpt;  // 4096
 constexpr int kRsDigits = 256;
 constexpr int kRsMaxBlocks = 2048;
+constexpr int kFewBlocks = 64;      // workgroups up to which a radix pass sums its count table itself
+constexpr int64_t kFoldBlocks = 1024;  // workgroups up to which a scan's second pass sums the totals
+
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallWaves = kSmallThreads / kWave;
+constexpr int kSmallIpt = 8;
+constexpr int64_t kSmallMax = (int64_t)kSmallThreads * kSmallIpt;  // items one workgroup sorts
 static_assert(kRsThreads == kRsDigits, "the downsweep maps one thread to one digit");
 
 __device__ __forceinline__ uint64_t lanemask_lt() {
@@ -90,6 +103,34 @@ __device__ __forceinline__ uint32_t scan_load(const uint32_t* x, const uint32_t*
     return x[idx ? idx[i] : i];
 }
 
+// The grand total of a scan, and, where the host waits for it (HostCount), its copy in host memory: the
+// total and the malformed-lobes flag first, then the sequence number that tells the host they are there.
+__device__ __forceinline__ void put_total(const ScanTotal& t, uint32_t total) {
+    if (t.total) *t.total = total;
+    if (t.host) {
+        t.host->total = total;
+        t.host->bad_lobes = t.status[kStatusBadLobes];
+        __hip_atomic_store(&t.host->seq, t.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// Sum of the workgroup totals before this workgroup (every thread receives it); the last workgroup also
+// hands out the grand total (saturated as in k_scan_top).
+__device__ __forceinline__ uint32_t fold_partials(const uint32_t* partial, const ScanTotal& t, uint64_t* lds64) {
+    uint64_t before = 0, all = 0;
+    for (int64_t i = threadIdx.x; i < gridDim.x; i += kScanThreads) {
+        const uint32_t v = partial[i];
+        all += v;
+        if (i < blockIdx.x) before += v;
+    }
+    before = block_sum64(before, lds64);
+    if (blockIdx.x == gridDim.x - 1) {  // uniform over the workgroup
+        all = block_sum64(all, lds64);
+        if (threadIdx.x == 0) put_total(t, sat32(all));
+    }
+    return (uint32_t)before;
+}
+
 // Per-workgroup totals. With an index list, the gathered values x[idx[i]] are also stored densely
 // to `gathered` (when given), so the second pass reads them without gathering again.
 __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t* x, const uint32_t* idx, int64_t n,
@@ -110,7 +151,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t* x,
 // Single workgroup: exclusive scan of partial[0..m) in place; writes the grand total, saturated at
 // 0xffffffff (sat32: a total 32 bits cannot hold, which the pair count check then refuses; the 32-bit
 // offsets written here are then meaningless).
-__global__ __launch_bounds__(kScanThreads) void k_scan_top(uint32_t* partial, int64_t m, uint32_t* total_out) {
+__global__ __launch_bounds__(kScanThreads) void k_scan_top(uint32_t* partial, int64_t m, ScanTotal out) {
     __shared__ uint32_t lds[4];
     __shared__ uint64_t lds64[4];
     uint32_t carry = 0;
@@ -135,12 +176,16 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_top(uint32_t* partial, in
         carry += total;
         carry64 += block_sum64(s64, lds64);
     }
-    if (threadIdx.x == 0 && total_out) *total_out = sat32(carry64);
+    if (threadIdx.x == 0) put_total(out, sat32(carry64));
 }
 
+// FOLD: the workgroup totals are as k_scan_reduce left them (not scanned), and fold_partials sums them.
+template <bool FOLD>
 __global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t* x, const uint32_t* idx, int64_t n,
-                                                            const uint32_t* partial, uint32_t* out) {
+                                                            const uint32_t* partial, uint32_t* out, ScanTotal t) {
     __shared__ uint32_t lds[4];
+    __shared__ uint64_t lds64[4];
+    const uint32_t first = FOLD ? fold_partials(partial, t, lds64) : partial[blockIdx.x];
     const int64_t base = (int64_t)blockIdx.x * kScanTile + threadIdx.x * kScanIpt;
     uint32_t v[kScanIpt];
     uint32_t s = 0;
@@ -149,7 +194,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t* x, c
         s += v[j];
     }
     uint32_t total;
-    uint32_t ex = block_excl_scan256(s, lds, total) + partial[blockIdx.x];
+    uint32_t ex = block_excl_scan256(s, lds, total) + first;
     for (int j = 0; j < kScanIpt; ++j) {
         if (base + j < n) out[base + j] = ex;
         ex += v[j];
@@ -183,9 +228,12 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_reduce_packed(const uint3
     if (threadIdx.x == 0) partial[blockIdx.x] = sat32(total);
 }
 
+template <bool FOLD>  // as in k_scan_down
 __global__ __launch_bounds__(kScanThreads) void k_scan_down_packed(uint32_t* order, const uint32_t* ntiles, int64_t n,
-                                                                   int idb, const uint32_t* partial, uint32_t* out) {
+                                                                   int idb, const uint32_t* partial, uint32_t* out,
+                                                                   ScanTotal t) {
     __shared__ uint32_t lds[4];
+    __shared__ uint64_t lds64[4];
     static_assert(kScanIpt == 8, "a thread's items are two 16-byte vectors");
     // a thread's 8 consecutive items move as two 16-byte vectors (order and out are 256-byte
     // aligned and base is a multiple of 8), so every access of the wave is contiguous
@@ -208,8 +256,9 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down_packed(uint32_t* ord
         s += v[j];
         w[j] &= idmask;
     }
+    const uint32_t first = FOLD ? fold_partials(partial, t, lds64) : partial[blockIdx.x];
     uint32_t total;
-    uint32_t ex = block_excl_scan256(s, lds, total) + partial[blockIdx.x];
+    uint32_t ex = block_excl_scan256(s, lds, total) + first;
     uint32_t o[kScanIpt];
 #pragma unroll
     for (int j = 0; j < kScanIpt; ++j) {
@@ -269,7 +318,8 @@ __device__ __forceinline__ Chunk chunk_of(const uint32_t* d_count, int64_t max_c
     return c;
 }
 
-template <typename K>
+// FEW: the count table is [G][256] and the downsweep sums it; else [256][G], scanned by k_radix_scan_rows.
+template <typename K, bool FEW>
 __global__ __launch_bounds__(kRsThreads) void k_radix_upsweep(const K* __restrict__ keys, const uint32_t* d_count,
                                                               int64_t max_count, int shift, uint32_t mask,
                                                               uint32_t* __restrict__ counts) {
@@ -319,7 +369,7 @@ __global__ __launch_bounds__(kRsThreads) void k_radix_upsweep(const K* __restric
         uint32_t s = 0;
         for (int ww = 0; ww < kRsWaves; ++ww)
             for (int cc = 0; cc < kCopies; ++cc) s += hist[ww][cc * kStride + d];
-        counts[(int64_t)d * gridDim.x + blockIdx.x] = s;
+        counts[FEW ? (int64_t)blockIdx.x * kRsDigits + d : (int64_t)d * gridDim.x + blockIdx.x] = s;
     }
 }
 
@@ -349,7 +399,7 @@ __global__ __launch_bounds__(kScanThreads) void k_radix_scan_rows(uint32_t* coun
     if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
-template <typename K>
+template <typename K, bool FEW>
 __global__ __launch_bounds__(kRsThreads) void k_radix_downsweep(const K* __restrict__ keys_in,
                                                                 const uint32_t* __restrict__ vals_in,
                                                                 K* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
@@ -365,15 +415,31 @@ __global__ __launch_bounds__(kRsThreads) void k_radix_downsweep(const K* __restr
     __shared__ K stage_k[kRsTile];
     __shared__ uint32_t stage_v[kRsTile];
     const int w = threadIdx.x / kWave, lane = __lane_id();
+    uint32_t digit_total;
     {
-        // digit base = exclusive prefix of the digit totals (thread = digit)
+        // digit base = exclusive prefix of the digit totals (thread = digit), plus the digit's keys in the
+        // workgroups before this one
+        uint32_t before = 0;
+        if (FEW) {
+            digit_total = 0;
+            const uint32_t* col = offsets + threadIdx.x;
+#pragma unroll 8
+            for (uint32_t b = 0; b < gridDim.x; ++b) {
+                const uint32_t v = col[b * kRsDigits];
+                digit_total += v;
+                before += b < blockIdx.x ? v : 0u;
+            }
+        } else {
+            digit_total = totals[threadIdx.x];
+            before = offsets[(int64_t)threadIdx.x * gridDim.x + blockIdx.x];
+        }
         uint32_t all;
-        const uint32_t digit_base = block_excl_scan256(totals[threadIdx.x], lds4, all);
-        run_off[threadIdx.x] = digit_base + offsets[(int64_t)threadIdx.x * gridDim.x + blockIdx.x];
+        const uint32_t digit_base = block_excl_scan256(digit_total, lds4, all);
+        run_off[threadIdx.x] = digit_base + before;
     }
     const Chunk c = chunk_of(d_count, max_count);
     // a pass whose digit is the same for every key is the identity permutation: copy the chunk
-    if (__syncthreads_or(totals[threadIdx.x] == (uint32_t)c.n && c.n > 0)) {
+    if (__syncthreads_or(digit_total == (uint32_t)c.n && c.n > 0)) {
         const int64_t i1 = c.t1 * kRsTile < c.n ? c.t1 * kRsTile : c.n;
         for (int64_t i = c.t0 * kRsTile + threadIdx.x; i < i1; i += kRsThreads) {
             keys_out[i] = keys_in[i];
@@ -443,29 +509,180 @@ __global__ __launch_bounds__(kRsThreads) void k_radix_downsweep(const K* __restr
     }
 }
 
+// One workgroup sorts up to kSmallMax pairs in LDS: the same stable LSD passes with the items in registers
+// between two barriers, each wave owning a contiguous segment. Passes whose digit all keys share are
+// skipped. SCAN: the values are the depth sort's packed ones (k_scan_reduce_packed), and the launch also
+// rewrites them as bare ids and writes the exclusive scan of their counts and its total; the sorted keys
+// are not written. On 2,000 records of one 128 x 128 view the depth sort and scan take one launch of 12 us
+// instead of fifteen (100 us of the GPU's time with the gaps between them).
+template <bool SCAN>
+__global__ __launch_bounds__(kSmallThreads) void k_sort_small(uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
+                                                              const uint32_t* d_count, int64_t max_count, int begin_bit,
+                                                              int end_bit, int width, const uint32_t* ntiles, int idb,
+                                                              uint32_t* __restrict__ offs, ScanTotal out) {
+    __shared__ uint32_t sk[kSmallMax], sv[kSmallMax];
+    __shared__ uint32_t whist[kSmallWaves][kRsDigits];
+    __shared__ uint32_t start[kRsDigits];
+    __shared__ uint32_t red[2][kSmallWaves];
+    __shared__ uint64_t red64[kSmallWaves];
+    const int tid = threadIdx.x, w = tid / kWave, lane = __lane_id();
+    const int n = (int)min((int64_t)*d_count, max_count);
+    uint32_t all1 = ~0u, any1 = 0u;  // the bits every key has, and the bits some key has
+    for (int i = tid; i < n; i += kSmallThreads) {
+        const uint32_t k = keys[i];
+        sk[i] = k;
+        sv[i] = vals[i];
+        all1 &= k;
+        any1 |= k;
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        all1 &= (uint32_t)__shfl_xor((int)all1, d);
+        any1 |= (uint32_t)__shfl_xor((int)any1, d);
+    }
+    if (lane == 0) {
+        red[0][w] = all1;
+        red[1][w] = any1;
+    }
+    __syncthreads();
+    for (int i = 0; i < kSmallWaves; ++i) {
+        all1 &= red[0][i];
+        any1 |= red[1][i];
+    }
+    const uint32_t differ = n > 0 ? all1 ^ any1 : 0u;
+    const int ipt = (n + kSmallThreads - 1) / kSmallThreads;  // 64-item steps of a wave's segment
+    const uint64_t lt = lanemask_lt();
+    for (int shift = begin_bit; shift < end_bit; shift += width) {
+        const int bits = min(end_bit - shift, width);
+        const uint32_t mask = (1u << bits) - 1u;
+        if (!((differ >> shift) & mask)) continue;
+        for (int i = tid; i < kSmallWaves * kRsDigits; i += kSmallThreads) (&whist[0][0])[i] = 0u;
+        __syncthreads();
+        uint32_t key[kSmallIpt], val[kSmallIpt], rank[kSmallIpt];
+#pragma unroll
+        for (int j = 0; j < kSmallIpt; ++j) {
+            if (j >= ipt) break;
+            const int idx = (w * ipt + j) * kWave + lane;
+            const bool ok = idx < n;
+            key[j] = ok ? sk[idx] : 0u;
+            val[j] = ok ? sv[idx] : 0u;
+            const uint32_t d = digit_of(key[j], shift, mask);
+            const uint64_t peers = match_digit(d, __ballot(ok), mask);
+            uint32_t before = 0;
+            if (ok) before = whist[w][d];
+            rank[j] = before + (uint32_t)__popcll(peers & lt);
+            if (ok && (__ffsll((unsigned long long)peers) - 1) == lane) whist[w][d] = before + (uint32_t)__popcll(peers);
+        }
+        __syncthreads();
+        // per digit (thread = digit): exclusive prefix over waves and over the digits before it
+        uint32_t total_d = 0, inc = 0;
+        if (tid < kRsDigits) {
+            for (int ww = 0; ww < kSmallWaves; ++ww) {
+                const uint32_t cnt = whist[ww][tid];
+                whist[ww][tid] = total_d;
+                total_d += cnt;
+            }
+            inc = wave_incl_scan(total_d);
+            if (lane == kWave - 1) red[0][w] = inc;
+        }
+        __syncthreads();
+        if (tid < kRsDigits) {
+            uint32_t base = 0;
+            for (int i = 0; i < w; ++i) base += red[0][i];
+            start[tid] = base + inc - total_d;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kSmallIpt; ++j) {
+            if (j >= ipt) break;
+            if ((w * ipt + j) * kWave + lane < n) {
+                const uint32_t d = digit_of(key[j], shift, mask);
+                const uint32_t pos = start[d] + whist[w][d] + rank[j];
+                sk[pos] = key[j];
+                sv[pos] = val[j];
+            }
+        }
+        __syncthreads();
+    }
+    if (!SCAN) {
+        for (int i = tid; i < n; i += kSmallThreads) {
+            keys[i] = sk[i];
+            vals[i] = sv[i];
+        }
+        return;
+    }
+    // items tid * ipt .. tid * ipt + ipt - 1 of the sorted order
+    uint32_t c[kSmallIpt], sum = 0;
+    uint64_t sum64 = 0;
+    for (int j = 0; j < ipt; ++j) {
+        const int i = tid * ipt + j;
+        c[j] = i < n ? packed_count(sv[i], ntiles, idb) : 0u;
+        sum += c[j];
+        sum64 += c[j];
+    }
+    const uint32_t inc = wave_incl_scan(sum);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) sum64 += __shfl_xor(sum64, d);
+    if (lane == kWave - 1) {
+        red[0][w] = inc;
+        red64[w] = sum64;
+    }
+    __syncthreads();
+    uint32_t ex = inc - sum;
+    for (int i = 0; i < w; ++i) ex += red[0][i];
+    for (int j = 0; j < ipt; ++j) {
+        const int i = tid * ipt + j;
+        if (i < n) {
+            vals[i] = sv[i] & ((1u << idb) - 1u);
+            offs[i] = ex;
+        }
+        ex += c[j];
+    }
+    if (tid == 0) {
+        uint64_t all = 0;
+        for (int i = 0; i < kSmallWaves; ++i) all += red64[i];
+        put_total(out, sat32(all));
+    }
+}
+
 template <typename K>
 hipError_t radix_sort(K* keys, uint32_t* vals, K* keys_alt, uint32_t* vals_alt, const uint32_t* d_count,
                       int64_t max_count, int begin_bit, int end_bit, void* scratch, hipStream_t stream, bool* in_alt) {
     *in_alt = false;
     if (max_count <= 0 || end_bit <= begin_bit) return hipSuccess;
+    // the fewest passes of at most 8 bits, with the bits spread evenly over them (14 tile bits sort
+    // as 7 + 7: fewer digits per pass give each digit longer runs in the scatter)
+    const int passes = radix_passes(begin_bit, end_bit);
+    const int width = (end_bit - begin_bit + passes - 1) / passes;
+    if constexpr (sizeof(K) == 4) {
+        if (max_count <= kSmallMax) {  // in place
+            hipLaunchKernelGGL(k_sort_small<false>, dim3(1), dim3(kSmallThreads), 0, stream, keys, vals, d_count,
+                               max_count, begin_bit, end_bit, width, static_cast<const uint32_t*>(nullptr), 0,
+                               static_cast<uint32_t*>(nullptr), ScanTotal{});
+            return hipGetLastError();
+        }
+    }
     int64_t tiles = (max_count + kRsTile - 1) / kRsTile;
     const int G = (int)(tiles < kRsMaxBlocks ? tiles : kRsMaxBlocks);
     uint32_t* counts = static_cast<uint32_t*>(scratch);
     uint32_t* totals = counts + (int64_t)kRsDigits * G;
     K* src_k = keys; uint32_t* src_v = vals;
     K* dst_k = keys_alt; uint32_t* dst_v = vals_alt;
-    // the fewest passes of at most 8 bits, with the bits spread evenly over them (14 tile bits sort
-    // as 7 + 7: fewer digits per pass give each digit longer runs in the scatter)
-    const int passes = radix_passes(begin_bit, end_bit);
-    const int width = (end_bit - begin_bit + passes - 1) / passes;
     for (int shift = begin_bit; shift < end_bit; shift += width) {
         const int bits = end_bit - shift < width ? end_bit - shift : width;
         const uint32_t mask = (1u << bits) - 1u;
-        hipLaunchKernelGGL(k_radix_upsweep<K>, dim3(G), dim3(kRsThreads), 0, stream, src_k, d_count, max_count, shift,
-                           mask, counts);
-        hipLaunchKernelGGL(k_radix_scan_rows, dim3(kRsDigits), dim3(kScanThreads), 0, stream, counts, G, totals);
-        hipLaunchKernelGGL(k_radix_downsweep<K>, dim3(G), dim3(kRsThreads), 0, stream, src_k, src_v, dst_k, dst_v,
-                           d_count, max_count, shift, mask, counts, totals);
+        if (G <= kFewBlocks) {
+            hipLaunchKernelGGL((k_radix_upsweep<K, true>), dim3(G), dim3(kRsThreads), 0, stream, src_k, d_count,
+                               max_count, shift, mask, counts);
+            hipLaunchKernelGGL((k_radix_downsweep<K, true>), dim3(G), dim3(kRsThreads), 0, stream, src_k, src_v, dst_k,
+                               dst_v, d_count, max_count, shift, mask, counts, totals);
+        } else {
+            hipLaunchKernelGGL((k_radix_upsweep<K, false>), dim3(G), dim3(kRsThreads), 0, stream, src_k, d_count,
+                               max_count, shift, mask, counts);
+            hipLaunchKernelGGL(k_radix_scan_rows, dim3(kRsDigits), dim3(kScanThreads), 0, stream, counts, G, totals);
+            hipLaunchKernelGGL((k_radix_downsweep<K, false>), dim3(G), dim3(kRsThreads), 0, stream, src_k, src_v, dst_k,
+                               dst_v, d_count, max_count, shift, mask, counts, totals);
+        }
         K* tk = src_k; src_k = dst_k; dst_k = tk;
         uint32_t* tv = src_v; src_v = dst_v; dst_v = tv;
         *in_alt = !*in_alt;
@@ -554,6 +771,24 @@ __device__ __forceinline__ uint64_t band_mask(int c0, int c1, int first, int nbi
     return lo <= hi ? upto & ~below : 0ull;
 }
 
+// The pair count the sort and ranges read, clamped to the table's capacity; the counted total goes to
+// status[0] (saturated at 2^31 - 1), and status[1] flags a total beyond the capacity or beyond 2^31 - 1
+// pairs (kMaxPairs: the tables' 32-bit positions and the status word hold no more).
+__device__ __forceinline__ void clamp_count(uint32_t t, int64_t capacity, uint32_t* count, int32_t* status) {
+    const bool over = (int64_t)t > capacity || t > kMaxPairs;
+    *count = over ? (uint32_t)(capacity < (int64_t)kMaxPairs ? capacity : (int64_t)kMaxPairs) : t;
+    status[0] = (int32_t)(t > kMaxPairs ? kMaxPairs : t);
+    if (over) status[1] = 1;
+}
+
+// The same without records to emit.
+__global__ void k_no_pairs(const uint32_t* total, int64_t capacity, uint32_t* count, int32_t* status,
+                           uint2* __restrict__ ranges, int64_t n_tiles) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) clamp_count(*total, capacity, count, status);
+    for (int64_t j = i; j < n_tiles; j += (int64_t)gridDim.x * blockDim.x) ranges[j] = make_uint2(0u, 0u);
+}
+
 // S: sub-tiles per tile edge when the keys carry sub-tile flags (tile = 8 S), 0 without flags.
 template <int S>
 __global__ __launch_bounds__(kEmitThreads) void k_emit(Records rec, const ViewInfo* __restrict__ views, int64_t n,
@@ -561,7 +796,12 @@ __global__ __launch_bounds__(kEmitThreads) void k_emit(Records rec, const ViewIn
                                                        const uint32_t* __restrict__ offsets,
                                                        const uint32_t* __restrict__ total, int64_t n_records,
                                                        uint32_t* __restrict__ tile_keys, uint64_t* __restrict__ keys64,
-                                                       uint32_t* __restrict__ vals, int64_t capacity, int32_t* status) {
+                                                       uint32_t* __restrict__ vals, int64_t capacity, int32_t* status,
+                                                       uint32_t* count, uint2* __restrict__ ranges, int64_t n_tiles) {
+    // what the launches after this one need set up: the clamped pair count and empty tile ranges
+    if (blockIdx.x == 0 && threadIdx.x == 0) clamp_count(*total, capacity, count, status);
+    for (int64_t i = (int64_t)blockIdx.x * kEmitThreads + threadIdx.x; i < n_tiles; i += (int64_t)gridDim.x * kEmitThreads)
+        ranges[i] = make_uint2(0u, 0u);
     constexpr int SUB = 8;
     constexpr int kBuckets = 64;  // tile counts >= 63 share the last bucket
     __shared__ uint32_t w_tile[kEmitWindow];
@@ -773,17 +1013,6 @@ __global__ void k_pair_reduce(const uint32_t* __restrict__ order, const uint32_t
     for (int c = 0; c < 9; ++c) grad2d[grad2d_index(r, c)] = acc[c];
 }
 
-// The pair count the sort and ranges read, clamped to the table's capacity; the counted total goes to
-// status[0] (saturated at 2^31 - 1), and status[1] flags a total beyond the capacity or beyond 2^31 - 1
-// pairs (kMaxPairs: the tables' 32-bit positions and the status word hold no more).
-__global__ void k_clamp_count(const uint32_t* total, int64_t capacity, uint32_t* count, int32_t* status) {
-    const uint32_t t = *total;
-    const bool over = (int64_t)t > capacity || t > kMaxPairs;
-    *count = over ? (uint32_t)(capacity < (int64_t)kMaxPairs ? capacity : (int64_t)kMaxPairs) : t;
-    status[0] = (int32_t)(t > kMaxPairs ? kMaxPairs : t);
-    if (over) status[1] = 1;
-}
-
 template <typename K>
 __global__ void k_ranges(const K* __restrict__ keys, int shift, uint32_t tmask, const uint32_t* d_count,
                          int64_t max_count, uint2* __restrict__ ranges) {
@@ -872,37 +1101,67 @@ size_t scan_scratch_bytes(int64_t n) {
     return (size_t)((blocks > 0 ? blocks : 1) * sizeof(uint32_t));
 }
 
-hipError_t launch_scan(const uint32_t* x, const uint32_t* idx, int64_t n, uint32_t* out, uint32_t* total,
+hipError_t launch_scan(const uint32_t* x, const uint32_t* idx, int64_t n, uint32_t* out, const ScanTotal& total,
                        void* scratch, hipStream_t stream, uint32_t* gathered) {
-    if (n <= 0) {
-        return launch_fill_u32(total, 0u, 1, stream);
-    }
+    if (n <= 0) return launch_fill_u32(total.total, 0u, 1, stream);
     const int64_t blocks = (n + kScanTile - 1) / kScanTile;
     uint32_t* partial = static_cast<uint32_t*>(scratch);
     uint32_t* g = idx ? gathered : nullptr;
     hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)blocks), dim3(kScanThreads), 0, stream, x, idx, n, partial, g);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanThreads), 0, stream, partial, blocks, total);
-    if (g)
-        hipLaunchKernelGGL(k_scan_down, dim3((unsigned)blocks), dim3(kScanThreads), 0, stream,
-                           static_cast<const uint32_t*>(g), static_cast<const uint32_t*>(nullptr), n, partial, out);
+    const bool fold = blocks <= kFoldBlocks;
+    if (!fold) hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanThreads), 0, stream, partial, blocks, total);
+    if (g) {
+        x = g;
+        idx = nullptr;
+    }
+    if (fold)
+        hipLaunchKernelGGL(k_scan_down<true>, dim3((unsigned)blocks), dim3(kScanThreads), 0, stream, x, idx, n, partial,
+                           out, total);
     else
-        hipLaunchKernelGGL(k_scan_down, dim3((unsigned)blocks), dim3(kScanThreads), 0, stream, x, idx, n, partial,
-                           out);
+        hipLaunchKernelGGL(k_scan_down<false>, dim3((unsigned)blocks), dim3(kScanThreads), 0, stream, x, idx, n, partial,
+                           out, total);
     return hipGetLastError();
 }
 
 hipError_t launch_scan_packed(uint32_t* order, const uint32_t* ntiles, int64_t n, int idb, uint32_t* out,
-                              uint32_t* total, void* scratch, hipStream_t stream) {
-    if (n <= 0) return launch_fill_u32(total, 0u, 1, stream);
+                              const ScanTotal& total, void* scratch, hipStream_t stream) {
+    if (n <= 0) return launch_fill_u32(total.total, 0u, 1, stream);
     if (idb < 1 || idb > 28) return hipErrorInvalidValue;
     const int64_t blocks = (n + kScanTile - 1) / kScanTile;
     uint32_t* partial = static_cast<uint32_t*>(scratch);
     hipLaunchKernelGGL(k_scan_reduce_packed, dim3((unsigned)blocks), dim3(kScanThreads), 0, stream, order, ntiles, n,
                        idb, partial);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanThreads), 0, stream, partial, blocks, total);
-    hipLaunchKernelGGL(k_scan_down_packed, dim3((unsigned)blocks), dim3(kScanThreads), 0, stream, order, ntiles, n,
-                       idb, partial, out);
+    if (blocks <= kFoldBlocks) {
+        hipLaunchKernelGGL(k_scan_down_packed<true>, dim3((unsigned)blocks), dim3(kScanThreads), 0, stream, order, ntiles,
+                           n, idb, partial, out, total);
+    } else {
+        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanThreads), 0, stream, partial, blocks, total);
+        hipLaunchKernelGGL(k_scan_down_packed<false>, dim3((unsigned)blocks), dim3(kScanThreads), 0, stream, order,
+                           ntiles, n, idb, partial, out, total);
+    }
     return hipGetLastError();
+}
+
+hipError_t launch_sort_scan(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
+                            const uint32_t* d_count, int64_t n, const uint32_t* ntiles, int idb, uint32_t* out,
+                            const ScanTotal& total, void* sort_scratch, void* scan_scratch, hipStream_t stream) {
+    if (n <= 0) return launch_fill_u32(total.total, 0u, 1, stream);
+    if (idb < 1 || idb > 28) return hipErrorInvalidValue;
+    if (n <= kSmallMax) {
+        StageTimer t(MEGS_STAGE_DEPTH_SORT, stream);
+        hipLaunchKernelGGL(k_sort_small<true>, dim3(1), dim3(kSmallThreads), 0, stream, keys, vals, d_count, n, 0, 32, 8,
+                           ntiles, idb, out, total);
+        return hipGetLastError();
+    }
+    {
+        StageTimer t(MEGS_STAGE_DEPTH_SORT, stream);
+        bool alt = false;
+        const hipError_t e = radix_sort<uint32_t>(keys, vals, keys_alt, vals_alt, d_count, n, 0, 32, sort_scratch, stream, &alt);
+        if (e != hipSuccess) return e;
+        if (alt) return hipErrorUnknown;  // four passes end where they began
+    }
+    StageTimer t(MEGS_STAGE_SCAN, stream);
+    return launch_scan_packed(vals, ntiles, n, idb, out, total, scan_scratch, stream);
 }
 
 // The fewest passes of at most 8 bits over [begin_bit, end_bit); the sorted data ends in the
@@ -932,20 +1191,24 @@ hipError_t launch_radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_
 hipError_t launch_emit(const Records& rec, const ViewInfo* views, int nv, int64_t n, int tile,
                        const uint32_t* order, const uint32_t* offsets, const uint32_t* total, int64_t n_records,
                        uint32_t* tile_keys, uint64_t* keys64, uint32_t* vals, int64_t capacity,
-                       int32_t* status, hipStream_t stream, int sub) {
+                       int32_t* status, uint32_t* count, uint2* ranges, int64_t n_tiles, hipStream_t stream, int sub) {
     (void)nv;
-    if (n_records <= 0) return hipSuccess;
+    if (n_records <= 0) {
+        hipLaunchKernelGGL(k_no_pairs, dim3(grid_for(n_tiles, 256, 1024)), dim3(256), 0, stream, total, capacity, count,
+                           status, ranges, n_tiles);
+        return hipGetLastError();
+    }
     if (sub && (sub != 8 || !tile_keys || (tile != 16 && tile != 32))) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((n_records + kEmitThreads - 1) / kEmitThreads));
     if (!sub)
         hipLaunchKernelGGL(k_emit<0>, grid, dim3(kEmitThreads), 0, stream, rec, views, n, tile, order, offsets,
-                           total, n_records, tile_keys, keys64, vals, capacity, status);
+                           total, n_records, tile_keys, keys64, vals, capacity, status, count, ranges, n_tiles);
     else if (tile == 16)
         hipLaunchKernelGGL(k_emit<2>, grid, dim3(kEmitThreads), 0, stream, rec, views, n, tile, order, offsets,
-                           total, n_records, tile_keys, keys64, vals, capacity, status);
+                           total, n_records, tile_keys, keys64, vals, capacity, status, count, ranges, n_tiles);
     else
         hipLaunchKernelGGL(k_emit<4>, grid, dim3(kEmitThreads), 0, stream, rec, views, n, tile, order, offsets,
-                           total, n_records, tile_keys, keys64, vals, capacity, status);
+                           total, n_records, tile_keys, keys64, vals, capacity, status, count, ranges, n_tiles);
     return hipGetLastError();
 }
 
@@ -985,12 +1248,6 @@ hipError_t launch_pair_reduce(const uint32_t* order, const uint32_t* offsets, co
     if (n_records <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_pair_reduce, dim3((unsigned)((n_records + 255) / 256)), dim3(256), 0, stream, order, offsets,
                        ntiles, n_records, inv, d_count, grad_pair, grad2d);
-    return hipGetLastError();
-}
-
-hipError_t launch_clamp_count(const uint32_t* total, int64_t capacity, uint32_t* count, int32_t* status,
-                              hipStream_t stream) {
-    hipLaunchKernelGGL(k_clamp_count, dim3(1), dim3(1), 0, stream, total, capacity, count, status);
     return hipGetLastError();
 }
 
