@@ -1145,19 +1145,23 @@ megs_status megs_photometric_loss(const float* images, const float* targets, int
         if (w <= 0 || h <= 0 || w > 16384 || h > 16384) return fail(MEGS_ERR_ARG, "view %d: image size %dx%d out of range", i, w, h);
         vs.v[i].width = w; vs.v[i].height = h;
         vs.v[i].pix_off = pix;
-        vs.v[i].part_off = parts;
-        vs.v[i].n_part = loss_partials(w, h);
         pix += (int64_t)w * h;
+    }
+    const int rows = loss_rows(pix);
+    for (int i = 0; i < n_views; ++i) {
+        vs.v[i].rows = rows;
+        vs.v[i].part_off = parts;
+        vs.v[i].n_part = loss_partials(vs.v[i].width, vs.v[i].height, rows);
         parts += vs.v[i].n_part;
     }
-    const size_t bytes = align256(sizeof(double) * 9 * pix) + align256(sizeof(double) * 2 * parts) +
-                         align256(sizeof(double) * n_views) + 256;
+    // the derivative maps (only for the gradient) and the loss partials
+    const int64_t n_maps = dl_dimages ? 9 * pix : 0;
+    const size_t bytes = align256(sizeof(double) * n_maps) + align256(sizeof(double) * 2 * parts) + 512;
     void* mem = alloc(alloc_ctx, bytes);
     if (bad_alloc(mem)) return fail(MEGS_ERR_ALLOC, "allocation of %zu bytes failed or not 256-byte aligned", bytes);
     Carver c{static_cast<char*>(mem), 0};
-    double* maps = c.take<double>(9 * pix);
+    double* maps = c.take<double>(n_maps);
     double* partial = c.take<double>(2 * parts);
-    double* terms = c.take<double>(n_views);
     Window11 g;
     double sum = 0.0;
     for (int k = 0; k < 11; ++k) {
@@ -1165,7 +1169,7 @@ megs_status megs_photometric_loss(const float* images, const float* targets, int
         sum += g.w[k];
     }
     for (int k = 0; k < 11; ++k) g.w[k] /= sum;
-    HIP_TRY(launch_loss(vs, n_views, images, targets, maps, partial, terms, loss, dl_dimages, g, lambda_dssim,
+    HIP_TRY(launch_loss(vs, n_views, images, targets, maps, partial, loss, dl_dimages, g, lambda_dssim,
                         static_cast<hipStream_t>(stream)));
     return MEGS_OK;
 }

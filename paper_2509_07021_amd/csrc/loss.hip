@@ -9,159 +9,272 @@
 // variables, the derivative of S at pixel q with respect to x at pixel p is
 //   G(p - q) (dS/dmx(q) + 2 x_p dS/dExx(q) + y_p dS/dExy(q)),
 //   dS/dmx = (2 my (a2 - a1) - 2 mx S (b2 - b1)) / (b1 b2), dS/dExx = -S / b2, dS/dExy = 2 a1 / (b1 b2),
-// so the gradient is a second windowed pass over those three maps. Both passes stage a tile and its
-// 5-pixel halo in LDS and apply the window as a row pass then a column pass. The moments cancel
-// (Exx - mx^2 against C2 = 9e-4), so all SSIM arithmetic is FP64; the planes are FP32. The loss sums
-// go through per-workgroup partials reduced in a fixed order, so the loss is deterministic.
+// so the gradient is a second windowed pass over those three maps. The moments cancel (Exx - mx^2 against
+// C2 = 9e-4), so all SSIM arithmetic is FP64; the planes are FP32. The loss sums go through per-wave
+// partials reduced in a fixed order, so the loss is deterministic.
+//
+// Both passes stream: one wave owns 64 columns of a strip of rows and walks them downwards. A row and its
+// 5-pixel halo pass through the wave's LDS for the horizontal window, and the vertical window is a shift
+// register of partial sums per moment (each new row's sum enters all 11, one FMA each, and the oldest leaves
+// complete), so nothing is staged twice and no wave waits for another. Per pixel and channel that is about
+// 160 FP64 instructions forward and 80 backward (they run at the FP32 rate here), and 24 bytes of maps
+// written and read. One 1080p image takes 74 + 62 us, where 16 x 16 tiles of FP64 patches in LDS took
+// 138 + 116 us; four take 248 + 254 us (the maps then exceed the last-level cache). Both passes in one, with
+// the maps kept in LDS, saves their traffic but needs 236 registers for one wave and measured 157 us (183 us
+// as two waves handing rows over).
 #include "megs_internal.hpp"
 
 namespace megs {
 namespace {
 
-constexpr int kT = 16;              // output tile edge
 constexpr int kR = 5;               // window radius
-constexpr int kP = kT + 2 * kR;     // staged patch edge
 constexpr double kC1 = 0.01 * 0.01, kC2 = 0.03 * 0.03;
+constexpr int kPatch = kWave + 2 * kR;
 
-__global__ __launch_bounds__(256) void k_ssim_fwd(LossView v, const float* __restrict__ x, const float* __restrict__ y,
-                                                  double* __restrict__ maps, double* __restrict__ partial,
-                                                  Window11 g) {
-    __shared__ float sx[kP][kP], sy[kP][kP];
-    __shared__ double hrow[kP][kT][5];
-    __shared__ double red[2][256];
-    const int tx = threadIdx.x % kT, ty = threadIdx.x / kT;
-    const int tiles_x = (v.width + kT - 1) / kT;
-    const int c = blockIdx.y;
-    const int x0 = (blockIdx.x % tiles_x) * kT, y0 = (blockIdx.x / tiles_x) * kT;
-    const int64_t plane = (int64_t)v.width * v.height;
-    const float* xc = x + v.pix_off * 3 + c * plane;
-    const float* yc = y + v.pix_off * 3 + c * plane;
-    for (int i = threadIdx.x; i < kP * kP; i += 256) {
-        const int r = i / kP, q = i % kP;
-        const int gy = y0 - kR + r, gx = x0 - kR + q;
-        const bool in = gx >= 0 && gy >= 0 && gx < v.width && gy < v.height;
-        sx[r][q] = in ? xc[(int64_t)gy * v.width + gx] : 0.f;
-        sy[r][q] = in ? yc[(int64_t)gy * v.width + gx] : 0.f;
+// The strip of work item `item`: view, channel, first column, rows [y0, y1).
+struct Strip {
+    LossView v;
+    int c, x0, y0, y1;
+    int64_t plane, off;  // pixels of a channel; the channel's first element in the image layout
+};
+
+__device__ __forceinline__ Strip strip_of(const LossViews& vs, int nv, int64_t item) {
+    int i = 0;
+    while (i + 1 < nv && vs.v[i + 1].part_off <= item) ++i;
+    Strip s;
+    s.v = vs.v[i];
+    const int64_t k = item - s.v.part_off;
+    const int sx = (s.v.width + kWave - 1) / kWave, per_c = sx * ((s.v.height + s.v.rows - 1) / s.v.rows);
+    s.c = (int)(k / per_c);
+    const int q = (int)(k - (int64_t)s.c * per_c);
+    s.x0 = (q % sx) * kWave;
+    s.y0 = (q / sx) * s.v.rows;
+    s.y1 = min(s.y0 + s.v.rows, s.v.height);
+    s.plane = (int64_t)s.v.width * s.v.height;
+    s.off = s.v.pix_off * 3 + s.c * s.plane;
+    return s;
+}
+
+// LDS written by some lanes of the wave and read by others.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A row's values for the wave's patch: column x0 - 5 + lane, and for lanes below 10 also column x0 + 59 + lane.
+// The loads go to clamped positions and nothing depends on them here, so they stay in flight until put_row,
+// which makes what lies outside the image zero.
+template <typename T>
+struct RowPair {
+    T a, b;
+};
+template <typename T>
+__device__ __forceinline__ void load_row(RowPair<T>& v, const T* __restrict__ p, const Strip& s, int r, int lane) {
+    const int xa = s.x0 - kR + lane, xb = xa + kWave, last = s.v.width - 1;
+    const T* q = p + (int64_t)min(max(r, 0), s.v.height - 1) * s.v.width;
+    v.a = q[min(max(xa, 0), last)];
+    if (lane < 2 * kR) v.b = q[min(xb, last)];
+}
+template <typename T>
+__device__ __forceinline__ void put_row(double* lds, const RowPair<T>& v, const Strip& s, int r, int lane) {
+    const int xa = s.x0 - kR + lane, xb = xa + kWave;
+    const bool row = r >= 0 && r < s.v.height;
+    lds[lane] = row && xa >= 0 && xa < s.v.width ? v.a : T(0);
+    if (lane < 2 * kR) lds[kWave + lane] = row && xb < s.v.width ? v.b : T(0);
+}
+
+// The horizontal window's moments at the patch column lane + 5: of x, y, x^2 + y^2 (the variances enter SSIM
+// only as their sum) and x y.
+__device__ __forceinline__ void row_moments(const double* sx, const double* sy, int lane, const Window11& g, double (&h)[4]) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) h[m] = 0.0;
+#pragma unroll
+    for (int k = 0; k < 11; ++k) {
+        const double a = sx[lane + k], b = sy[lane + k];
+        const double wa = g.w[k] * a, wb = g.w[k] * b;
+        h[0] += wa;
+        h[1] += wb;
+        h[2] = fma(wb, b, fma(wa, a, h[2]));
+        h[3] = fma(wa, b, h[3]);
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < kP * kT; i += 256) {
-        const int r = i / kT, q = i % kT;
-        double s[5] = {0, 0, 0, 0, 0};
-        for (int k = 0; k < 11; ++k) {
-            const double a = sx[r][q + k], b = sy[r][q + k], w = g.w[k];
-            s[0] += w * a; s[1] += w * b; s[2] += w * a * a; s[3] += w * b * b; s[4] += w * a * b;
-        }
-        for (int m = 0; m < 5; ++m) hrow[r][q][m] = s[m];
-    }
-    __syncthreads();
-    double mo[5] = {0, 0, 0, 0, 0};
-    for (int k = 0; k < 11; ++k)
-        for (int m = 0; m < 5; ++m) mo[m] += g.w[k] * hrow[ty + k][tx][m];
-    const int px = x0 + tx, py = y0 + ty;
+}
+
+// SSIM from the windowed moments, and its derivatives in mx, Exx and Exy.
+struct Ssim {
+    double S, d[3];
+};
+__device__ __forceinline__ Ssim ssim_of(const double (&mo)[4]) {
+    const double mx = mo[0], my = mo[1];
+    const double a1 = fma(2.0 * mx, my, kC1), a2 = fma(2.0, mo[3] - mx * my, kC2);
+    const double mm = fma(mx, mx, my * my), b1 = mm + kC1, b2 = (mo[2] - mm) + kC2;
+    const double rd = 1.0 / (b1 * b2);
+    Ssim r;
+    r.S = a1 * a2 * rd;
+    r.d[0] = 2.0 * (my * (a2 - a1) - mx * r.S * (b2 - b1)) * rd;
+    r.d[1] = -r.S * b1 * rd;
+    r.d[2] = 2.0 * a1 * rd;
+    return r;
+}
+
+// w h + c into a register of its own. Written out, because the compiler forms the shift register's steps
+// with the two-address v_fmac_f64 and copies most of its registers once a row (105 moves beside 160 arithmetic
+// instructions in the forward: 71 us for a 1080p image without its gradient instead of 56).
+__device__ __forceinline__ double fma_to(double w, double h, double c) {
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "s"(w), "v"(h), "v"(c));
+    return r;
+}
+
+// Enters a row's sum into the shift register of the vertical window; returns the row 5 above, complete.
+__device__ __forceinline__ double shift_in(double (&acc)[10], double h, const Window11& g) {
+    const double out = fma_to(g.w[10], h, acc[0]);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) acc[i] = fma_to(g.w[9 - i], h, acc[i + 1]);
+    acc[9] = g.w[0] * h;
+    return out;
+}
+
+__device__ __forceinline__ double wave_sum_f64(double x) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d);
+    return x;
+}
+
+// The loss sums, and with MAPS (a gradient follows) the derivative maps.
+template <bool MAPS>
+__global__ __launch_bounds__(64) void k_ssim_fwd(LossViews vs, int nv, const float* __restrict__ x,
+                                                 const float* __restrict__ y, double* __restrict__ maps,
+                                                 double* __restrict__ partial, Window11 g) {
+    __shared__ double sx[kPatch], sy[kPatch];
+    const int lane = threadIdx.x;
+    const int64_t item = xcd_item(blockIdx.x, gridDim.x);  // neighbouring strips share an L2 and halos
+    const Strip s = strip_of(vs, nv, item);
+    const float* xc = x + s.off;
+    const float* yc = y + s.off;
+    double* mc = maps + s.off * 3;
+    const bool col = s.x0 + lane < s.v.width;
+    double acc[4][10] = {};
     double ssim = 0.0, l1 = 0.0;
-    if (px < v.width && py < v.height) {
-        const double mx = mo[0], my = mo[1];
-        const double a1 = 2.0 * mx * my + kC1, a2 = 2.0 * (mo[4] - mx * my) + kC2;
-        const double b1 = mx * mx + my * my + kC1, b2 = (mo[2] - mx * mx) + (mo[3] - my * my) + kC2;
-        const double den = b1 * b2;
-        const double S = a1 * a2 / den;
-        ssim = S;
-        l1 = fabs((double)sx[ty + kR][tx + kR] - (double)sy[ty + kR][tx + kR]);
-        const int64_t p = (int64_t)py * v.width + px;
-        double* mc = maps + (v.pix_off * 3 + c * plane) * 3;
-        mc[p] = (2.0 * my * (a2 - a1) - 2.0 * mx * S * (b2 - b1)) / den;
-        mc[plane + p] = -S / b2;
-        mc[2 * plane + p] = 2.0 * a1 / den;
-    }
-    red[0][threadIdx.x] = ssim;
-    red[1][threadIdx.x] = l1;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + s];
-            red[1][threadIdx.x] += red[1][threadIdx.x + s];
+    RowPair<float> nx, ny;
+    load_row(nx, xc, s, s.y0 - kR, lane);
+    load_row(ny, yc, s, s.y0 - kR, lane);
+    for (int r = s.y0 - kR; r < s.y1 + kR; ++r) {
+        put_row(sx, nx, s, r, lane);
+        put_row(sy, ny, s, r, lane);
+        wave_sync();
+        load_row(nx, xc, s, r + 1, lane);  // the next row, in flight while this one is summed
+        load_row(ny, yc, s, r + 1, lane);
+        double h[4], mo[4];
+        row_moments(sx, sy, lane, g, h);
+        if (r >= s.y0 && r < s.y1 && col) l1 += fabs(sx[lane + kR] - sy[lane + kR]);
+        wave_sync();
+#pragma unroll
+        for (int m = 0; m < 4; ++m) mo[m] = shift_in(acc[m], h[m], g);
+        const int q = r - kR;
+        if (q >= s.y0 && col) {
+            const Ssim t = ssim_of(mo);
+            ssim += t.S;
+            if (MAPS) {
+                const int64_t p = (int64_t)q * s.v.width + s.x0 + lane;
+#pragma unroll
+                for (int m = 0; m < 3; ++m) mc[m * s.plane + p] = t.d[m];
+            }
         }
-        __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        const int64_t b = v.part_off + (int64_t)c * gridDim.x + blockIdx.x;
-        partial[2 * b] = red[0][0];
-        partial[2 * b + 1] = red[1][0];
+    ssim = wave_sum_f64(ssim);
+    l1 = wave_sum_f64(l1);
+    if (lane == 0) {
+        partial[2 * item] = ssim;
+        partial[2 * item + 1] = l1;
     }
 }
 
-__global__ __launch_bounds__(256) void k_ssim_bwd(LossView v, const float* __restrict__ x, const float* __restrict__ y,
-                                                  const double* __restrict__ maps, float* __restrict__ dl, Window11 g,
-                                                  double lam) {
-    __shared__ double sm[3][kP][kP];
-    __shared__ double hrow[kP][kT][3];
-    const int tx = threadIdx.x % kT, ty = threadIdx.x / kT;
-    const int tiles_x = (v.width + kT - 1) / kT;
-    const int c = blockIdx.y;
-    const int x0 = (blockIdx.x % tiles_x) * kT, y0 = (blockIdx.x / tiles_x) * kT;
-    const int64_t plane = (int64_t)v.width * v.height;
-    const double* mc = maps + (v.pix_off * 3 + c * plane) * 3;
-    for (int i = threadIdx.x; i < kP * kP; i += 256) {
-        const int r = i / kP, q = i % kP;
-        const int gy = y0 - kR + r, gx = x0 - kR + q;
-        const bool in = gx >= 0 && gy >= 0 && gx < v.width && gy < v.height;
-        const int64_t p = (int64_t)gy * v.width + gx;
-        for (int m = 0; m < 3; ++m) sm[m][r][q] = in ? mc[m * plane + p] : 0.0;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < kP * kT; i += 256) {
-        const int r = i / kT, q = i % kT;
-        double s[3] = {0, 0, 0};
-        for (int k = 0; k < 11; ++k)
-            for (int m = 0; m < 3; ++m) s[m] += g.w[k] * sm[m][r][q + k];
-        for (int m = 0; m < 3; ++m) hrow[r][q][m] = s[m];
-    }
-    __syncthreads();
-    const int px = x0 + tx, py = y0 + ty;
-    if (px >= v.width || py >= v.height) return;
-    double b[3] = {0, 0, 0};
-    for (int k = 0; k < 11; ++k)
-        for (int m = 0; m < 3; ++m) b[m] += g.w[k] * hrow[ty + k][tx][m];
-    const int64_t p = (int64_t)py * v.width + px;
-    const int64_t off = v.pix_off * 3 + c * plane + p;
-    const double xv = x[off], yv = y[off];
-    const double n = 3.0 * (double)plane;
-    const double sgn = xv > yv ? 1.0 : (xv < yv ? -1.0 : 0.0);
-    const double dssim = b[0] + 2.0 * xv * b[1] + yv * b[2];
-    dl[off] = (float)((1.0 - lam) * sgn / n - lam * dssim / n);
-}
-
-// One workgroup per view: the view's loss term from its partial sums, in a fixed order.
-__global__ __launch_bounds__(256) void k_loss_views(const double* __restrict__ partial, const LossViews vs,
-                                                    double lam, double* __restrict__ terms) {
-    __shared__ double red[2][256];
-    const LossView& v = vs.v[blockIdx.x];
-    double s = 0.0, l = 0.0;
-    for (int64_t b = threadIdx.x; b < v.n_part; b += 256) {
-        s += partial[2 * (v.part_off + b)];
-        l += partial[2 * (v.part_off + b) + 1];
-    }
-    red[0][threadIdx.x] = s;
-    red[1][threadIdx.x] = l;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if ((int)threadIdx.x < k) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + k];
-            red[1][threadIdx.x] += red[1][threadIdx.x + k];
+__global__ __launch_bounds__(64) void k_ssim_bwd(LossViews vs, int nv, const float* __restrict__ x,
+                                                 const float* __restrict__ y, const double* __restrict__ maps,
+                                                 float* __restrict__ dl, Window11 g, double lam) {
+    __shared__ double sm[3][kPatch];
+    const int lane = threadIdx.x;
+    const int64_t item = xcd_item(blockIdx.x, gridDim.x);  // neighbouring strips share an L2 and halos
+    const Strip s = strip_of(vs, nv, item);
+    const double* mc = maps + s.off * 3;
+    const bool col = s.x0 + lane < s.v.width;
+    const double n = 3.0 * (double)s.plane, cl = (1.0 - lam) / n, cs = lam / n;
+    double acc[3][10] = {};
+    RowPair<double> even[3], odd[3];
+    auto load = [&](RowPair<double> (&v)[3], int r) {
+#pragma unroll
+        for (int m = 0; m < 3; ++m) load_row(v[m], mc + m * s.plane, s, r, lane);
+    };
+    // row r, in v, which then takes row r + 2 (two rows of maps in flight per wave: with one the waves wait for
+    // memory 60% of the time)
+    auto step = [&](RowPair<double> (&v)[3], int r) {
+#pragma unroll
+        for (int m = 0; m < 3; ++m) put_row(sm[m], v[m], s, r, lane);
+        wave_sync();
+        const int q = r - kR;
+        const int64_t p = s.off + (int64_t)max(q, 0) * s.v.width + min(s.x0 + lane, s.v.width - 1);
+        const float xf = x[p], yf = y[p];
+        load(v, r + 2);
+        double b[3];
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            double h = 0.0;
+#pragma unroll
+            for (int k = 0; k < 11; ++k) h = fma(g.w[k], sm[m][lane + k], h);
+            b[m] = shift_in(acc[m], h, g);
         }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        const double n = 3.0 * (double)v.width * v.height;
-        terms[blockIdx.x] = (1.0 - lam) * red[1][0] / n + lam * (1.0 - red[0][0] / n);
+        wave_sync();
+        if (q >= s.y0 && col) {
+            const double xv = xf, yv = yf;
+            const double sgn = xf > yf ? cl : (xf < yf ? -cl : 0.0);
+            const double dssim = fma(yv, b[2], fma(2.0 * xv, b[1], b[0]));
+            dl[p] = (float)fma(-cs, dssim, sgn);
+        }
+    };
+    const int r1 = s.y1 + kR;
+    load(even, s.y0 - kR);
+    load(odd, s.y0 - kR + 1);
+    for (int r = s.y0 - kR; r < r1; r += 2) {
+        step(even, r);
+        if (r + 1 < r1) step(odd, r + 1);
     }
 }
 
-__global__ void k_loss_total(const double* __restrict__ terms, int nv, double* __restrict__ loss) {
-    if (threadIdx.x != 0) return;
-    double s = 0.0;
-    for (int i = 0; i < nv; ++i) s += terms[i];
-    loss[0] = s;
+// The loss from the partial sums, in a fixed order: a view's term per wave, then the views in order.
+__global__ __launch_bounds__(1024) void k_loss_total(const double* __restrict__ partial, LossViews vs, int nv, double lam,
+                                                     double* __restrict__ loss) {
+    __shared__ double term[MEGS_MAX_VIEWS];
+    const int lane = __lane_id();
+    // one view takes all sixteen waves, more views a wave each
+    __shared__ double part[16][2];
+    const int w = threadIdx.x / kWave, per = nv == 1 ? 16 : 1;
+    for (int i = w / per; i < nv; i += 16 / per) {
+        const LossView v = vs.v[i];
+        double s = 0.0, l = 0.0;
+        for (int64_t b = (w % per) * kWave + lane; b < v.n_part; b += per * kWave) {
+            s += partial[2 * (v.part_off + b)];
+            l += partial[2 * (v.part_off + b) + 1];
+        }
+        s = wave_sum_f64(s);
+        l = wave_sum_f64(l);
+        if (per > 1) {
+            if (lane == 0) { part[w][0] = s; part[w][1] = l; }
+            __syncthreads();  // (one view: every wave is here once)
+            s = l = 0.0;
+            for (int k = 0; k < per; ++k) { s += part[k][0]; l += part[k][1]; }
+        }
+        if (lane == 0 && w % per == 0) {
+            const double n = 3.0 * (double)v.width * v.height;
+            term[i] = (1.0 - lam) * l / n + lam * (1.0 - s / n);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int i = 0; i < nv; ++i) s += term[i];
+        loss[0] = s;
+    }
 }
 
 // Adam (Kingma and Ba) with bias correction, FP32 arithmetic; the parameter is read from and
@@ -184,26 +297,38 @@ __global__ __launch_bounds__(256) void k_adam(int64_t count, void* __restrict__ 
 }  // namespace
 
 hipError_t launch_loss(const LossViews& vs, int nv, const float* x, const float* y, double* maps, double* partial,
-                       double* terms, double* loss, float* dl, const Window11& g, double lam, hipStream_t stream) {
-    for (int i = 0; i < nv; ++i) {
-        const LossView& v = vs.v[i];
-        const int tiles = ((v.width + kT - 1) / kT) * ((v.height + kT - 1) / kT);
-        hipLaunchKernelGGL(k_ssim_fwd, dim3(tiles, 3), dim3(256), 0, stream, v, x, y, maps, partial, g);
-    }
-    hipLaunchKernelGGL(k_loss_views, dim3(nv), dim3(256), 0, stream, partial, vs, lam, terms);
-    hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(64), 0, stream, terms, nv, loss);
-    if (dl) {
-        for (int i = 0; i < nv; ++i) {
-            const LossView& v = vs.v[i];
-            const int tiles = ((v.width + kT - 1) / kT) * ((v.height + kT - 1) / kT);
-            hipLaunchKernelGGL(k_ssim_bwd, dim3(tiles, 3), dim3(256), 0, stream, v, x, y, maps, dl, g, lam);
-        }
-    }
+                       double* loss, float* dl, const Window11& g, double lam, hipStream_t stream) {
+    const dim3 grid((unsigned)(vs.v[nv - 1].part_off + vs.v[nv - 1].n_part));
+    if (dl)
+        hipLaunchKernelGGL(k_ssim_fwd<true>, grid, dim3(kWave), 0, stream, vs, nv, x, y, maps, partial, g);
+    else
+        hipLaunchKernelGGL(k_ssim_fwd<false>, grid, dim3(kWave), 0, stream, vs, nv, x, y, maps, partial, g);
+    hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(1024), 0, stream, partial, vs, nv, lam, loss);
+    if (dl) hipLaunchKernelGGL(k_ssim_bwd, grid, dim3(kWave), 0, stream, vs, nv, x, y, maps, dl, g, lam);
     return hipGetLastError();
 }
 
-int64_t loss_partials(int width, int height) {
-    return 3ll * ((width + kT - 1) / kT) * ((height + kT - 1) / kT);
+// Rows of a strip: the strips above and below sum its 10 rows of halo again, so tall strips cost least, but a
+// strip is one wave's serial walk, and about two waves for each of the 1,024 SIMDs are needed to fill the
+// chip: the rows that make (rows + 10) times the rounds of 2,048 strips least. Measured (forward + backward)
+// in strips of 64 / 32 / 16 rows for a 1080p image 84 + 68, 74 + 62 and 74 + 63 us (at least), in strips of
+// 16 / 8 / 4 rows for one of 979 x 546 29 + 24, 35 + 28 and 43 + 38 us.
+int loss_rows(int64_t pixels) {
+    int best = 64;
+    double least = 1e300;
+    for (int rows = 64; rows >= 4; rows /= 2) {
+        const double rounds = 3.0 * (double)pixels / (kWave * rows) / 2048.0;
+        const double t = (rows + 2 * kR) * (rounds > 1.0 ? rounds : 1.0);
+        if (t < least) {
+            least = t;
+            best = rows;
+        }
+    }
+    return best;
+}
+
+int64_t loss_partials(int width, int height, int rows) {
+    return 3ll * ((width + kWave - 1) / kWave) * ((height + rows - 1) / rows);
 }
 
 hipError_t launch_adam(int64_t count, void* param, int dt, const float* grad, float* m, float* v, float lr, float b1,

@@ -462,9 +462,11 @@ hipError_t launch_compact_write(const CompactArgs& a, hipStream_t stream);
 // training-step pieces (loss.hip)
 struct LossView {
     int32_t width, height;
+    int32_t rows;      // rows of a strip (loss_rows)
+    int32_t pad;
     int64_t pix_off;   // first pixel of the view in the concatenated image layout
-    int64_t part_off;  // first loss partial of the view
-    int64_t n_part;    // partials of the view (3 channels x tiles)
+    int64_t part_off;  // first strip (and loss partial) of the view
+    int64_t n_part;    // strips of the view (3 channels x blocks of columns x blocks of rows)
 };
 struct LossViews {
     LossView v[MEGS_MAX_VIEWS];
@@ -472,9 +474,11 @@ struct LossViews {
 struct Window11 {
     double w[11];
 };
-int64_t loss_partials(int width, int height);
+int loss_rows(int64_t pixels);  // rows of a strip, for the pixels of all views
+int64_t loss_partials(int width, int height, int rows);
+// dl null: the loss alone, which uses no maps
 hipError_t launch_loss(const LossViews& vs, int nv, const float* x, const float* y, double* maps, double* partial,
-                       double* terms, double* loss, float* dl, const Window11& g, double lam, hipStream_t stream);
+                       double* loss, float* dl, const Window11& g, double lam, hipStream_t stream);
 hipError_t launch_adam(int64_t count, void* param, int dt, const float* grad, float* m, float* v, float lr, float b1,
                        float b2, float eps, int step, hipStream_t stream);
 
