@@ -30,6 +30,10 @@ namespace {
 constexpr int kR = 5;               // window radius
 constexpr double kC1 = 0.01 * 0.01, kC2 = 0.03 * 0.03;
 constexpr int kPatch = kWave + 2 * kR;
+// Strips whose loss sums one wave reduces, beside the gradient's strips where there are any: a launch saved,
+// and even a wave alone takes less than a pass over that many strips (a launch of its own took 4.7 us of the
+// 24 us of a 128 x 128 image).
+constexpr int64_t kWaveSums = 8192;
 
 // The strip of work item `item`: view, channel, first column, rows [y0, y1).
 struct Strip {
@@ -156,15 +160,14 @@ __global__ __launch_bounds__(64) void k_ssim_fwd(LossViews vs, int nv, const flo
     const bool col = s.x0 + lane < s.v.width;
     double acc[4][10] = {};
     double ssim = 0.0, l1 = 0.0;
-    RowPair<float> nx, ny;
-    load_row(nx, xc, s, s.y0 - kR, lane);
-    load_row(ny, yc, s, s.y0 - kR, lane);
-    for (int r = s.y0 - kR; r < s.y1 + kR; ++r) {
-        put_row(sx, nx, s, r, lane);
-        put_row(sy, ny, s, r, lane);
+    RowPair<float> xe, ye, xo, yo;
+    // row r, in v and w, which then take row r + 2
+    auto step = [&](RowPair<float>& v, RowPair<float>& w, int r) {
+        put_row(sx, v, s, r, lane);
+        put_row(sy, w, s, r, lane);
         wave_sync();
-        load_row(nx, xc, s, r + 1, lane);  // the next row, in flight while this one is summed
-        load_row(ny, yc, s, r + 1, lane);
+        load_row(v, xc, s, r + 2, lane);
+        load_row(w, yc, s, r + 2, lane);
         double h[4], mo[4];
         row_moments(sx, sy, lane, g, h);
         if (r >= s.y0 && r < s.y1 && col) l1 += fabs(sx[lane + kR] - sy[lane + kR]);
@@ -181,6 +184,15 @@ __global__ __launch_bounds__(64) void k_ssim_fwd(LossViews vs, int nv, const flo
                 for (int m = 0; m < 3; ++m) mc[m * s.plane + p] = t.d[m];
             }
         }
+    };
+    const int r1 = s.y1 + kR;
+    load_row(xe, xc, s, s.y0 - kR, lane);
+    load_row(ye, yc, s, s.y0 - kR, lane);
+    load_row(xo, xc, s, s.y0 - kR + 1, lane);
+    load_row(yo, yc, s, s.y0 - kR + 1, lane);
+    for (int r = s.y0 - kR; r < r1; r += 2) {
+        step(xe, ye, r);
+        if (r + 1 < r1) step(xo, yo, r + 1);
     }
     ssim = wave_sum_f64(ssim);
     l1 = wave_sum_f64(l1);
@@ -190,12 +202,44 @@ __global__ __launch_bounds__(64) void k_ssim_fwd(LossViews vs, int nv, const flo
     }
 }
 
+// A view's term of the loss, and the loss from the partial sums by one wave, in a fixed order.
+__device__ __forceinline__ double view_loss(const LossView& v, double ssim, double l1, double lam) {
+    const double n = 3.0 * (double)v.width * v.height;
+    return (1.0 - lam) * l1 / n + lam * (1.0 - ssim / n);
+}
+__device__ __forceinline__ void loss_by_wave(const double* __restrict__ partial, const LossViews& vs, int nv, double lam,
+                                             double* __restrict__ loss, int lane) {
+    double sum = 0.0;
+    for (int i = 0; i < nv; ++i) {
+        const LossView v = vs.v[i];
+        double s[4] = {}, l[4] = {};
+        for (int64_t b = lane; b < v.n_part; b += 4 * kWave)
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (b + u * kWave < v.n_part) {
+                    const double2 p = reinterpret_cast<const double2*>(partial)[v.part_off + b + u * kWave];
+                    s[u] += p.x;
+                    l[u] += p.y;
+                }
+        const double ss = wave_sum_f64((s[0] + s[1]) + (s[2] + s[3])), ll = wave_sum_f64((l[0] + l[1]) + (l[2] + l[3]));
+        sum += view_loss(v, ss, ll, lam);
+    }
+    if (lane == 0) loss[0] = sum;
+}
+
+// The gradient. With `loss` given, one more workgroup than strips reduces the loss beside them.
 __global__ __launch_bounds__(64) void k_ssim_bwd(LossViews vs, int nv, const float* __restrict__ x,
                                                  const float* __restrict__ y, const double* __restrict__ maps,
-                                                 float* __restrict__ dl, Window11 g, double lam) {
+                                                 float* __restrict__ dl, Window11 g, double lam,
+                                                 const double* __restrict__ partial, double* __restrict__ loss) {
     __shared__ double sm[3][kPatch];
     const int lane = threadIdx.x;
-    const int64_t item = xcd_item(blockIdx.x, gridDim.x);  // neighbouring strips share an L2 and halos
+    if (loss && blockIdx.x == 0) {
+        loss_by_wave(partial, vs, nv, lam, loss, lane);
+        return;
+    }
+    const unsigned first = loss ? 1 : 0;
+    const int64_t item = xcd_item(blockIdx.x - first, gridDim.x - first);  // neighbouring strips share an L2 and halos
     const Strip s = strip_of(vs, nv, item);
     const double* mc = maps + s.off * 3;
     const bool col = s.x0 + lane < s.v.width;
@@ -241,35 +285,33 @@ __global__ __launch_bounds__(64) void k_ssim_bwd(LossViews vs, int nv, const flo
     }
 }
 
-// The loss from the partial sums, in a fixed order: a view's term per wave, then the views in order.
+// The loss by a workgroup of its own, in the same order (the same bits): 256 threads per view, thread
+// 64 u + lane with the sums that lane adds up in its u-th place above; four views at a time.
 __global__ __launch_bounds__(1024) void k_loss_total(const double* __restrict__ partial, LossViews vs, int nv, double lam,
                                                      double* __restrict__ loss) {
     __shared__ double term[MEGS_MAX_VIEWS];
-    const int lane = __lane_id();
-    // one view takes all sixteen waves, more views a wave each
-    __shared__ double part[16][2];
-    const int w = threadIdx.x / kWave, per = nv == 1 ? 16 : 1;
-    for (int i = w / per; i < nv; i += 16 / per) {
-        const LossView v = vs.v[i];
-        double s = 0.0, l = 0.0;
-        for (int64_t b = (w % per) * kWave + lane; b < v.n_part; b += per * kWave) {
-            s += partial[2 * (v.part_off + b)];
-            l += partial[2 * (v.part_off + b) + 1];
+    __shared__ double2 part[1024];
+    const int t = threadIdx.x % 256, group = threadIdx.x / 256;
+    for (int i0 = 0; i0 < nv; i0 += 4) {
+        const int i = i0 + group;
+        if (i < nv) {
+            double s = 0.0, l = 0.0;
+            for (int64_t b = t; b < vs.v[i].n_part; b += 256) {
+                const double2 p = reinterpret_cast<const double2*>(partial)[vs.v[i].part_off + b];
+                s += p.x;
+                l += p.y;
+            }
+            part[threadIdx.x] = make_double2(s, l);
         }
-        s = wave_sum_f64(s);
-        l = wave_sum_f64(l);
-        if (per > 1) {
-            if (lane == 0) { part[w][0] = s; part[w][1] = l; }
-            __syncthreads();  // (one view: every wave is here once)
-            s = l = 0.0;
-            for (int k = 0; k < per; ++k) { s += part[k][0]; l += part[k][1]; }
+        __syncthreads();
+        if (i < nv && t < kWave) {
+            const double2* q = part + group * 256 + t;
+            const double s = wave_sum_f64((q[0].x + q[64].x) + (q[128].x + q[192].x));
+            const double l = wave_sum_f64((q[0].y + q[64].y) + (q[128].y + q[192].y));
+            if (t == 0) term[i] = view_loss(vs.v[i], s, l, lam);
         }
-        if (lane == 0 && w % per == 0) {
-            const double n = 3.0 * (double)v.width * v.height;
-            term[i] = (1.0 - lam) * l / n + lam * (1.0 - s / n);
-        }
+        __syncthreads();
     }
-    __syncthreads();
     if (threadIdx.x == 0) {
         double s = 0.0;
         for (int i = 0; i < nv; ++i) s += term[i];
@@ -298,27 +340,33 @@ __global__ __launch_bounds__(256) void k_adam(int64_t count, void* __restrict__ 
 
 hipError_t launch_loss(const LossViews& vs, int nv, const float* x, const float* y, double* maps, double* partial,
                        double* loss, float* dl, const Window11& g, double lam, hipStream_t stream) {
-    const dim3 grid((unsigned)(vs.v[nv - 1].part_off + vs.v[nv - 1].n_part));
+    const int64_t strips = vs.v[nv - 1].part_off + vs.v[nv - 1].n_part;
+    const bool few = strips <= kWaveSums;
+    const dim3 grid((unsigned)strips), wave(kWave);
     if (dl)
-        hipLaunchKernelGGL(k_ssim_fwd<true>, grid, dim3(kWave), 0, stream, vs, nv, x, y, maps, partial, g);
+        hipLaunchKernelGGL(k_ssim_fwd<true>, grid, wave, 0, stream, vs, nv, x, y, maps, partial, g);
     else
-        hipLaunchKernelGGL(k_ssim_fwd<false>, grid, dim3(kWave), 0, stream, vs, nv, x, y, maps, partial, g);
-    hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(1024), 0, stream, partial, vs, nv, lam, loss);
-    if (dl) hipLaunchKernelGGL(k_ssim_bwd, grid, dim3(kWave), 0, stream, vs, nv, x, y, maps, dl, g, lam);
+        hipLaunchKernelGGL(k_ssim_fwd<false>, grid, wave, 0, stream, vs, nv, x, y, maps, partial, g);
+    if (!few || !dl)
+        hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(nv > 1 ? 1024 : 256), 0, stream, partial, vs, nv, lam, loss);
+    if (dl)
+        hipLaunchKernelGGL(k_ssim_bwd, dim3((unsigned)strips + (few ? 1 : 0)), wave, 0, stream, vs, nv, x, y, maps, dl, g,
+                           lam, partial, few ? loss : static_cast<double*>(nullptr));
     return hipGetLastError();
 }
 
 // Rows of a strip: the strips above and below sum its 10 rows of halo again, so tall strips cost least, but a
-// strip is one wave's serial walk, and about two waves for each of the 1,024 SIMDs are needed to fill the
-// chip: the rows that make (rows + 10) times the rounds of 2,048 strips least. Measured (forward + backward)
-// in strips of 64 / 32 / 16 rows for a 1080p image 84 + 68, 74 + 62 and 74 + 63 us (at least), in strips of
-// 16 / 8 / 4 rows for one of 979 x 546 29 + 24, 35 + 28 and 43 + 38 us.
+// strip is one wave's serial walk, and the chip's 1,024 SIMDs want waves: the rows that make (rows + 10)
+// times (1 + strips per SIMD) least. Measured (forward + backward) in strips of 64 / 32 / 16 rows for a 1080p
+// image 84 + 68, 74 + 62 and 74 + 63 us, in strips of 16 / 8 / 4 rows for one of 979 x 546 29 + 24, 35 + 28
+// and 43 + 38 us, the whole loss with its gradient in strips of 4 / 2 / 1 rows for one of 240 x 180 23, 25
+// and 30 us.
 int loss_rows(int64_t pixels) {
     int best = 64;
     double least = 1e300;
-    for (int rows = 64; rows >= 4; rows /= 2) {
-        const double rounds = 3.0 * (double)pixels / (kWave * rows) / 2048.0;
-        const double t = (rows + 2 * kR) * (rounds > 1.0 ? rounds : 1.0);
+    for (int rows = 64; rows >= 2; rows /= 2) {
+        const double per_simd = 3.0 * (double)pixels / (kWave * rows) / 1024.0;
+        const double t = (rows + 2 * kR) * (1.0 + per_simd);
         if (t < least) {
             least = t;
             best = rows;
