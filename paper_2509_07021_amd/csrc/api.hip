@@ -163,7 +163,7 @@ struct SlotUse {
         if (cap == hipStreamCaptureStatusNone) slot = g_slots.take(&seq);
     }
     // Polls for a while (the wait is normally tens of microseconds), then waits for the stream.
-    hipError_t wait(uint32_t* total, int32_t* bad_lobes) {
+    hipError_t wait(uint32_t* total, int32_t* bad_lobes, uint32_t* total2 = nullptr) {
         const auto t0 = std::chrono::steady_clock::now();
         bool there = false;
         while (!(there = __atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) == seq)) {
@@ -176,6 +176,7 @@ struct SlotUse {
             if (__atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) != seq) return hipErrorUnknown;
         }
         *total = slot->total;
+        if (total2) *total2 = slot->total2;
         *bad_lobes = slot->bad_lobes;
         g_slots.give(slot);
         slot = nullptr;
@@ -1063,32 +1064,35 @@ megs_status megs_compact(const megs_scene* scene, double opacity_min, double sha
     a.in.lobe_off = scene->lobe_off;
     a.opacity_min = opacity_min;
     a.sharp_min = sharp_min;
-    // working block: keep, count, new_idx, lobe_pos [n], totals [2], status [8], scan scratch
-    const size_t wbytes = 4 * align256(sizeof(uint32_t) * (n ? n : 1)) + 2 * align256(32) +
-                          align256(scan_scratch_bytes(n)) + 256;
+    // working block: code [n], sums and first [compact_blocks(n)], totals, status
+    const int64_t nb = compact_blocks(n);
+    const size_t wbytes = align256(n ? n : 1) + align256(sizeof(uint32_t) * (nb ? nb : 1)) +
+                          align256(sizeof(uint2) * (nb ? nb : 1)) + align256(32) + 256;
     void* wm = alloc(alloc_ctx, wbytes);
     if (bad_alloc(wm)) return fail(MEGS_ERR_ALLOC, "allocation of %zu bytes failed or not 256-byte aligned", wbytes);
     Carver w{static_cast<char*>(wm), 0};
-    a.keep = w.take<uint32_t>(n);
-    a.count = w.take<uint32_t>(n);
-    a.new_idx = w.take<uint32_t>(n);
-    a.lobe_pos = w.take<uint32_t>(n);
-    uint32_t* totals = w.take<uint32_t>(8);
-    int32_t* status = w.take<int32_t>(8);
-    void* scan_scratch = w.take<char>((int64_t)scan_scratch_bytes(n));
+    a.code = w.take<uint8_t>(n);
+    a.sums = w.take<uint32_t>(nb);
+    a.first = w.take<uint2>(nb);
+    int32_t* status = w.take<int32_t>(8);  // and behind the four flags the totals
+    a.totals = reinterpret_cast<uint32_t*>(status + 4);
     a.in.status = status;
-    HIP_TRY(launch_fill_u32(totals, 0u, 8, s));
     HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(status), 0u, 8, s));
-    HIP_TRY(launch_compact_mark(a, s));
-    if (n > 0) {
-        HIP_TRY(launch_scan(a.keep, nullptr, n, a.new_idx, ScanTotal{totals + 0}, scan_scratch, s));
-        HIP_TRY(launch_scan(a.count, nullptr, n, a.lobe_pos, ScanTotal{totals + 1}, scan_scratch, s));
-    }
     uint32_t ht[2] = {0, 0};
-    int32_t hs[4] = {0, 0, 0, 0};
-    HIP_TRY(hipMemcpyAsync(ht, totals, sizeof(ht), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(hs, status, sizeof(hs), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    int32_t hs[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (n > 0) {
+        SlotUse slot(s);
+        a.host = slot.slot;
+        a.seq = slot.seq;
+        HIP_TRY(launch_compact_mark(a, s));
+        if (a.host) HIP_TRY(slot.wait(&ht[0], &hs[kStatusBadLobes], &ht[1]));
+    }
+    if (!a.host) {
+        HIP_TRY(hipMemcpyAsync(hs, status, sizeof(hs), hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+        ht[0] = (uint32_t)hs[4];
+        ht[1] = (uint32_t)hs[5];
+    }
     if (hs[kStatusBadLobes]) return fail(MEGS_ERR_ARG, "malformed lobe_off (compressed-row lobes)");
     const int64_t no = ht[0], lo = ht[1];
     a.n_out = no;
@@ -1113,7 +1117,7 @@ megs_status megs_compact(const megs_scene* scene, double opacity_min, double sha
     a.lobe_off = o.take<int32_t>(no + 1);
     a.kept = o.take<int32_t>(no);
     a.lobe_src = o.take<int32_t>(lo);
-    HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(a.lobe_off + no), (uint32_t)lo, 1, s));
+    if (no == 0) HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(a.lobe_off), (uint32_t)lo, 1, s));
     HIP_TRY(launch_compact_write(a, s));
 
     memset(out, 0, sizeof(*out));

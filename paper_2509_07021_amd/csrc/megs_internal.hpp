@@ -188,22 +188,19 @@ __device__ __forceinline__ float load_elem(const void* p, int dt, int64_t idx) {
     return __uint_as_float(bits);
 }
 
-// FP32 to the storage dtype, round to nearest even (BF16: the upper half of the FP32 pattern after
+// FP32 to a 16-bit storage dtype, round to nearest even (BF16: the upper half of the FP32 pattern after
 // adding 0x7fff plus the lowest kept bit; NaNs stay NaN).
-__device__ __forceinline__ void store_elem(void* p, int dt, int64_t idx, float v) {
-    if (dt == MEGS_F32) { static_cast<float*>(p)[idx] = v; return; }
-    if (dt == MEGS_F16) { static_cast<__half*>(p)[idx] = __float2half_rn(v); return; }
+__device__ __forceinline__ uint16_t round_elem(int dt, float v) {
+    if (dt == MEGS_F16) return __half_as_ushort(__float2half_rn(v));
     const uint32_t b = __float_as_uint(v);
-    const uint32_t r = isnan(v) ? ((b >> 16) | 0x40u) : ((b + 0x7fffu + ((b >> 16) & 1u)) >> 16);
-    static_cast<uint16_t*>(p)[idx] = (uint16_t)r;
+    return (uint16_t)(isnan(v) ? ((b >> 16) | 0x40u) : ((b + 0x7fffu + ((b >> 16) & 1u)) >> 16));
 }
 
-// Copies one stored element bit for bit.
-__device__ __forceinline__ void copy_elem(void* dst, int64_t di, const void* src, int64_t si, int dt) {
+__device__ __forceinline__ void store_elem(void* p, int dt, int64_t idx, float v) {
     if (dt == MEGS_F32)
-        static_cast<uint32_t*>(dst)[di] = static_cast<const uint32_t*>(src)[si];
+        static_cast<float*>(p)[idx] = v;
     else
-        static_cast<uint16_t*>(dst)[di] = static_cast<const uint16_t*>(src)[si];
+        static_cast<uint16_t*>(p)[idx] = round_elem(dt, v);
 }
 
 // Where the lobes of Gaussian i live. Dense scenes: K lobes, element l n + i of a one-row plane
@@ -343,13 +340,14 @@ hipError_t launch_project_bwd(const SceneDev& sc, const ViewInfo* views, int nv,
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t count, hipStream_t stream);
 hipError_t launch_iota(uint32_t* p, int64_t count, hipStream_t stream);
 
-// A scan's grand total: to device memory, and, for a forward that waits for it, to host memory as well
+// A scan's grand total: to device memory, and, for a call that waits for it, to host memory as well
 // (pinned, coherent): a slot whose sequence number the host gives out, written last.
 struct HostCount {
     uint32_t total;
     int32_t bad_lobes;
     uint32_t seq;
-    uint32_t pad[13];  // one slot per 64 bytes
+    uint32_t total2;  // of a compaction: kept lobes
+    uint32_t pad[12];  // one slot per 64 bytes
 };
 struct ScanTotal {
     uint32_t* total = nullptr;
@@ -446,16 +444,20 @@ hipError_t launch_pair_reduce(const uint32_t* order, const uint32_t* offsets, co
 struct CompactArgs {
     SceneDev in;
     double opacity_min, sharp_min;
-    uint32_t* keep;      // [n] 1 when Gaussian i is kept
-    uint32_t* count;     // [n] lobes Gaussian i keeps
-    uint32_t* new_idx;   // [n] exclusive scan of keep
-    uint32_t* lobe_pos;  // [n] exclusive scan of count
+    uint8_t* code;       // [n] kept flag and number of kept lobes of Gaussian i
+    uint32_t* sums;      // [compact_blocks(n)] kept Gaussians and lobes of each workgroup
+    uint2* first;        // [compact_blocks(n)] output positions of each workgroup's first ones
+    uint32_t* totals;    // [2] kept Gaussians, kept lobes
+    HostCount* host;     // the same for the host that waits, or null
+    uint32_t seq;
     int64_t n_out, l_out;
     void *pos, *logscale, *quat, *op_logit, *base, *axis, *sharp, *amp;  // compacted planes
     int32_t* lobe_off;   // [n_out + 1]
     int32_t* kept;       // [n_out] source Gaussian
     int32_t* lobe_src;   // [l_out] source lobe element
 };
+int64_t compact_blocks(int64_t n);
+// the keep decisions, output positions and totals
 hipError_t launch_compact_mark(const CompactArgs& a, hipStream_t stream);
 hipError_t launch_compact_write(const CompactArgs& a, hipStream_t stream);
 
