@@ -343,6 +343,7 @@ struct Frame {
     uint32_t* counters;  // [0] pairs counted, [1] pairs used, [2] record count
     int32_t* status;     // [0] pairs counted, [1] overflow, [4..7] two uint64 fragment counters
     uint2* ranges;
+    uint32_t* tile_order;  // the forward's (BlendArgs)
     float* T_final;
     uint32_t* last;
     uint32_t* queue;     // the forward's work counters (persistent launch): [0] per-tile, [0..7] sub-tile
@@ -364,7 +365,7 @@ size_t frame_main_bytes(const Layout& L) {
         b += align256(sizeof(double4) * nr1(L));
     }
     b += align256(sizeof(uint32_t) * 8) + align256(sizeof(int32_t) * 8);
-    b += align256(sizeof(uint2) * L.n_tiles);
+    b += align256(sizeof(uint2) * L.n_tiles) + align256(sizeof(uint32_t) * L.n_tiles);
     b += 2 * align256(sizeof(float) * L.n_pixels);
     b += align256(sizeof(uint32_t) * kQueueWords);
     return b;
@@ -378,9 +379,10 @@ size_t work_fwd_bytes(const Layout& L) {
 }
 
 // The backward's scratch: the per-record sums of the blend backward [NR][9] (grad2d_index), the
-// persistent launch's work counters, and in deterministic mode the per-pair slots [P][9].
+// persistent launch's work counters, the blend's tile order, and in deterministic mode the per-pair slots [P][9].
 size_t backward_bytes(const Layout& L, const megs_config* cfg, int64_t cap) {
-    size_t b = align256(sizeof(float) * 9 * nr1(L)) + align256(sizeof(uint32_t) * kQueueWords);
+    size_t b = align256(sizeof(float) * 9 * nr1(L)) + align256(sizeof(uint32_t) * kQueueWords) +
+               align256(sizeof(uint32_t) * L.n_tiles);
     if (cfg->flags & MEGS_FLAG_DETERMINISTIC) b += align256(sizeof(float) * 9 * (cap > 0 ? cap : 1));
     return b;
 }
@@ -442,6 +444,7 @@ Frame carve_frame(void* mem, const Layout& L, size_t work) {
     f.counters = c.take<uint32_t>(8);
     f.status = c.take<int32_t>(8);
     f.ranges = c.take<uint2>(L.n_tiles);
+    f.tile_order = c.take<uint32_t>(L.n_tiles);
     f.T_final = c.take<float>(L.n_pixels);
     f.last = c.take<uint32_t>(L.n_pixels);
     f.queue = c.take<uint32_t>(kQueueWords);
@@ -633,6 +636,7 @@ megs_status enqueue_back(const megs_scene* sc, const Layout& L, const megs_confi
     a.vals = sorted_v; a.ranges = f.ranges;
     a.image = images; a.T_final = f.T_final; a.last = f.last;
     a.queue = f.queue;
+    a.tile_order = f.tile_order;
     a.stats = (cfg->flags & MEGS_FLAG_STATS) ? reinterpret_cast<unsigned long long*>(f.status + 4) : nullptr;
     a.importance = importance;
     a.n = L.n;
@@ -681,6 +685,7 @@ megs_status enqueue_backward(const megs_scene* sc, const Layout& L, const megs_c
     Carver c{static_cast<char*>(scratch), 0};
     float* grad2d = c.take<float>(9 * L.nr);
     uint32_t* queue = c.take<uint32_t>(kQueueWords);
+    uint32_t* tile_order = c.take<uint32_t>(L.n_tiles);
     float* grad_pair = nullptr;
     if (cfg->flags & MEGS_FLAG_DETERMINISTIC) {
         if (!st->det_inv) return fail(MEGS_ERR_ARG, "deterministic backward needs a deterministic forward state");
@@ -701,6 +706,7 @@ megs_status enqueue_backward(const megs_scene* sc, const Layout& L, const megs_c
     a.dl = dl;
     a.grad2d = grad2d;
     a.queue = queue;
+    a.tile_order = tile_order;
     a.grad_pair = grad_pair;
     if (grad_pair)
         HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(grad_pair), 0u, 9 * st->pair_capacity, s));

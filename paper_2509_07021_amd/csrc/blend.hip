@@ -27,6 +27,8 @@
 // float atomic, only when some lane of the wave contributed.
 #include "megs_internal.hpp"
 
+#include <utility>
+
 namespace megs {
 namespace {
 
@@ -138,20 +140,24 @@ __device__ __forceinline__ bool box_meets(const float4& b, int x0, int x1, int y
 // exponent, which a sum of squares never is. The threshold is tested on the unclamped value (the
 // same decision for any number, and a NaN fails it). The forward and the backward call this same
 // function, so both take identical decisions; w1 and w2 are returned for the backward's moments.
-template <class E>  // Staged or Kept
-__device__ __forceinline__ bool frag(const E& s, float px, float py, float& w1, float& w2, float& G,
-                                     float& alpha, bool& clamped) {
-    w1 = __fmaf_rn(s.p0.x, px, __fmaf_rn(s.p0.y, py, s.p0.z));
-    w2 = __fmaf_rn(s.p1.x, py, s.p1.y);
+__device__ __forceinline__ bool alpha_of(float w1, float w2, float o, float& G, float& alpha, bool& clamped) {
     const float q2 = __fmaf_rn(-w1, w1, -(w2 * w2));
     G = __builtin_amdgcn_exp2f(q2);
-    const float raw = s.p0.w * G;
+    const float raw = o * G;
     clamped = raw > kAlphaMax;
     alpha = fminf(raw, kAlphaMax);
     // keeps the clamp next to the product: moved into the callers' blend branches, it would need a
     // separate NaN-quieting step there
     asm volatile("" : "+v"(alpha));
     return raw >= kAlphaMin;
+}
+
+template <class E>  // Staged or Kept
+__device__ __forceinline__ bool frag(const E& s, float px, float py, float& w1, float& w2, float& G,
+                                     float& alpha, bool& clamped) {
+    w1 = __fmaf_rn(s.p0.x, px, __fmaf_rn(s.p0.y, py, s.p0.z));
+    w2 = __fmaf_rn(s.p1.x, py, s.p1.y);
+    return alpha_of(w1, w2, s.p0.w, G, alpha, clamped);
 }
 
 struct TileCtx {
@@ -554,16 +560,23 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Without the work queue, the forward's workgroup b runs item xcd_item(b): each XCD takes one
-// contiguous eighth of the sub-tiles (with 8 views, one view each), so the records an XCD gathers
-// stay in its own L2. The backward keeps identity order, which measured faster for it.
+// Without the work queue a workgroup runs one item. Workgroups are handed out in order, each to the next
+// XCD in turn, and one whose XCD is full holds up all behind it; so the XCDs have to be equally busy at
+// every moment, and the longest items must not come last. From kOrderItemsFwd or kOrderItemsBwd sub-tiles
+// on, the tiles are run by falling length of their lists (k_tile_order), each XCD taking all sub-tiles of a
+// tile (forward) or of four tiles (backward) in turn, which share the list and the records in its L2.
+// Measured against each XCD running one contiguous eighth (forward) and the sub-tiles as numbered (backward):
+// eight 1080p views 0.96 -> 0.91 and 2.15 -> 1.97 ms, one 1080p view 0.25 -> 0.22 and 0.345 -> 0.335 ms, four
+// 720p views (importance) 0.39 -> 0.32 ms. With fewer sub-tiles all of them are resident at once and the
+// order costs its launch: then the eighths and the numbered order stand (8,928 sub-tiles: forward 0.352 and
+// 0.355 + 0.004 ms, backward 0.375 and 0.364 + 0.004 ms; 14,400 sub-tiles: forward 0.165 and 0.148 + 0.006 ms).
 //
 // With the work queue (persistent launch) the items are split into kSlices contiguous slices, one per
 // XCD (the same eighths as above), with one counter each (queue[s * kQueueStride], one per 256 bytes).
 // A wave pulls one item at a time from the slice of the XCD it runs on (the XCC_ID hardware register),
 // so a tile's sub-tiles and its list stay in one L2. Once its slice is drained it reads all the
-// counters at once (one lane each) and moves to the first slice with items left, its own XCD's first. Every pull advances a counter, so every item is handed out exactly once, and a wave
-// ends when every counter has passed its slice's end. The register only steers locality: any value in
+// counters at once (one lane each) and moves to the first slice with items left, its own XCD's first. Every
+// pull advances a counter, so every item is handed out exactly once, and a wave ends when every counter has passed its slice's end. The register only steers locality: any value in
 // it gives the same result. Measured on the 8-view 1080p workload (forward / backward blend): with the
 // eight counters in one cache line, pulls serialised on it and the blends took 3.7 / 4.3 ms instead of
 // 0.99 / 2.24 ms for one workgroup per item; a line per counter brings them to 1.35 / 2.48 ms. More
@@ -572,6 +585,51 @@ __device__ __forceinline__ void wave_sync() {
 // the item's work) changed nothing, and a static assignment without atomics took as long (1.32 ms).
 constexpr int kSlices = kXcds;
 static_assert(kSlices % kXcds == 0 && kSlices <= 64 && kSlices * kQueueStride <= kQueueWords, "slice counters");
+
+// The tiles by falling list length (to an eighth of an octave), for next_item. One workgroup counts and
+// places them; each of the 256 lengths has eight counters, one per lane & 7, so that a wave of equally
+// short lists does not queue up at one (14.6 us for 16,320 tiles, 5.3 us for 2,040: two passes of latency).
+constexpr int kOrderThreads = 1024;
+__global__ __launch_bounds__(kOrderThreads) void k_tile_order(const uint2* __restrict__ ranges, uint32_t n,
+                                                              uint32_t* __restrict__ order) {
+    constexpr int kCounters = 256 * 8, kEach = 8;  // 32 octaves of 8 lengths of 8 counters
+    static_assert(kCounters == 2 * kOrderThreads, "two counters a thread");
+    __shared__ uint32_t count[kCounters];
+    __shared__ uint32_t wave_total[kOrderThreads / kWave];
+    const int t = threadIdx.x;
+    auto for_tiles = [&](auto f) {
+        for (uint32_t i0 = 0; i0 < n; i0 += kOrderThreads * kEach) {
+            uint2 r[kEach];
+#pragma unroll
+            for (int j = 0; j < kEach; ++j) r[j] = ranges[min(i0 + j * kOrderThreads + t, n - 1u)];
+#pragma unroll
+            for (int j = 0; j < kEach; ++j) {
+                const uint32_t i = i0 + j * kOrderThreads + t;
+                // the float of length + 1 >= 1: exponent and three bits of the fraction, falling
+                const uint32_t b = 255u - ((__float_as_uint((float)(r[j].y - r[j].x + 1u)) >> 20) - (127u << 3));
+                if (i < n) f(i, b * 8u + (t & 7));
+            }
+        }
+    };
+    count[t] = count[t + kOrderThreads] = 0;
+    __syncthreads();
+    for_tiles([&](uint32_t, uint32_t b) { atomicAdd(&count[b], 1u); });
+    __syncthreads();
+    const uint32_t c0 = count[2 * t], c1 = count[2 * t + 1];
+    uint32_t inc = c0 + c1;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t y = __shfl_up(inc, d, kWave);
+        if (__lane_id() >= d) inc += y;
+    }
+    if (__lane_id() == kWave - 1) wave_total[t / kWave] = inc;
+    __syncthreads();
+    for (int w = 0; w < t / kWave; ++w) inc += wave_total[w];
+    count[2 * t] = inc - c0 - c1;
+    count[2 * t + 1] = inc - c1;
+    __syncthreads();
+    for_tiles([&](uint32_t i, uint32_t b) { order[atomicAdd(&count[b], 1u)] = i; });
+}
 
 struct Pull {
     int slice = -1;  // the slice the wave pulls from (-1 before its first pull)
@@ -584,10 +642,15 @@ __device__ __forceinline__ void slice_of(int64_t n_items, int s, int64_t& base, 
 }
 
 __device__ __forceinline__ int64_t next_item(const BlendArgs& a, int64_t prev, bool persistent, int64_t n_items,
-                                             Pull& q, bool by_xcd) {
+                                             Pull& q, bool by_xcd, int sub_log2) {
     if (!persistent) {
         if (prev >= 0) return n_items;
-        return by_xcd ? xcd_item((int64_t)blockIdx.x, n_items) : (int64_t)blockIdx.x;
+        if (!a.tile_order) return by_xcd ? xcd_item((int64_t)blockIdx.x, n_items) : (int64_t)blockIdx.x;
+        const uint32_t b = blockIdx.x, run = sub_log2 + (by_xcd ? 0 : 2), rest = (uint32_t)n_items >> (run + 3) << (run + 3);
+        uint32_t i = b;  // (past the last whole run of every XCD: as they come)
+        if (b < rest) i = ((b >> 3 >> run) * kXcds + (b & 7u)) << run | (b >> 3 & ((1u << run) - 1u));
+        const uint32_t t = a.tile_order[i >> sub_log2];
+        return ((int64_t)t << sub_log2) + (i & ((1u << sub_log2) - 1u));
     }
     const int lane = __lane_id();
     constexpr int kPer = kSlices / kXcds;
@@ -667,22 +730,146 @@ __device__ __forceinline__ bool reaches(const Staged& s, int bx, int by) {
     return box_meets(s.box, bx, bx + 7, by, by + 7) & !(__fmaf_rn(m1, m1, m2 * m2) > lim);
 }
 
+// The entries of a sub-tile's list whose flag is set, in list order (DOWN: in reverse order from a given
+// position), for the sub-tile kernels when the tile keys carry flags. A 32 x 32 tile's list holds some
+// eight entries for each one that reaches a given sub-tile of it, so the wave first runs through the keys
+// alone, BLOCKS x 64 at a time, and queues the flagged entries' record ids and positions in LDS; records
+// are gathered, staged and blended 64 at a time. (Taking each 64 candidates through all of that, a wave
+// spent its time on one gather's latency after the other: forward 0.295 -> 0.249 ms for one 1080p view of 1 M
+// Gaussians, 1.07 -> 0.93 ms for sixteen views of 0.5 M; backward 0.335 -> 0.288 ms for one 1080p view of 0.96 M.)
+// The next keys are loaded while the queue is worked off.
+constexpr int kRing = 256;
+template <int BLOCKS, bool DOWN>
+struct FlagQueue {
+    static_assert(kRing >= 63 + 64 * BLOCKS, "a refill fits behind the 63 entries that ask for it");
+    uint32_t key[BLOCKS], id[BLOCKS];  // of the candidates from `cursor` on
+    uint32_t first, count;             // list index of candidate 0, and the number of candidates
+    uint32_t begin;                    // list index of the tile's range
+    uint32_t cursor, head, tail;       // queued: ring positions head .. tail - 1
+    uint32_t flag;
+
+    __device__ __forceinline__ uint32_t index(uint32_t j) const { return DOWN ? first - j : first + j; }
+    __device__ __forceinline__ void load(const BlendArgs& a) {
+#pragma unroll
+        for (int b = 0; b < BLOCKS; ++b) {
+            const uint32_t j = cursor + 64u * b + __lane_id();
+            key[b] = 0u;
+            if (j < count) {
+                key[b] = a.tkeys[index(j)];
+                id[b] = a.vals[index(j)];
+            }
+        }
+    }
+    __device__ __forceinline__ void start(const BlendArgs& a, uint32_t range, uint32_t at, uint32_t n, int sidx) {
+        begin = range; first = at; count = n;
+        cursor = head = tail = 0;
+        flag = 1u << (16 + sidx);
+        load(a);
+    }
+    // queues entries until there are 64 or the list ends
+    __device__ __forceinline__ void fill(const BlendArgs& a, uint2* ring) {
+        while (tail - head < 64u && cursor < count) {
+#pragma unroll
+            for (int b = 0; b < BLOCKS; ++b) {
+                const bool hit = key[b] & flag;
+                const uint64_t m = __ballot(hit);
+                if (hit) {
+                    const uint32_t j = cursor + 64u * b + __lane_id();
+                    ring[(tail + (uint32_t)lane_rank(m)) % kRing] = make_uint2(id[b], index(j) - begin + 1u);
+                }
+                tail += (uint32_t)__popcll(m);
+            }
+            cursor += 64u * BLOCKS;
+            load(a);
+        }
+        wave_sync();
+    }
+    // takes up to 64 entries: their number, and this lane's (record id, one past the list position)
+    __device__ __forceinline__ int take(const uint2* ring, uint2& entry) {
+        const int n = (int)min(tail - head, 64u);
+        entry = ring[(head + __lane_id()) % kRing];
+        head += (uint32_t)n;
+        return n;
+    }
+};
+
+constexpr int kRow = 16;  // lanes of a DPP row
+
+// Lane L of each row of sixteen lanes, as an operand of the instruction that uses it (all lanes active).
+template <int L>
+__device__ __forceinline__ float bcast16(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + L, 0xf, 0xf, true));  // row_newbcast
+}
+
+// acc += (lane L of v's row of sixteen) * x, in one instruction (the compiler folds the broadcast into a
+// product but not into a multiply-add). A register must be written two wait states before a row broadcast
+// reads it; the compiler does not look into the statement, so it waits by itself.
+template <int L>
+__device__ __forceinline__ void fmac_bcast16(float& acc, float v, float x) {
+    asm("s_nop 1\n\tv_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf bound_ctrl:1"
+        : "+v"(acc)
+        : "v"(v), "v"(x), "n"(L));
+}
+template <int L>
+__device__ __forceinline__ void fmac3_bcast16(float& a0, float& a1, float& a2, float v0, float v1, float v2, float x) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %3, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f32_dpp %1, %4, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f32_dpp %2, %5, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf bound_ctrl:1"
+        : "+v"(a0), "+v"(a1), "+v"(a2)
+        : "v"(v0), "v"(v1), "v"(v2), "v"(x), "n"(L));
+}
+
+template <typename F, int... I>
+__device__ __forceinline__ void for_each_of_row(F& f, std::integer_sequence<int, I...>) {
+    (void)(f(std::integral_constant<int, I>{}) && ...);
+}
+
+// &p[k] through a VGPR copy of its byte offset (see kept_at).
+__device__ __forceinline__ const float4* uniform_at(const float4* p, int k) {
+    uint32_t off;
+    asm("v_mov_b32 %0, %1" : "=v"(off) : "s"(k * (int)sizeof(float4)));
+    return reinterpret_cast<const float4*>(reinterpret_cast<const char*>(p) + off);
+}
+
+// The kept entries of a chunk, as the forward sub-tile blend reads them back: every entry's 40 bytes taken
+// by every lane is 20 cycles of the CU's LDS for 18 VALU instructions, so a lane reads only what enters two
+// multiply-adds with an addend of the entry (four entries ahead); the other factors it reads once per
+// sixteen entries, for the entry of its place in a row of sixteen lanes, and the instructions that use them
+// take them from there by row broadcast. The transmittance of a stopped pixel needs no mark and no test (the
+// lane mask `alive` is in scalar registers). With the list queue: sixteen
+// views of 0.5 M Gaussians 0.96 -> 0.83 ms, one 1080p view of 1 M 0.217 -> 0.182 ms, one 979 x 546 view of 0.3 M
+// 0.355 -> 0.292 ms. Seven waves per SIMD (72 registers); at eight, five spilled registers cost as much.
+template <bool IMP>
+struct KeptRow {
+    float4 each[64];       // ay, c1, by, c2 of Staged
+    float4 lane_vals[64];  // ax, o, r, g
+    float blue[64];
+    uint32_t pos1[64];     // one past the entry's list position
+    uint32_t id[IMP ? 64 : 1];
+};
+
 template <bool STATS, bool IMP, SubMode MODE>
-__global__ __launch_bounds__(64) void k_blend_fwd_sub(BlendArgs a, int tile, int persistent) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) void k_blend_fwd_sub(BlendArgs a, int tile, int persistent) {
     constexpr bool FLAGS = MODE == kSubFlags;
-    __shared__ Kept lds[64];
+    __shared__ KeptRow<IMP> lds;
+    __shared__ uint2 ring[FLAGS ? kRing : 1];
     const int lane = __lane_id();
-    const int64_t n_items = a.n_tiles * (int64_t)(tile / 8) * (tile / 8);
-    uint32_t n_blended = 0, n_evaluated = 0;
+    const int sub_log2 = tile == 32 ? 4 : 2;  // (sub-tiles of a 32 x 32 or a 16 x 16 tile)
+    const int64_t n_items = a.n_tiles << sub_log2;
+    uint64_t n_blended = 0, n_evaluated = 0;  // of the wave
     Pull pull;
-    for (int64_t w = next_item(a, -1, persistent, n_items, pull, true); w < n_items;
-         w = next_item(a, w, persistent, n_items, pull, true)) {
+    for (int64_t w = next_item(a, -1, persistent, n_items, pull, true, sub_log2); w < n_items;
+         w = next_item(a, w, persistent, n_items, pull, true, sub_log2)) {
         const SubCtx q = sub_ctx(a, w, tile);
         const TileCtx& c = q.c;
         const int lx = q.sx + (lane & 7), ly = q.sy + (lane >> 3);
         const bool inside = c.x0 + lx < c.width && c.y0 + ly < c.height;
-        if (!__any(inside)) continue;  // a sub-tile past the image edge has no pixel
-        float T = inside ? 1.0f : -1.0f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
+        // the lanes whose pixel is in the image and has not terminated: a lane mask in scalar registers,
+        // so that its updates and tests cost the vector unit nothing
+        uint64_t alive = __ballot(inside);
+        if (!alive) continue;  // a sub-tile past the image edge has no pixel
+        float T = 1.0f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
         uint32_t last = 0;
         const uint2 rg = a.ranges[q.t];
         // the frame the entries are staged in (the tile or the sub-tile): its corner, the sub-tile's corner
@@ -690,102 +877,114 @@ __global__ __launch_bounds__(64) void k_blend_fwd_sub(BlendArgs a, int tile, int
         const int bx = MODE == kSubInTile ? q.sx : 0, by = MODE == kSubInTile ? q.sy : 0;
         const double fx0 = (double)(c.x0 + q.sx - bx), fy0 = (double)(c.y0 + q.sy - by);
         const float px = bx + (lane & 7) + 0.5f, py = by + (lane >> 3) + 0.5f;
-        // each chunk's tile keys and record ids are loaded one chunk ahead, while the previous
-        // chunk's entries are blended
-        uint32_t key_n = 0, id_n = 0;
-        if (rg.x + lane < rg.y) {
-            id_n = a.vals[rg.x + lane];
-            key_n = FLAGS ? a.tkeys[rg.x + lane] : 0u;
-        }
-        for (uint32_t base = rg.x; base < rg.y; base += 64) {
-            if (!__any(T > 0.0f)) break;
-            const uint32_t idx = base + lane;
-            const uint32_t key = key_n, gid = id_n;
-            bool hit = false;
-            Staged st;
-            uint32_t g = 0;
-            if (idx < rg.y) {
-                // the key's sub-tile flags, when present, decide before the record is gathered
-                g = gid;
-                const bool flagged = !FLAGS || ((key >> (16 + q.sidx)) & 1u);
-                if (flagged) {
-                    stage(a, g, fx0, fy0, &st, !FLAGS);
-                    hit = FLAGS || reaches(st, bx, by);  // the flags already tested the ellipse
-                }
-            }
-            const uint64_t m = __ballot(hit);
-            const int nhit = __popcll(m);
-            if (hit) {
-                const int slot = lane_rank(m);
-                lds[slot] = Kept{st.p0, st.p1, st.b, idx - rg.x + 1u, g};
-            }
-            if (idx + 64u < rg.y) {
-                id_n = a.vals[idx + 64u];
-                key_n = FLAGS ? a.tkeys[idx + 64u] : 0u;
-            }
-            wave_sync();
-            for (int k0 = 0; k0 < nhit; k0 += 4) {
-                // the wave stops once all its pixels have terminated; checked every 4 entries (a
-                // terminated pixel has T < 0 and takes no further fragment in between)
-                if (!__any(T > 0.0f)) break;
-                const Kept* kp = kept_at(lds, k0);
+        auto keep = [&](int slot, const Staged& st, uint32_t pos1, uint32_t g) {
+            lds.each[slot] = make_float4(st.p0.y, st.p0.z, st.p1.x, st.p1.y);
+            lds.lane_vals[slot] = make_float4(st.p0.x, st.p0.w, st.p1.z, st.p1.w);
+            lds.blue[slot] = st.b;
+            lds.pos1[slot] = pos1;
+            if (IMP) lds.id[slot] = g;
+        };
+        auto blend_kept = [&](int nhit) {
+            for (int k0 = 0; k0 < nhit; k0 += kRow) {
+                // sixteen entries, one per lane of each row of sixteen lanes
+                const float4 per_lane = lds.lane_vals[k0 + (lane & (kRow - 1))];
+                const float blue = lds.blue[k0 + (lane & (kRow - 1))];
+                const float4* const each = uniform_at(lds.each, k0);
+                float4 ahead[4];
+                int taken = -1;     // the last of the sixteen that the pixel includes
+                float sums = 0.0f;  // lane k: the weights of the k-th, summed over the wave (IMP)
+                auto blend = [&](auto index) {
+                    constexpr int kk = decltype(index)::value;
+                    if (k0 + kk >= nhit) return false;  // wave-uniform
+                    // the wave stops once all its pixels have terminated; checked every 4 entries
+                    if (kk % 4 == 0 && !alive) return false;
+                    if constexpr (kk % 4 == 0) {
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) {
-                    const int k = k0 + kk;
-                    if (k < nhit) {  // wave-uniform
-                        const Kept s = kp[kk];
-                        float w1, w2, G, alpha;
-                        bool clamped;
-                        // a live pixel has T >= kTMin, a terminated one (or one outside the image)
-                        // T < 0; this compare, not shared with the termination test above, lets the
-                        // wave vote below branch on the lane mask directly
-                        const bool pass = frag(s, px, py, w1, w2, G, alpha, clamped) & (T >= kTMin);
-                        if (STATS) n_evaluated += T > 0.0f;
-                        if (__any(pass)) {
-                            const float Tn = T * (1.0f - alpha);
-                            const bool term = pass & (Tn < kTMin);
-                            const bool incl = pass & !term;
-                            const float wgt = incl ? alpha * T : 0.0f;
-                            C0 = __fmaf_rn(wgt, s.p1.z, C0);
-                            C1 = __fmaf_rn(wgt, s.p1.w, C1);
-                            C2 = __fmaf_rn(wgt, s.b, C2);
-                            T = incl ? Tn : (term ? -T : T);
-                            last = incl ? s.pos1 : last;
-                            if (STATS) n_blended += incl;
-                            if (IMP) {
-                                const float wsum = wave_sum(wgt);
-                                if (lane == kWave - 1 && wsum != 0.0f)
-                                    unsafeAtomicAdd(a.importance + ((int64_t)s.slot - (int64_t)c.view * a.n), wsum);
-                            }
-                        }
+                        for (int i = 0; i < 4; ++i) ahead[i] = each[kk + i];
                     }
-                }
+                    const float4 s = ahead[kk % 4];
+                    float w1 = __fmaf_rn(s.x, py, s.y);
+                    fmac_bcast16<kk>(w1, per_lane.x, px);
+                    const float w2 = __fmaf_rn(s.z, py, s.w);
+                    float G, alpha;
+                    bool clamped;
+                    const bool over = alpha_of(w1, w2, bcast16<kk>(per_lane.y), G, alpha, clamped);
+                    if (STATS) n_evaluated += (uint32_t)__popcll(alive);
+                    const uint64_t pass = __ballot(over) & alive;
+                    if (!pass) return true;  // wave-uniform
+                    const float Tn = T * (1.0f - alpha);
+                    const uint64_t incl = pass & ~__ballot(Tn < kTMin);
+                    alive &= incl | ~pass;
+                    if (STATS) n_blended += (uint32_t)__popcll(incl);
+                    const bool in = __builtin_amdgcn_inverse_ballot_w64(incl);
+                    const float wgt = in ? alpha * T : 0.0f;
+                    fmac3_bcast16<kk>(C0, C1, C2, per_lane.z, per_lane.w, blue, wgt);
+                    T = in ? Tn : T;
+                    taken = in ? kk : taken;
+                    if (IMP) {
+                        const int wsum = __builtin_amdgcn_readlane(__float_as_int(wave_sum(wgt)), kWave - 1);
+                        asm("s_nop 3\n\tv_writelane_b32 %0, %1, %2" : "+v"(sums) : "s"(wsum), "n"(kk));
+                    }
+                    return true;
+                };
+                for_each_of_row(blend, std::make_integer_sequence<int, kRow>{});
+                if (taken >= 0) last = lds.pos1[k0 + taken];
+                if (IMP && lane < kRow && sums != 0.0f)
+                    unsafeAtomicAdd(a.importance + ((int64_t)lds.id[k0 + lane] - (int64_t)c.view * a.n), sums);
+                if (!alive) break;
             }
-            wave_sync();
+        };
+        if (FLAGS) {
+            FlagQueue<3, false> queue;
+            queue.start(a, rg.x, rg.x, rg.y - rg.x, q.sidx);
+            queue.fill(a, ring);
+            while (alive) {
+                uint2 entry;
+                const int n = queue.take(ring, entry);
+                if (n == 0) break;
+                RecVecs raw;
+                if (lane < n) raw = gather(a, entry.x);
+                queue.fill(a, ring);
+                if (lane < n) keep(lane, staged_of(raw, fx0, fy0, false), entry.y, entry.x);
+                wave_sync();
+                blend_kept(n);
+                wave_sync();
+            }
+        } else {
+            // each chunk's record ids are loaded one chunk ahead, while the previous chunk's entries are blended
+            uint32_t id_n = rg.x + lane < rg.y ? a.vals[rg.x + lane] : 0u;
+            for (uint32_t base = rg.x; base < rg.y && alive; base += 64) {
+                const uint32_t idx = base + lane, g = id_n;
+                bool hit = false;
+                Staged st;
+                if (idx < rg.y) {
+                    stage(a, g, fx0, fy0, &st);
+                    hit = reaches(st, bx, by);
+                }
+                const uint64_t m = __ballot(hit);
+                if (hit) keep(lane_rank(m), st, idx - rg.x + 1u, g);
+                if (idx + 64u < rg.y) id_n = a.vals[idx + 64u];
+                wave_sync();
+                blend_kept(__popcll(m));
+                wave_sync();
+            }
         }
         if (inside) {
             const int x = c.x0 + lx, y = c.y0 + ly;
             const int64_t p = (int64_t)y * c.width + x;
             const int64_t plane = (int64_t)c.width * c.height;
             float* img = a.image + 3 * c.pix_off;
-            const float Tf = fabsf(T);
-            img[p] = __fmaf_rn(Tf, c.bg[0], C0);
-            img[plane + p] = __fmaf_rn(Tf, c.bg[1], C1);
-            img[2 * plane + p] = __fmaf_rn(Tf, c.bg[2], C2);
-            a.T_final[c.pix_off + p] = Tf;
+            img[p] = __fmaf_rn(T, c.bg[0], C0);
+            img[plane + p] = __fmaf_rn(T, c.bg[1], C1);
+            img[2 * plane + p] = __fmaf_rn(T, c.bg[2], C2);
+            a.T_final[c.pix_off + p] = T;
             a.last[c.pix_off + p] = last;
         }
     }
     if (STATS) {
-        unsigned long long nb = n_blended, ne = n_evaluated;
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            nb += __shfl_xor(nb, d);
-            ne += __shfl_xor(ne, d);
-        }
         if (lane == 0) {
-            atomicAdd(a.stats, nb);
-            atomicAdd(a.stats + 1, ne);
+            atomicAdd(a.stats, (unsigned long long)n_blended);
+            atomicAdd(a.stats + 1, (unsigned long long)n_evaluated);
         }
     }
 }
@@ -816,6 +1015,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     // depends on the row and the entry, so that the 16 lanes of a 16-byte read (two entries' eight rows)
     // touch every LDS bank once
     __shared__ __align__(16) float2 rows[kGroup * 64];
+    __shared__ uint2 ring[FLAGS ? kRing : 1];
     __shared__ __align__(16) float dlr[3][64];  // the pixels' colour gradients
     const int lane = __lane_id();
     // as replaying lane: pixel (lane & 7, lane >> 3); as summing lane: entry lane >> 3, pixel row lane & 7
@@ -830,10 +1030,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     // as adding lane: sum lane % 9 of entry lane / 9 (lane 63 adds nothing)
     const int add_entry = min(lane / 9, kGroup - 1), add_comp = lane % 9;
     const float4* const fin = reinterpret_cast<const float4*>(sums + min(lane, 9 * kGroup - 1) * 8);
-    const int64_t n_items = a.n_tiles * (int64_t)(tile / 8) * (tile / 8);
+    const int sub_log2 = tile == 32 ? 4 : 2;
+    const int64_t n_items = a.n_tiles << sub_log2;
     Pull pull;
-    for (int64_t w = next_item(a, -1, persistent, n_items, pull, false); w < n_items;
-         w = next_item(a, w, persistent, n_items, pull, false)) {
+    for (int64_t w = next_item(a, -1, persistent, n_items, pull, false, sub_log2); w < n_items;
+         w = next_item(a, w, persistent, n_items, pull, false, sub_log2)) {
         const SubCtx q = sub_ctx(a, w, tile);
         const TileCtx& c = q.c;
         const int lx = q.sx + (lane & 7), ly = q.sy + (lane >> 3);
@@ -870,25 +1071,36 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         const double fx0 = (double)(c.x0 + q.sx - bx), fy0 = (double)(c.y0 + q.sy - by);
         const float px = bx + (lane & 7) + 0.5f, py = by + (lane >> 3) + 0.5f;
         const float row_y = by + sum_row + 0.5f;
-        // The list is walked in chunks of 64 from position wave_last - 1 downwards, pipelined: a chunk's
-        // tile keys and record ids are loaded two chunks ahead, and its records are gathered while the
-        // chunk before it is replayed, and taken over before that chunk's first atomics leave (memory
-        // operations complete in order, so a load waited for behind them would wait for them too).
-        const uint32_t first = rg.x + wave_last;  // one past the first chunk's first position
-        uint32_t key_n = 0, id_n = 0, g = 0;
+        // The list is walked in chunks of 64 (of its flagged entries, FlagQueue) from position wave_last - 1
+        // downwards, pipelined: a chunk's record ids are loaded two chunks ahead, and its records are
+        // gathered while the chunk before it is replayed, and taken over before that chunk's first atomics
+        // leave (memory operations complete in order, so a load waited for behind them would wait for them
+        // too).
+        uint32_t cur = wave_last;  // without flags: positions not yet taken, from 0 up
+        uint32_t id_n = 0, g = 0, pos1 = 0;
         bool flagged = false, hit = false;
         RecVecs raw;
         Staged st;
-        auto load_ids = [&](uint32_t end) {  // ids and keys of the chunk that ends below `end`
-            if ((uint32_t)lane < end - rg.x) {
-                id_n = a.vals[end - 1u - (uint32_t)lane];
-                key_n = FLAGS ? a.tkeys[end - 1u - (uint32_t)lane] : 0u;
+        FlagQueue<2, true> queue;
+        // the next entries' records: true when there are any
+        auto issue = [&]() {
+            uint32_t n;
+            if constexpr (FLAGS) {
+                queue.fill(a, ring);
+                uint2 entry;
+                n = (uint32_t)queue.take(ring, entry);
+                g = entry.x;
+                pos1 = entry.y;
+            } else {
+                n = min(cur, 64u);
+                g = id_n;
+                pos1 = cur - (uint32_t)lane;
+                cur -= n;
+                if ((uint32_t)lane < cur) id_n = a.vals[rg.x + cur - 1u - (uint32_t)lane];
             }
-        };
-        auto issue = [&](uint32_t end) {  // the records of that chunk, from its ids
-            flagged = (uint32_t)lane < end - rg.x && (!FLAGS || ((key_n >> (16 + q.sidx)) & 1u));
-            g = id_n;
+            flagged = (uint32_t)lane < n;
             if (flagged) raw = gather(a, g);
+            return n != 0;
         };
         auto take = [&]() {
             hit = false;
@@ -897,11 +1109,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 hit = FLAGS || reaches(st, bx, by);  // the flags already tested the ellipse
             }
         };
-        load_ids(first);
-        issue(first);
-        uint32_t end = first;
-        uint32_t next = end - rg.x > 64u ? end - 64u : rg.x;
-        load_ids(next);
+        if constexpr (FLAGS)
+            queue.start(a, rg.x, rg.x + wave_last - 1u, wave_last, q.sidx);
+        else if ((uint32_t)lane < cur)
+            id_n = a.vals[rg.x + cur - 1u - (uint32_t)lane];
+        issue();
         take();
         int carried = 0;
         for (;;) {
@@ -909,13 +1121,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
             const int n = carried + __popcll(m);
             if (hit) {
                 const int slot = carried + lane_rank(m);
-                lds[slot] = Kept{st.p0, st.p1, st.b, end - (uint32_t)lane - rg.x, (uint64_t)grad2d_index(g, 0)};
+                lds[slot] = Kept{st.p0, st.p1, st.b, pos1, (uint64_t)grad2d_index(g, 0)};
             }
-            issue(next);
-            const uint32_t after = next - rg.x > 64u ? next - 64u : rg.x;
-            load_ids(after);
+            const bool last = !issue();
             wave_sync();
-            const bool last = next == rg.x;
             // whole groups; what is left waits for the next chunk, and after the last chunk it is a group too
             const int todo = last ? n : n - n % kGroup;
             for (int k0 = 0; k0 < todo; k0 += kGroup) {
@@ -1007,8 +1216,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 reinterpret_cast<float4*>(lds)[lane] = v;
             }
             wave_sync();
-            end = next;
-            next = after;
         }
     }
 }
@@ -1058,8 +1265,22 @@ void launch_fwd_sub_t(const BlendArgs& a, unsigned grid, int tile, SubMode mode,
         hipLaunchKernelGGL((k_blend_fwd_sub<false, IMP, kSubInTile>), dim3(grid), dim3(64), 0, stream, a, tile, (int)persistent);
 }
 
-hipError_t launch_fwd_sub(const BlendArgs& a, int tile, SubMode mode, bool persistent, hipStream_t stream) {
-    const int64_t items = a.n_tiles * (int64_t)(tile / 8) * (tile / 8);
+// Sub-tiles from which a blend runs the tiles by falling list length (measured above next_item).
+constexpr int64_t kOrderItemsFwd = 12288, kOrderItemsBwd = 8192;
+
+// The arguments with the tile order made, or without it.
+BlendArgs with_order(const BlendArgs& a, int64_t items, int64_t from, bool persistent, hipStream_t stream) {
+    BlendArgs r = a;
+    if (persistent || items <= from) r.tile_order = nullptr;
+    if (r.tile_order)
+        hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(kOrderThreads), 0, stream, a.ranges, (uint32_t)a.n_tiles,
+                           a.tile_order);
+    return r;
+}
+
+hipError_t launch_fwd_sub(const BlendArgs& args, int tile, SubMode mode, bool persistent, hipStream_t stream) {
+    const int64_t items = args.n_tiles * (int64_t)(tile / 8) * (tile / 8);
+    const BlendArgs a = with_order(args, items, kOrderItemsFwd, persistent, stream);
     const int64_t groups = persistent ? kPersistentGroups : items;
     const unsigned grid = (unsigned)(groups < items ? groups : items);
     if (a.importance)
@@ -1071,8 +1292,9 @@ hipError_t launch_fwd_sub(const BlendArgs& a, int tile, SubMode mode, bool persi
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_sub(const BlendArgs& a, int tile, SubMode mode, bool persistent, hipStream_t stream) {
-    const int64_t items = a.n_tiles * (int64_t)(tile / 8) * (tile / 8);
+hipError_t launch_bwd_sub(const BlendArgs& args, int tile, SubMode mode, bool persistent, hipStream_t stream) {
+    const int64_t items = args.n_tiles * (int64_t)(tile / 8) * (tile / 8);
+    const BlendArgs a = with_order(args, items, kOrderItemsBwd, persistent, stream);
     const int64_t groups = persistent ? kPersistentGroups : items;
     const unsigned grid = (unsigned)(groups < items ? groups : items);
     if (mode == kSubFlags)

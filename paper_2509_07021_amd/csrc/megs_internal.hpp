@@ -420,6 +420,7 @@ struct BlendArgs {
     unsigned long long* stats;  // forward fragment counters [blended, evaluated] (null: not counted)
     float* importance;          // forward: per-Gaussian sum of blending weights (null: not computed)
     int64_t n;                  // Gaussians per view (record r of view v is Gaussian r - v n)
+    uint32_t* tile_order;       // [n_tiles] room for the order in which the tiles are run (null: as numbered)
 };
 // subtile 8 (with 16 x 16 or 32 x 32 tiles): one independent wave per 8 x 8 sub-tile walking its
 // tile's list (the deterministic backward keeps the per-tile kernels). waves 0: the library's choice.

@@ -64,3 +64,31 @@ def test_default_launch_matches_the_per_tile_kernels(tile, flags):
     for p, g in ga.items():
         if g is not None and g.numel():
             assert float((g - gb[p]).norm() / gb[p].norm()) <= 1e-5, p
+
+
+@pytest.mark.parametrize("tile,size", [(16, (121, 77)), (32, (121, 77)), (16, (1003, 803)), (32, (1003, 803)),
+                                       (16, (640, 1025))])
+@pytest.mark.parametrize("n", [400, 6000])
+def test_long_lists_and_tile_order(tile, size, n):
+    """Sub-tile lists queued by their flags against lists tested entry by entry (one-stage keys carry no
+    flags), and the default launch against the per-tile kernels, on images of few and of many sub-tiles
+    (run as numbered, or by list length) with remainders: the same decisions over the same lists, so the
+    images, transmittances and last indices are the same bits."""
+    rng = np.random.default_rng(n)
+    sc = S.random_scene(rng, n, 1, False, spread=0.7, logscale_mu=-2.0)
+    cams = [S.look_at((0.0, -4.0, 0.3), *size, bg=(0.3, 0.1, 0.2)), S.look_at((3.0, -2.0, 0.3), size[1], size[0])]
+    ds = R.DeviceScene.from_scene(sc)
+    npix = sum(c.width * c.height for c in cams)
+    dl = torch.rand(3 * npix, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    for pair in ([R.Config(tile, 64, subtile=8), R.Config(tile, 64, subtile=8, flags=L.MEGS_FLAG_ONE_STAGE_SORT)],
+                 [R.Config(tile, 64), R.Config(tile, 64, waves=4)]):
+        out = []
+        for cfg in pair:
+            fr = R.forward(ds, cams, cfg)
+            out.append(([fr.images.clone(), fr.buffer("T_final", npix, torch.float32).clone(),
+                         fr.buffer("last", npix, torch.int32).clone()], R.backward(ds, fr, dl)))
+        for x, y in zip(out[0][0], out[1][0]):
+            assert torch.equal(x, y)
+        for p, g in out[0][1].items():
+            if g is not None and g.numel():
+                assert float((g - out[1][1][p]).norm() / g.norm()) <= 1e-5, p
