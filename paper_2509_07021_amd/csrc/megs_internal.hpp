@@ -257,20 +257,45 @@ __device__ __forceinline__ uint32_t tile_rect(double u, double v, int32_t r, con
 // when their x-ranges overlap. With S = C^-1, the points of E with extreme x lie at
 // dy = +-S_xy sqrt(k / S_xx); the x-extent over the band is reached there, clamped into the band
 // (x_max(dy) is concave, x_min(dy) convex). FP64 throughout.
+//
+// Evaluated from the factors (Shape): S_yy = 1 / l22^2, S_xx = (r / l22)^2 + 1 / l11^2, S_xy = -r / l22^2, and
+// the half width of E at dy is sqrt(k - (l22 dy)^2) / l11 about -r dy. The projection (which counts the listed
+// tiles) and the key emission (which lists them) are bound by their FP64 instructions, and most of those were
+// the IEEE divisions and square roots of the conic's form; the reciprocals and roots here are the hardware's
+// approximations with two Newton steps (within an ulp or two, as the terms they enter are). Both kernels
+// evaluate this same code without contraction, so they always agree. Measured on eight 1080p views of 1 M
+// Gaussians: VALU instructions 140 -> 115 M and 231 -> 201 M, projection 285 -> 240 us, emission 400 -> 370 us.
 struct EllipseRows {
-    double u, v, b, det, ia, ka, ry, dys;
+    double u, v, r, l22, k, il11, ry, dys;
     bool full;  // degenerate conic: list the whole rectangle
 };
 
-__device__ __forceinline__ void ellipse_rows(double u, double v, const Shape& q, double k, EllipseRows& e) {
-    e.u = u; e.v = v; e.b = q.b;
-    e.det = q.det;
-    e.full = !(e.det > 0.0) || !(q.a > 0.0) || !(k > 0.0);
-    const double sxx = q.c / e.det, syy = q.a / e.det, sxy = -q.b / e.det;
-    e.ry = sqrt(k * syy);
-    e.dys = sxy * sqrt(k / sxx);
-    e.ia = 1.0 / q.a;
-    e.ka = k * q.a;
+__device__ __forceinline__ double rcp64(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ __forceinline__ double rsq64(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+// sqrt of x, 0 (to 1e-145) where x is not positive
+__device__ __forceinline__ double sqrt64(double x) {
+    x = fmax(x, 1e-290);
+    const double y = rsq64(x), s = x * y;
+    return fma(fma(-s, s, x), 0.5 * y, s);
+}
+
+__device__ __forceinline__ void ellipse_rows(double u, double v, float l11, double r, float l22, double k,
+                                             EllipseRows& e) {
+    const double p = (double)l11, q = (double)l22;
+    e.u = u; e.v = v; e.r = r; e.l22 = q; e.k = k;
+    e.full = !(p * q * (p * q) > 0.0) || !(k > 0.0);
+    e.il11 = rcp64(p);
+    const double il22 = rcp64(q), rq = r * il22, sk = sqrt64(k);
+    e.ry = sk * il22;
+    e.dys = -rq * e.ry * rsq64(fma(rq, rq, e.il11 * e.il11));
 }
 
 // Columns [lo, hi] of tile row ty listed for the record (within the rectangle columns [x0, x1]);
@@ -280,28 +305,17 @@ __device__ __forceinline__ bool row_span(const EllipseRows& e, int width, int he
                                          int x1, int& lo, int& hi) {
     if (e.full) { lo = x0; hi = x1; return true; }
     const int ye = (ty + 1) * tile < height ? (ty + 1) * tile : height;
-    double dl = (ty * tile + 0.5) - e.v, dh = (ye - 0.5) - e.v;
-    if (dl < -e.ry) dl = -e.ry;
-    if (dh > e.ry) dh = e.ry;
+    const double dl = fmax((ty * tile + 0.5) - e.v, -e.ry), dh = fmin((ye - 0.5) - e.v, e.ry);
     if (dl > dh) return false;
-    double d1 = e.dys;
-    if (d1 < dl) d1 = dl;
-    if (d1 > dh) d1 = dh;
-    double d2 = -e.dys;
-    if (d2 < dl) d2 = dl;
-    if (d2 > dh) d2 = dh;
-    const double r1 = e.ka - (e.det * d1) * d1;
-    const double r2 = e.ka - (e.det * d2) * d2;
-    const double s1 = sqrt(r1 > 0.0 ? r1 : 0.0);
-    const double s2 = sqrt(r2 > 0.0 ? r2 : 0.0);
-    const double xmax = e.u + (s1 - e.b * d1) * e.ia;
-    const double xmin = e.u - (s2 + e.b * d2) * e.ia;
+    const double d1 = fmin(fmax(e.dys, dl), dh), d2 = fmin(fmax(-e.dys, dl), dh);
+    const double t1 = e.l22 * d1, t2 = e.l22 * d2;
+    const double xmax = e.u + fma(sqrt64(fma(-t1, t1, e.k)), e.il11, -(e.r * d1));
+    const double xmin = e.u - fma(sqrt64(fma(-t2, t2, e.k)), e.il11, e.r * d2);
     if (xmin > width - 0.5) return false;
     // division by the power-of-two tile size as an exact exponent shift (the same value as x / tile)
     const int sh = __ffs(tile) - 1;
-    double flo = ceil(ldexp(xmin + 0.5, -sh) - 1.0), fhi = floor(ldexp(xmax - 0.5, -sh));
-    if (flo < x0) flo = x0;
-    if (fhi > x1) fhi = x1;
+    const double flo = fmax(ceil(ldexp(xmin + 0.5, -sh) - 1.0), (double)x0);
+    const double fhi = fmin(floor(ldexp(xmax - 0.5, -sh)), (double)x1);
     if (flo > fhi) return false;
     lo = (int)flo;
     hi = (int)fhi;

@@ -467,7 +467,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kProjectWav
             int x0, x1, y0, y1;
             if (tile_rect(p.u, p.v, p.radius, vw, tile, x0, x1, y0, y1)) {
                 EllipseRows er;
-                ellipse_rows(p.u, p.v, shp, cut, er);
+                ellipse_rows(p.u, p.v, p.l11, p.r, p.l22, cut, er);
                 for (int ty = y0; ty <= y1; ++ty) {
                     int lo, hi;
                     if (row_span(er, vw.width, vw.height, tile, ty, x0, x1, lo, hi)) nt += (uint32_t)(hi - lo + 1);

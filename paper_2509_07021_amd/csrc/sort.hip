@@ -710,7 +710,7 @@ constexpr int kEmitWindow = 2048;
 // exact ones (the blend still tests every flagged record). The pair sort orders on the tile bits
 // only, so the flags ride along.
 struct BandsF {
-    float v, ry, dys, ka, det, b, ia, u;
+    float u, v, r, l22, k, il11, ry, dys;
     bool full;
 };
 
@@ -718,8 +718,8 @@ __device__ __forceinline__ BandsF bands_of(const EllipseRows& e) {
     constexpr float kMargin = 0.25f;
     BandsF f;
     f.full = e.full;
-    f.u = (float)e.u; f.v = (float)e.v; f.b = (float)e.b; f.det = (float)e.det; f.ia = (float)e.ia;
-    f.ka = (float)e.ka; f.dys = (float)e.dys;
+    f.u = (float)e.u; f.v = (float)e.v; f.r = (float)e.r; f.l22 = (float)e.l22; f.k = (float)e.k;
+    f.il11 = (float)e.il11; f.dys = (float)e.dys;
     f.ry = (float)e.ry + kMargin;
     return f;
 }
@@ -738,10 +738,11 @@ __device__ __forceinline__ void band_extent(const BandsF& f, int sub, int y8, in
     if (dl > dh) return;
     const float d1 = fminf(fmaxf(f.dys, dl), dh), d2 = fminf(fmaxf(-f.dys, dl), dh);
     // hardware square root (about 1 ulp): the quarter-pixel margin dwarfs its error
-    const float s1 = __builtin_amdgcn_sqrtf(fmaxf(f.ka - f.det * d1 * d1, 0.0f));
-    const float s2 = __builtin_amdgcn_sqrtf(fmaxf(f.ka - f.det * d2 * d2, 0.0f));
-    xmax = f.u + (s1 - f.b * d1) * f.ia + kMargin;
-    xmin = f.u - (s2 + f.b * d2) * f.ia - kMargin;
+    const float t1 = f.l22 * d1, t2 = f.l22 * d2;
+    const float s1 = __builtin_amdgcn_sqrtf(fmaxf(__fmaf_rn(-t1, t1, f.k), 0.0f));
+    const float s2 = __builtin_amdgcn_sqrtf(fmaxf(__fmaf_rn(-t2, t2, f.k), 0.0f));
+    xmax = (f.u + kMargin) + __fmaf_rn(s1, f.il11, -(f.r * d1));
+    xmin = (f.u - kMargin) - __fmaf_rn(s2, f.il11, f.r * d2);
 }
 
 // The image's sub-columns [c0, c1] (8 pixels each) whose pixel-centre range meets [xmin, xmax],
@@ -889,7 +890,7 @@ __global__ __launch_bounds__(kEmitThreads) void k_emit(Records rec, const ViewIn
         // the radius the projection stored for this record (a record with tiles has a finite one)
         const int32_t rad = (int32_t)ceilf(footprint_rho(q1.z, rr, q1.w, o));
         tile_rect(mx, my, rad, vw, tile, x0, x1, y0, y1);
-        ellipse_rows(mx, my, shape_of(q1.z, rr, q1.w), cutoff_of(o), er);
+        ellipse_rows(mx, my, q1.z, rr, q1.w, cutoff_of(o), er);
     }
     for (int64_t w0 = lo; w0 < hi; w0 += kEmitWindow) {
         const int64_t w1 = w0 + kEmitWindow < hi ? w0 + kEmitWindow : hi;
