@@ -292,7 +292,17 @@ inline unsigned grid_of(int64_t n) {
 
 }  // namespace
 
-size_t select_scratch_bytes(int64_t) { return sizeof(SelectScratch); }
+// Scores of a workgroup, a multiple of its threads, and the workgroups.
+inline int64_t select_chunk(int64_t n) {
+    int64_t chunk = (n + kSelBlocks - 1) / kSelBlocks;
+    if (chunk < kSelChunk) chunk = kSelChunk;
+    return (chunk + kSelThreads - 1) / kSelThreads * kSelThreads;
+}
+inline unsigned select_blocks(int64_t n) { return (unsigned)((n + select_chunk(n) - 1) / select_chunk(n)); }
+
+size_t select_scratch_bytes(int64_t n) {  // (the last pass's tables of the workgroups there are)
+    return n <= kSelSmall ? 256 : offsetof(SelectScratch, last) + select_blocks(n) * sizeof(SelectScratch::last[0]);
+}
 
 hipError_t launch_select_topk(const float* score, int64_t n, int64_t kappa, void* scratch, uint8_t* keep,
                               hipStream_t stream) {
@@ -306,10 +316,8 @@ hipError_t launch_select_topk(const float* score, int64_t n, int64_t kappa, void
         return hipGetLastError();
     }
     SelectScratch* sc = static_cast<SelectScratch*>(scratch);
-    int64_t chunk = (n + kSelBlocks - 1) / kSelBlocks;
-    if (chunk < kSelChunk) chunk = kSelChunk;
-    chunk = (chunk + kSelThreads - 1) / kSelThreads * kSelThreads;
-    const dim3 grid((unsigned)((n + chunk - 1) / chunk)), block(kSelThreads);
+    const int64_t chunk = select_chunk(n);
+    const dim3 grid(select_blocks(n)), block(kSelThreads);
     hipLaunchKernelGGL(k_select_init, dim3(1), block, 0, stream, sc, (uint32_t)kappa);
     hipLaunchKernelGGL(k_select_hist<0>, grid, block, 0, stream, score, n, chunk, sc);
     hipLaunchKernelGGL(k_select_hist<1>, grid, block, 0, stream, score, n, chunk, sc);
