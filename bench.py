@@ -52,9 +52,9 @@ FLOP_TEST, FLOP_FWD_BLEND, FLOP_BWD_BLEND = 15, 10, 30
 # when the counters were taken; a changed source reports traffic as null.
 TRAFFIC = {
     # 1M masked Gaussians, FP16, 8 x 1920x1080, 32x32 tiles, 8x8 sub-tile blending: FETCH_SIZE
-    # 2,173,650 KiB x 1.9998 (a 512 MiB copy read 262,167 KiB) + WRITE_SIZE 1,187,047 KiB x 1.0000
-    "blend_bwd": {"bytes": 5666777281,
-                  "source_sha256": "7c9dbb326179f52600e406b28a064c01c7630fbd32e397db7d3ae56f4519ed07"},
+    # 676,552 KiB x 1.9998 (a 512 MiB copy read 262,167 KiB) + WRITE_SIZE 1,187,045 KiB x 1.0000
+    "blend_bwd": {"bytes": 2600990001,
+                  "source_sha256": "d2ed67598f24ad448b64ecadc20679c458e84e8878cb4073836ff797eba70c29"},
 }
 # VALU instructions per launch of the blend kernels on the same workload, from a rocprofv3 --pmc
 # SQ_INSTS_VALU run (per dispatch, averaged), with the SHA-256 of the source they were taken on (a
@@ -62,10 +62,10 @@ TRAFFIC = {
 # 1024 SIMDs at 2.4 GHz they give the issue time; set against the measured time it is the kernel's
 # VALU utilisation.
 VALU = {
-    "blend_fwd": {"instructions": 512547725,
-                  "source_sha256": "7c9dbb326179f52600e406b28a064c01c7630fbd32e397db7d3ae56f4519ed07"},
-    "blend_bwd": {"instructions": 1196378670,
-                  "source_sha256": "7c9dbb326179f52600e406b28a064c01c7630fbd32e397db7d3ae56f4519ed07"},
+    "blend_fwd": {"instructions": 460027223,
+                  "source_sha256": "d2ed67598f24ad448b64ecadc20679c458e84e8878cb4073836ff797eba70c29"},
+    "blend_bwd": {"instructions": 841467483,
+                  "source_sha256": "d2ed67598f24ad448b64ecadc20679c458e84e8878cb4073836ff797eba70c29"},
 }
 SIMDS, CLOCK_HZ, VALU_CYCLES = 1024, 2.4e9, 4
 STAGE_SOURCE = {"project": "project.hip", "project_bwd": "project.hip", "blend_fwd": "blend.hip",
@@ -198,19 +198,18 @@ def stage_bytes(stage, n, nv, pairs, npix, ntiles, geom_bytes, k, tile_bits=14):
 
 def compact_bytes(scene, out_n, out_lobes):
     """Algorithmic HBM bytes of the post-processing compaction: the mark pass reads the opacity,
-    mask and sharpness planes and writes a flag and a count per Gaussian; the two scans read and
-    write 4 B per Gaussian each; the write pass reads every input plane once and writes the
-    compacted planes, offsets and index maps."""
+    mask and sharpness planes and writes one byte per Gaussian; the write pass reads that byte and
+    every input plane once and writes the compacted planes, offsets and index maps (the positions in
+    between are 12 bytes per 512 Gaussians)."""
     eg = 4 if scene.dt_geom == "f32" else 2
     ec = 4 if scene.dt_color == "f32" else 2
     ea = 4 if scene.dt_amp == "f32" else 2
     n, k = scene.n, scene.k
     masks = scene.pmask_logit is not None
-    mark = n * (eg * (1 + masks) + ec * k) + 8 * n
-    scans = 2 * 2 * 4 * n
-    read = n * (eg * (11 + masks) + ec * 3 + k * (ec * (4 + masks) + ea * 3)) + 12 * n
+    mark = n * (eg * (1 + masks) + ec * k) + n
+    read = n * (eg * (11 + masks) + ec * 3 + k * (ec * (4 + masks) + ea * 3)) + n
     write = out_n * (eg * 11 + ec * 3 + 8) + out_lobes * (ec * 4 + ea * 3 + 4) + 4
-    return mark + scans + read + write
+    return mark + read + write
 
 
 def post_processing(args, cfg):

@@ -48,15 +48,14 @@ struct Staged {
     float b;    // blue
 };
 
-// An entry kept for an 8x8 sub-tile, as the sub-tile blends read it back from LDS: the staged
+// An entry kept for an 8x8 sub-tile, as the sub-tile backward reads it back from LDS: the staged
 // record without its box (the box only decides whether the entry is kept), plus the entry's list
 // position and a record index, so that one LDS address serves every read of the entry (48 bytes).
 struct Kept {
     float4 p0, p1;   // as in Staged
     float b;         // as in Staged
     uint32_t pos1;   // one past the entry's list position (relative to the tile's range start)
-    uint64_t slot;   // forward: the record id (importance output); backward: the record's first
-                     // element in the per-record sums (grad2d_index)
+    uint64_t slot;   // the record's first element in the per-record sums (grad2d_index)
 };
 static_assert(sizeof(Kept) == 48 && offsetof(Kept, slot) % 8 == 0, "kept entries are 48 bytes, slot 8-aligned");
 
@@ -546,12 +545,12 @@ __global__ __launch_bounds__(64 * WAVES) void k_blend_bwd(BlendArgs a, int batch
 // ------------------------------------------------------------- sub-tile kernels ----
 // One wave64 per 8 x 8 sub-tile of a 16 x 16 or 32 x 32 tile: the tile's sorted list (and so the
 // key table and its sort) stays at the tile's size, while blending runs at sub-tile size. The wave
-// walks the list in chunks of 64 entries; each lane stages one entry and keeps it only when the
-// tile key flags the sub-tile (the emission tested the entry's ellipse against it), or, without
-// flags, when the entry's footprint box meets the sub-tile; the kept entries are packed in list
-// order into the wave's own LDS (ballot prefix) and blended. Entries are staged relative to the
-// sub-tile's corner, so each pixel's exponent factors stay within eight pixels of it. Sub-tiles of a tile never wait for each other: there
-// is no workgroup barrier anywhere.
+// takes 64 entries at a time, one per lane: those of the list that the tile keys flag for the sub-tile
+// (FlagQueue; the emission tested the entry's ellipse against it), or, without flags, the list's next 64,
+// of which those whose footprint reaches the sub-tile are kept. The kept entries are packed in list order
+// into the wave's own LDS (ballot prefix) and blended. Entries are staged relative to the sub-tile's corner,
+// so each pixel's exponent factors stay within eight pixels of it. Sub-tiles of a tile never wait for each
+// other: there is no workgroup barrier anywhere.
 
 // LDS written by some lanes of a wave and read by others: order the wave's accesses.
 __device__ __forceinline__ void wave_sync() {
@@ -999,8 +998,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) void k_
 // kGroup records leave through one atomic instruction, nine consecutive lanes per record (kGroup = 7: 63
 // lanes). That is about 12 VALU instructions an entry: on eight 1080p views of 1 M Gaussians, 937 M VALU
 // instructions per launch instead of 1,369 M, and 2.17 ms instead of 2.42 ms (one 1080p view of 0.96 M:
-// 0.35 instead of 0.42 ms). VALU issue is then 74% of the time; the float atomics' completion is another
-// 0.29 ms (a copy without them ran 1.88 ms), and the rest is latency at four waves per SIMD. The kernel is
+// 0.35 instead of 0.42 ms; with the list queue and the tile order 1.94 and 0.288 ms). VALU issue is then 82%
+// of the time; the rest is the float atomics' completion and latency at four waves per SIMD. (The same sums
+// as FP32 matrix products, the entries as rows and 1, x, y, x^2, x y, y^2 and the colour gradients as columns,
+// took 2.30 ms: seven entries keep the matrix pipe busy for 512 cycles.) The kernel is
 // compiled for four: at five (96 registers) it spills, and since memory operations complete in order, each
 // reload from scratch memory waits for the atomics before it (2.69 ms).
 constexpr int kGroup = 7;
