@@ -10,14 +10,15 @@
 //
 // What bounds it is what a score passes through: one read per pass (3M scores: 12 MB, from the cache
 // after the first), the histogram's atomics, and the launches. At most 256 workgroups of 1,024 threads
-// own one contiguous chunk each, so that a bucket of the device histogram receives at most 256 adds
-// (scores share few exponents: with one workgroup per 1,024 scores the first two passes' adds to a
-// handful of addresses took 97 and 155 us at 3M scores), and a workgroup counts in 16 tables, one per
-// lane group, which holds the adds of a wave to one address to four. Each pass finds the digit of the
-// pass before it in its own prologue (256 counts, one scan) instead of a one-thread launch between
-// them, and the last pass leaves every workgroup's table, from which the selection knows how many equal
-// keys lie before its chunk: no flags, no scan, and with distinct scores no second look at all.
-// Measured at 1M and 3M scores with kappa = n / 3: 195 and 360 us for 13 launches, now 6 launches.
+// own one contiguous chunk each and add to one of eight device histograms, so that a bucket receives at
+// most 32 adds (scores share few exponents: with one workgroup per 1,024 scores and one histogram the first
+// two passes' adds to a handful of addresses took 97 and 155 us at 3M scores; with 256 workgroups and one
+// histogram 6 and 10 us, with eight 4.5 us each), and a workgroup counts in 16 tables, one per lane group,
+// which holds the adds of a wave to one address to four. Each pass finds the digit of the pass before it
+// in its own prologue (256 counts, one scan) instead of a one-thread launch between them, and the last pass
+// leaves every workgroup's table, from which the selection knows how many equal keys lie before its chunk:
+// no flags, no scan, and with distinct scores no second look at all. Measured at 1M and 3M scores with kappa
+// = 3 n / 5 and n / 3: 195 and 360 us in 13 launches, now some 20 and 28 us in six.
 #include "megs_internal.hpp"
 
 namespace megs {
@@ -27,6 +28,7 @@ constexpr int kSelThreads = 1024;
 constexpr int kSelBlocks = 256;
 constexpr int kSelCopies = 16;               // histograms of a workgroup, one per lane & 15
 constexpr int kSelStride = 257;              // words between them: equal digits fall into different LDS banks
+constexpr int kSelHists = 8;                 // histograms of a pass in memory: an eighth of the adds to one address
 constexpr int kSelChunk = 2048;              // scores of a workgroup before there are kSelBlocks of them
 constexpr int kSelSmall = 16 * kSelThreads;  // scores that one workgroup holds in registers
 
@@ -39,7 +41,7 @@ struct SelectState {
 // every workgroup.
 struct SelectScratch {
     SelectState st[4];
-    uint32_t hist[4][256];
+    uint32_t hist[4][kSelHists][256];  // a pass's histogram is the sum of kSelHists, a workgroup adds to one
     uint32_t last[kSelBlocks][256];
 };
 
@@ -96,7 +98,9 @@ __device__ __forceinline__ uint32_t sum_tables(const uint32_t* h, int digit) {
 }
 
 __global__ __launch_bounds__(kSelThreads) void k_select_init(SelectScratch* sc, uint32_t kappa) {
-    sc->hist[threadIdx.x >> 8][threadIdx.x & 255] = 0;
+    uint32_t* const h = &sc->hist[0][0][0];
+#pragma unroll
+    for (int i = 0; i < kSelHists; ++i) h[i * kSelThreads + threadIdx.x] = 0;  // 4 passes of 256 digits each
     if (threadIdx.x == 0) sc->st[0] = {0u, kappa};
 }
 
@@ -107,8 +111,14 @@ __device__ __forceinline__ SelectState select_state(SelectScratch* sc, uint32_t*
     SelectState st = sc->st[PASS ? PASS - 1 : 0];
     if (PASS) {
         uint32_t digit, take;
-        const uint32_t* hist = sc->hist[PASS - 1];
-        pick_digit([&](int d) { return hist[d]; }, st.need, digit, *equal, take);
+        pick_digit(
+            [&](int d) {
+                uint32_t s = 0;
+#pragma unroll
+                for (int i = 0; i < kSelHists; ++i) s += sc->hist[PASS - 1][i][d];
+                return s;
+            },
+            st.need, digit, *equal, take);
         st.prefix |= digit << (32 - 8 * PASS);
         st.need = take;
         if (PASS < 4 && blockIdx.x == 0 && threadIdx.x == 0) sc->st[PASS] = st;
@@ -152,7 +162,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_hist(const float* __rest
     __syncthreads();
     if (threadIdx.x < 256) {
         const uint32_t s = sum_tables(h, threadIdx.x);
-        if (s) atomicAdd(&sc->hist[PASS][threadIdx.x], s);
+        if (s) atomicAdd(&sc->hist[PASS][blockIdx.x % kSelHists][threadIdx.x], s);
         if (PASS == 3) sc->last[blockIdx.x][threadIdx.x] = s;
     }
 }
