@@ -16,6 +16,8 @@
 // in its second pass.
 #include "megs_internal.hpp"
 
+#include <algorithm>
+
 namespace megs {
 namespace {
 
@@ -25,8 +27,14 @@ constexpr int kScanTile = kScanThreads * kScanIpt;  // 2048
 
 constexpr int kRsThreads = 256;
 constexpr int kRsWaves = kRsThreads / kWave;
+// Keys a thread of a radix pass takes at once: a tile of 4,096 keys writes a digit's run in longer pieces, but
+// below some millions of keys there are fewer tiles than the chip has room for, and a pass then lasts as long
+// as one workgroup's chain of ranking steps. Below kRsItems8 a thread takes 8, below kRsItems4 4 keys.
+// Measured with 16 / 8 / 4 keys (four depth passes, us): 20,000 records 68 / 48 / 41, 200,000 80 / 61 / 54, 500,000
+// 85 / 67 / 65, 1 M 92 / 78 / 84, 1.5 M 101 / 90 / 115; two pair passes: 0.54 M pairs 42 / 34 / 32, 1.35 M 49 / 43 / 47,
+// 4.5 M 78 / 75 / 79, 6.8 M 98 / 97 / 104.
 constexpr int kRsIpt = 16;
-constexpr int kRsTile = kRsThreads * kRsIpt;  // 4096
+constexpr int64_t kRsItems8 = 4 << 20, kRsItems4 = 640 << 10;
 constexpr int kRsDigits = 256;
 constexpr int kRsMaxBlocks = 2048;
 constexpr int kFewBlocks = 64;      // workgroups up to which a radix pass sums its count table itself
@@ -307,7 +315,9 @@ struct Chunk {
     int64_t n, t0, t1;
 };
 
+template <int IPT>
 __device__ __forceinline__ Chunk chunk_of(const uint32_t* d_count, int64_t max_count) {
+    constexpr int kRsTile = kRsThreads * IPT;
     Chunk c;
     int64_t n = (int64_t)*d_count;
     c.n = n < max_count ? n : max_count;
@@ -319,7 +329,7 @@ __device__ __forceinline__ Chunk chunk_of(const uint32_t* d_count, int64_t max_c
 }
 
 // FEW: the count table is [G][256] and the downsweep sums it; else [256][G], scanned by k_radix_scan_rows.
-template <typename K, bool FEW>
+template <typename K, bool FEW, int IPT>
 __global__ __launch_bounds__(kRsThreads) void k_radix_upsweep(const K* __restrict__ keys, const uint32_t* d_count,
                                                               int64_t max_count, int shift, uint32_t mask,
                                                               uint32_t* __restrict__ counts) {
@@ -328,14 +338,14 @@ __global__ __launch_bounds__(kRsThreads) void k_radix_upsweep(const K* __restric
     // wave keeps kCopies histograms, lane l adding to copy l % kCopies: lanes with equal digits
     // then collide on one address a quarter as often (the atomics on one address serialise), and
     // the odd stride puts the copies of a digit in different LDS banks.
-    constexpr int U = 8;
+    constexpr int U = IPT < 8 ? IPT : 8, kRsTile = kRsThreads * IPT;
     constexpr int kCopies = 4, kStride = kRsDigits + 1;
     __shared__ uint32_t hist[kRsWaves][kCopies * kStride];
     const int w = threadIdx.x / kWave, lane = __lane_id();
     const int cp = (lane & (kCopies - 1)) * kStride;
     for (int i = threadIdx.x; i < kRsWaves * kCopies * kStride; i += kRsThreads) (&hist[0][0])[i] = 0u;
     __syncthreads();
-    const Chunk c = chunk_of(d_count, max_count);
+    const Chunk c = chunk_of<IPT>(d_count, max_count);
     const int64_t i1 = c.t1 * kRsTile < c.n ? c.t1 * kRsTile : c.n;
     for (int64_t base = c.t0 * kRsTile + (int64_t)w * kWave * U; base < i1; base += (int64_t)kRsThreads * U) {
         // every key load first (lanes past the end read the chunk's last key), so the U loads are in
@@ -399,7 +409,7 @@ __global__ __launch_bounds__(kScanThreads) void k_radix_scan_rows(uint32_t* coun
     if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
-template <typename K, bool FEW>
+template <typename K, bool FEW, int IPT>
 __global__ __launch_bounds__(kRsThreads) void k_radix_downsweep(const K* __restrict__ keys_in,
                                                                 const uint32_t* __restrict__ vals_in,
                                                                 K* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
@@ -408,6 +418,7 @@ __global__ __launch_bounds__(kRsThreads) void k_radix_downsweep(const K* __restr
                                                                 const uint32_t* __restrict__ totals) {
     // Per tile: stable ranks -> local sorted order staged in LDS -> coalesced writes of each
     // digit's run to its global position.
+    constexpr int kRsTile = kRsThreads * IPT;
     __shared__ uint32_t run_off[kRsDigits];
     __shared__ uint32_t whist[kRsWaves][kRsDigits];
     __shared__ uint32_t tile_start[kRsDigits];
@@ -423,11 +434,15 @@ __global__ __launch_bounds__(kRsThreads) void k_radix_downsweep(const K* __restr
         if (FEW) {
             digit_total = 0;
             const uint32_t* col = offsets + threadIdx.x;
-#pragma unroll 8
-            for (uint32_t b = 0; b < gridDim.x; ++b) {
-                const uint32_t v = col[b * kRsDigits];
-                digit_total += v;
-                before += b < blockIdx.x ? v : 0u;
+            for (uint32_t b0 = 0; b0 < gridDim.x; b0 += 16) {  // sixteen loads in flight
+                uint32_t v[16];
+#pragma unroll
+                for (uint32_t j = 0; j < 16; ++j) v[j] = col[min(b0 + j, gridDim.x - 1u) * kRsDigits];
+#pragma unroll
+                for (uint32_t j = 0; j < 16; ++j) {
+                    digit_total += b0 + j < gridDim.x ? v[j] : 0u;
+                    before += b0 + j < blockIdx.x ? v[j] : 0u;
+                }
             }
         } else {
             digit_total = totals[threadIdx.x];
@@ -437,7 +452,7 @@ __global__ __launch_bounds__(kRsThreads) void k_radix_downsweep(const K* __restr
         const uint32_t digit_base = block_excl_scan256(digit_total, lds4, all);
         run_off[threadIdx.x] = digit_base + before;
     }
-    const Chunk c = chunk_of(d_count, max_count);
+    const Chunk c = chunk_of<IPT>(d_count, max_count);
     // a pass whose digit is the same for every key is the identity permutation: copy the chunk
     if (__syncthreads_or(digit_total == (uint32_t)c.n && c.n > 0)) {
         const int64_t i1 = c.t1 * kRsTile < c.n ? c.t1 * kRsTile : c.n;
@@ -451,18 +466,18 @@ __global__ __launch_bounds__(kRsThreads) void k_radix_downsweep(const K* __restr
     for (int64_t t = c.t0; t < c.t1; ++t) {
         for (int i = threadIdx.x; i < kRsWaves * kRsDigits; i += kRsThreads) (&whist[0][0])[i] = 0u;
         __syncthreads();
-        K key[kRsIpt];
-        uint32_t val[kRsIpt], dig[kRsIpt], rank[kRsIpt];
-        const int64_t base = t * kRsTile + (int64_t)w * kWave * kRsIpt + lane;
+        K key[IPT];
+        uint32_t val[IPT], dig[IPT], rank[IPT];
+        const int64_t base = t * kRsTile + (int64_t)w * kWave * IPT + lane;
         // all of the tile's loads first (no branch between them), so they are in flight together
 #pragma unroll
-        for (int j = 0; j < kRsIpt; ++j) {
+        for (int j = 0; j < IPT; ++j) {
             const int64_t idx = base + j * kWave;
             const bool ok = idx < c.n;
             key[j] = ok ? keys_in[ok ? idx : 0] : K(0);
             val[j] = ok ? vals_in[ok ? idx : 0] : 0u;
         }
-        for (int j = 0; j < kRsIpt; ++j) {
+        for (int j = 0; j < IPT; ++j) {
             const int64_t idx = base + j * kWave;
             const bool ok = idx < c.n;
             const uint32_t d = ok ? digit_of(key[j], shift, mask) : 0u;
@@ -488,7 +503,7 @@ __global__ __launch_bounds__(kRsThreads) void k_radix_downsweep(const K* __restr
         const uint32_t start_d = block_excl_scan256(total_d, lds4, tile_count);
         tile_start[threadIdx.x] = start_d;
         __syncthreads();
-        for (int j = 0; j < kRsIpt; ++j) {
+        for (int j = 0; j < IPT; ++j) {
             if (dig[j] == 0xffffffffu) continue;
             const uint32_t lpos = tile_start[dig[j]] + whist[w][dig[j]] + rank[j];
             stage_k[lpos] = key[j];
@@ -645,6 +660,32 @@ __global__ __launch_bounds__(kSmallThreads) void k_sort_small(uint32_t* __restri
     }
 }
 
+constexpr int radix_ipt(int64_t n) { return n < kRsItems4 ? 4 : n < kRsItems8 ? 8 : kRsIpt; }
+
+constexpr int radix_groups(int64_t n) {
+    const int64_t tile = kRsThreads * radix_ipt(n), tiles = (n + tile - 1) / tile;
+    return (int)(tiles < kRsMaxBlocks ? (tiles > 0 ? tiles : 1) : kRsMaxBlocks);
+}
+
+template <typename K, int IPT>
+void radix_pass(int G, const K* src_k, const uint32_t* src_v, K* dst_k, uint32_t* dst_v, const uint32_t* d_count,
+                int64_t max_count, int shift, uint32_t mask, uint32_t* counts, hipStream_t stream) {
+    uint32_t* totals = counts + (int64_t)kRsDigits * G;
+    const dim3 grid(G), block(kRsThreads);
+    if (G <= kFewBlocks) {
+        hipLaunchKernelGGL((k_radix_upsweep<K, true, IPT>), grid, block, 0, stream, src_k, d_count, max_count, shift,
+                           mask, counts);
+        hipLaunchKernelGGL((k_radix_downsweep<K, true, IPT>), grid, block, 0, stream, src_k, src_v, dst_k, dst_v,
+                           d_count, max_count, shift, mask, counts, totals);
+    } else {
+        hipLaunchKernelGGL((k_radix_upsweep<K, false, IPT>), grid, block, 0, stream, src_k, d_count, max_count, shift,
+                           mask, counts);
+        hipLaunchKernelGGL(k_radix_scan_rows, dim3(kRsDigits), dim3(kScanThreads), 0, stream, counts, G, totals);
+        hipLaunchKernelGGL((k_radix_downsweep<K, false, IPT>), grid, block, 0, stream, src_k, src_v, dst_k, dst_v,
+                           d_count, max_count, shift, mask, counts, totals);
+    }
+}
+
 template <typename K>
 hipError_t radix_sort(K* keys, uint32_t* vals, K* keys_alt, uint32_t* vals_alt, const uint32_t* d_count,
                       int64_t max_count, int begin_bit, int end_bit, void* scratch, hipStream_t stream, bool* in_alt) {
@@ -662,27 +703,15 @@ hipError_t radix_sort(K* keys, uint32_t* vals, K* keys_alt, uint32_t* vals_alt, 
             return hipGetLastError();
         }
     }
-    int64_t tiles = (max_count + kRsTile - 1) / kRsTile;
-    const int G = (int)(tiles < kRsMaxBlocks ? tiles : kRsMaxBlocks);
+    const int G = radix_groups(max_count), ipt = radix_ipt(max_count);
     uint32_t* counts = static_cast<uint32_t*>(scratch);
-    uint32_t* totals = counts + (int64_t)kRsDigits * G;
     K* src_k = keys; uint32_t* src_v = vals;
     K* dst_k = keys_alt; uint32_t* dst_v = vals_alt;
     for (int shift = begin_bit; shift < end_bit; shift += width) {
         const int bits = end_bit - shift < width ? end_bit - shift : width;
         const uint32_t mask = (1u << bits) - 1u;
-        if (G <= kFewBlocks) {
-            hipLaunchKernelGGL((k_radix_upsweep<K, true>), dim3(G), dim3(kRsThreads), 0, stream, src_k, d_count,
-                               max_count, shift, mask, counts);
-            hipLaunchKernelGGL((k_radix_downsweep<K, true>), dim3(G), dim3(kRsThreads), 0, stream, src_k, src_v, dst_k,
-                               dst_v, d_count, max_count, shift, mask, counts, totals);
-        } else {
-            hipLaunchKernelGGL((k_radix_upsweep<K, false>), dim3(G), dim3(kRsThreads), 0, stream, src_k, d_count,
-                               max_count, shift, mask, counts);
-            hipLaunchKernelGGL(k_radix_scan_rows, dim3(kRsDigits), dim3(kScanThreads), 0, stream, counts, G, totals);
-            hipLaunchKernelGGL((k_radix_downsweep<K, false>), dim3(G), dim3(kRsThreads), 0, stream, src_k, src_v, dst_k,
-                               dst_v, d_count, max_count, shift, mask, counts, totals);
-        }
+        auto pass = ipt == 4 ? radix_pass<K, 4> : ipt == 8 ? radix_pass<K, 8> : radix_pass<K, kRsIpt>;
+        pass(G, src_k, src_v, dst_k, dst_v, d_count, max_count, shift, mask, counts, stream);
         K* tk = src_k; src_k = dst_k; dst_k = tk;
         uint32_t* tv = src_v; src_v = dst_v; dst_v = tv;
         *in_alt = !*in_alt;
@@ -1170,9 +1199,11 @@ hipError_t launch_sort_scan(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, 
 int radix_passes(int begin_bit, int end_bit) { return end_bit > begin_bit ? (end_bit - begin_bit + 7) / 8 : 0; }
 
 size_t radix_scratch_bytes(int64_t max_count) {
-    const int64_t tiles = (max_count + kRsTile - 1) / kRsTile;
-    const int64_t G = tiles < kRsMaxBlocks ? (tiles > 0 ? tiles : 1) : kRsMaxBlocks;
-    return (size_t)((kRsDigits * G + kRsDigits) * sizeof(uint32_t));
+    // (a larger count never asks for less, though its tiles may be larger and fewer)
+    int groups = radix_groups(max_count);
+    if (max_count >= kRsItems4) groups = std::max(groups, radix_groups(kRsItems4 - 1));
+    if (max_count >= kRsItems8) groups = std::max(groups, radix_groups(kRsItems8 - 1));
+    return ((size_t)kRsDigits * groups + kRsDigits) * sizeof(uint32_t);
 }
 
 hipError_t launch_radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,

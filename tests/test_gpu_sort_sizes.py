@@ -1,5 +1,5 @@
 """The key table at the sizes where the sorts and scans change their form: one workgroup (up to 8,192 items),
-count tables summed by the scatter (up to 64 workgroups of 4,096), scans whose second pass sums the totals
+count tables summed by the scatter (up to 64 workgroups), 4, 8 or 16 keys a thread of a radix pass, scans whose second pass sums the totals
 (up to 1,024 workgroups of 2,048), and the general form; and forwards from several threads at once."""
 import threading
 
@@ -33,8 +33,8 @@ def _table(ds, cams, cfg, n):
     return out
 
 
-@pytest.mark.parametrize("n", [1, 2, 63, 65, 1023, 1024, 1025, 4096, 4097, 8191, 8192, 8193, 65_537, 262_144, 262_145,
-                               2_097_152, 2_097_153])
+@pytest.mark.parametrize("n", [1, 2, 63, 65, 1023, 1024, 1025, 4096, 4097, 8191, 8192, 8193, 65_536, 65_537, 262_144, 262_145,
+                               655_359, 655_360, 2_097_152, 2_097_153, 4_194_303, 4_194_304])
 def test_key_table_at_the_sorts_size_limits(n):
     rng = np.random.default_rng(n)
     scene = S.random_scene(rng, n, 0, False, spread=1.5, logscale_mu=-5.0 if n > 100_000 else -3.0)
