@@ -343,7 +343,6 @@ struct Frame {
     uint32_t* counters;  // [0] pairs counted, [1] pairs used, [2] record count
     int32_t* status;     // [0] pairs counted, [1] overflow, [4..7] two uint64 fragment counters
     uint2* ranges;
-    uint32_t* tile_order;  // the forward's (BlendArgs)
     float* T_final;
     uint32_t* last;
     uint32_t* queue;     // the forward's work counters (persistent launch): [0] per-tile, [0..7] sub-tile
@@ -365,7 +364,7 @@ size_t frame_main_bytes(const Layout& L) {
         b += align256(sizeof(double4) * nr1(L));
     }
     b += align256(sizeof(uint32_t) * 8) + align256(sizeof(int32_t) * 8);
-    b += align256(sizeof(uint2) * L.n_tiles) + align256(sizeof(uint32_t) * L.n_tiles);
+    b += align256(sizeof(uint2) * L.n_tiles);
     b += 2 * align256(sizeof(float) * L.n_pixels);
     b += align256(sizeof(uint32_t) * kQueueWords);
     return b;
@@ -444,7 +443,6 @@ Frame carve_frame(void* mem, const Layout& L, size_t work) {
     f.counters = c.take<uint32_t>(8);
     f.status = c.take<int32_t>(8);
     f.ranges = c.take<uint2>(L.n_tiles);
-    f.tile_order = c.take<uint32_t>(L.n_tiles);
     f.T_final = c.take<float>(L.n_pixels);
     f.last = c.take<uint32_t>(L.n_pixels);
     f.queue = c.take<uint32_t>(kQueueWords);
@@ -570,7 +568,7 @@ megs_status enqueue_front(const megs_scene* sc, const Layout& L, const megs_conf
         HIP_TRY(launch_iota(f.order, L.nr, s));
         bool alt = false;
         HIP_TRY(launch_radix_sort_u32(f.rec.dkey, f.order, f.dkey_alt, f.order_alt, f.counters + 2, L.nr, 0, 32,
-                                      f.rs_scratch, s, &alt));
+                                      f.rs_scratch, f.offs, sizeof(uint32_t) * (size_t)L.nr, s, &alt));
         if (alt) return fail(MEGS_ERR_HIP, "depth sort ended in the alternate buffer");
     }
     StageTimer t(MEGS_STAGE_SCAN, s);
@@ -601,13 +599,15 @@ megs_status enqueue_back(const megs_scene* sc, const Layout& L, const megs_confi
     const uint32_t* sorted_v = nullptr;
     {
         StageTimer t(MEGS_STAGE_PAIR_SORT, s);
+        void* const spare = f.T_final;  // written by the blend only
+        const size_t spare_bytes = sizeof(float) * (size_t)L.n_pixels;
         if (one_stage) {
             HIP_TRY(launch_radix_sort_u64(p.k64, p.vals, p.k64_alt, p.vals_alt, f.counters + 1, p.capacity, 0,
-                                          32 + L.tile_bits, p.rs_scratch, s, &alt));
+                                          32 + L.tile_bits, p.rs_scratch, spare, spare_bytes, s, &alt));
             sorted_k = alt ? p.k64_alt : p.k64;
         } else {
             HIP_TRY(launch_radix_sort_u32(p.tkeys, p.vals, p.tkeys_alt, p.vals_alt, f.counters + 1, p.capacity, 0,
-                                          L.tile_bits, p.rs_scratch, s, &alt));
+                                          L.tile_bits, p.rs_scratch, spare, spare_bytes, s, &alt));
             sorted_t = alt ? p.tkeys_alt : p.tkeys;
         }
     }
@@ -636,7 +636,9 @@ megs_status enqueue_back(const megs_scene* sc, const Layout& L, const megs_confi
     a.vals = sorted_v; a.ranges = f.ranges;
     a.image = images; a.T_final = f.T_final; a.last = f.last;
     a.queue = f.queue;
-    a.tile_order = f.tile_order;
+    // the tile order goes to the work space, which is free again here unless the deterministic mode keeps it
+    a.tile_order = !det && sizeof(uint32_t) * (size_t)L.n_tiles <= f.work_bytes ? reinterpret_cast<uint32_t*>(f.work)
+                                                                                 : nullptr;
     a.stats = (cfg->flags & MEGS_FLAG_STATS) ? reinterpret_cast<unsigned long long*>(f.status + 4) : nullptr;
     a.importance = importance;
     a.n = L.n;

@@ -382,22 +382,24 @@ hipError_t launch_scan(const uint32_t* x, const uint32_t* idx, int64_t n, uint32
 hipError_t launch_scan_packed(uint32_t* order, const uint32_t* ntiles, int64_t n, int idb, uint32_t* out,
                               const ScanTotal& total, void* scratch, hipStream_t stream);
 // The depth sort of such values (n of them, *d_count = n) followed by that scan; the sorted keys are not
-// part of the result. One launch for few records.
+// part of the result, and `out` also serves the sort as spare memory. One launch for few records.
 hipError_t launch_sort_scan(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
                             const uint32_t* d_count, int64_t n, const uint32_t* ntiles, int idb, uint32_t* out,
                             const ScanTotal& total, void* sort_scratch, void* scan_scratch, hipStream_t stream);
 
 // Stable LSD radix sort of (key, value) pairs on bits [begin_bit, end_bit). The element count is
 // read on device from *d_count (capped at max_count). Sorted output ends in keys/vals when
-// the return flag `in_alt` is false, else in keys_alt/vals_alt.
+// the return flag `in_alt` is false, else in keys_alt/vals_alt. spare (or null): memory nothing else uses
+// during the sort, for the count table of the shorter tables' finer passes (radix_scratch_bytes does not
+// hold it).
 size_t radix_scratch_bytes(int64_t max_count);
 int radix_passes(int begin_bit, int end_bit);
 hipError_t launch_radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
                                  const uint32_t* d_count, int64_t max_count, int begin_bit, int end_bit,
-                                 void* scratch, hipStream_t stream, bool* in_alt);
+                                 void* scratch, void* spare, size_t spare_bytes, hipStream_t stream, bool* in_alt);
 hipError_t launch_radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt,
                                  const uint32_t* d_count, int64_t max_count, int begin_bit, int end_bit,
-                                 void* scratch, hipStream_t stream, bool* in_alt);
+                                 void* scratch, void* spare, size_t spare_bytes, hipStream_t stream, bool* in_alt);
 
 // Key emission: for every record (in `order`, or index order when order is null) write its
 // tiles' keys at offsets[pos]; total: the scan's grand total (device). Two-stage: u32 global tile ids;

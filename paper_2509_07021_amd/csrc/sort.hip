@@ -662,9 +662,12 @@ __global__ __launch_bounds__(kSmallThreads) void k_sort_small(uint32_t* __restri
 
 constexpr int radix_ipt(int64_t n) { return n < kRsItems4 ? 4 : n < kRsItems8 ? 8 : kRsIpt; }
 
-constexpr int radix_groups(int64_t n) {
-    const int64_t tile = kRsThreads * radix_ipt(n), tiles = (n + tile - 1) / tile;
+constexpr int radix_groups(int64_t n, int ipt) {
+    const int64_t tile = kRsThreads * ipt, tiles = (n + tile - 1) / tile;
     return (int)(tiles < kRsMaxBlocks ? (tiles > 0 ? tiles : 1) : kRsMaxBlocks);
+}
+constexpr size_t radix_table_bytes(int64_t n, int ipt) {
+    return ((size_t)kRsDigits * radix_groups(n, ipt) + kRsDigits) * sizeof(uint32_t);
 }
 
 template <typename K, int IPT>
@@ -688,7 +691,8 @@ void radix_pass(int G, const K* src_k, const uint32_t* src_v, K* dst_k, uint32_t
 
 template <typename K>
 hipError_t radix_sort(K* keys, uint32_t* vals, K* keys_alt, uint32_t* vals_alt, const uint32_t* d_count,
-                      int64_t max_count, int begin_bit, int end_bit, void* scratch, hipStream_t stream, bool* in_alt) {
+                      int64_t max_count, int begin_bit, int end_bit, void* scratch, void* spare, size_t spare_bytes,
+                      hipStream_t stream, bool* in_alt) {
     *in_alt = false;
     if (max_count <= 0 || end_bit <= begin_bit) return hipSuccess;
     // the fewest passes of at most 8 bits, with the bits spread evenly over them (14 tile bits sort
@@ -703,7 +707,16 @@ hipError_t radix_sort(K* keys, uint32_t* vals, K* keys_alt, uint32_t* vals_alt, 
             return hipGetLastError();
         }
     }
-    const int G = radix_groups(max_count), ipt = radix_ipt(max_count);
+    // the count table of fewer keys a thread is larger than the scratch: it goes to the spare memory, or
+    // the passes take their keys as for a longer table
+    int ipt = radix_ipt(max_count);
+    if (ipt < kRsIpt) {
+        if (spare && radix_table_bytes(max_count, ipt) <= spare_bytes)
+            scratch = spare;
+        else
+            ipt = kRsIpt;
+    }
+    const int G = radix_groups(max_count, ipt);
     uint32_t* counts = static_cast<uint32_t*>(scratch);
     K* src_k = keys; uint32_t* src_v = vals;
     K* dst_k = keys_alt; uint32_t* dst_v = vals_alt;
@@ -1186,7 +1199,8 @@ hipError_t launch_sort_scan(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, 
     {
         StageTimer t(MEGS_STAGE_DEPTH_SORT, stream);
         bool alt = false;
-        const hipError_t e = radix_sort<uint32_t>(keys, vals, keys_alt, vals_alt, d_count, n, 0, 32, sort_scratch, stream, &alt);
+        const hipError_t e = radix_sort<uint32_t>(keys, vals, keys_alt, vals_alt, d_count, n, 0, 32, sort_scratch, out,
+                                                   (size_t)n * sizeof(uint32_t), stream, &alt);
         if (e != hipSuccess) return e;
         if (alt) return hipErrorUnknown;  // four passes end where they began
     }
@@ -1199,25 +1213,21 @@ hipError_t launch_sort_scan(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, 
 int radix_passes(int begin_bit, int end_bit) { return end_bit > begin_bit ? (end_bit - begin_bit + 7) / 8 : 0; }
 
 size_t radix_scratch_bytes(int64_t max_count) {
-    // (a larger count never asks for less, though its tiles may be larger and fewer)
-    int groups = radix_groups(max_count);
-    if (max_count >= kRsItems4) groups = std::max(groups, radix_groups(kRsItems4 - 1));
-    if (max_count >= kRsItems8) groups = std::max(groups, radix_groups(kRsItems8 - 1));
-    return ((size_t)kRsDigits * groups + kRsDigits) * sizeof(uint32_t);
+    return radix_table_bytes(max_count, kRsIpt);
 }
 
 hipError_t launch_radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
                                  const uint32_t* d_count, int64_t max_count, int begin_bit, int end_bit,
-                                 void* scratch, hipStream_t stream, bool* in_alt) {
+                                 void* scratch, void* spare, size_t spare_bytes, hipStream_t stream, bool* in_alt) {
     return radix_sort<uint32_t>(keys, vals, keys_alt, vals_alt, d_count, max_count, begin_bit, end_bit, scratch,
-                                stream, in_alt);
+                                spare, spare_bytes, stream, in_alt);
 }
 
 hipError_t launch_radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt,
                                  const uint32_t* d_count, int64_t max_count, int begin_bit, int end_bit,
-                                 void* scratch, hipStream_t stream, bool* in_alt) {
+                                 void* scratch, void* spare, size_t spare_bytes, hipStream_t stream, bool* in_alt) {
     return radix_sort<uint64_t>(keys, vals, keys_alt, vals_alt, d_count, max_count, begin_bit, end_bit, scratch,
-                                stream, in_alt);
+                                spare, spare_bytes, stream, in_alt);
 }
 
 hipError_t launch_emit(const Records& rec, const ViewInfo* views, int nv, int64_t n, int tile,
