@@ -564,6 +564,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_sort_small(uint32_t* __restri
         all1 &= red[0][i];
         any1 |= red[1][i];
     }
+    __syncthreads();  // the passes and the scan write red again, with no barrier before where all keys are equal
     const uint32_t differ = n > 0 ? all1 ^ any1 : 0u;
     const int ipt = (n + kSmallThreads - 1) / kSmallThreads;  // 64-item steps of a wave's segment
     const uint64_t lt = lanemask_lt();

@@ -6,6 +6,8 @@ import threading
 import numpy as np
 import pytest
 
+from gpu_util import IMG_TOL
+from oracle import oracle as O
 from paper_2509_07021_amd import _lib as L
 from paper_2509_07021_amd import render as R
 from paper_2509_07021_amd import scenes as S
@@ -57,6 +59,39 @@ def test_key_table_at_the_sorts_size_limits(n):
     b = _table(ds, cams, R.Config(16, 64, flags=planes | L.MEGS_FLAG_ONE_STAGE_SORT), n)
     assert np.array_equal(a["vals"], b["vals"]) and np.array_equal(a["tile"], b["tile"])
     assert np.array_equal(a["ranges"], b["ranges"]) and torch.equal(a["images"], b["images"])
+
+
+@pytest.mark.parametrize("culled", [False, True])
+@pytest.mark.parametrize("n", [1, 2, 64, 65, 1000, 1025, 8192])
+def test_key_table_of_records_at_one_depth(n, culled):
+    """Every depth key the same, so that no digit of the depth sort differs: a plane of Gaussians that faces the
+    camera, and the same plane behind it (all culled). The depth order is the record order."""
+    rng = np.random.default_rng(n)
+    scene = S.random_scene(rng, n, 0, False, logscale_mu=-3.0)
+    scene.pos[0], scene.pos[2] = rng.uniform(-1.0, 1.0, (2, n))
+    scene.pos[1] = -9.0 if culled else 0.25
+    scene.op_logit[:] = 1.0
+    cams = [S.look_at((0.0, -4.0, 0.0), 93, 70)]
+    ds = R.DeviceScene.from_scene(scene)
+    planes = L.MEGS_FLAG_RECORD_PLANES
+    a = _table(ds, cams, R.Config(16, 64, flags=planes), n)
+    assert a["pairs"] == int(a["ntiles"].astype(np.int64).sum()) == a["counts"]["pairs_needed"]
+    assert a["counts"]["culled"] == (n if culled else 0)
+    if culled:
+        assert a["pairs"] == 0 and not a["ranges"].any()
+    else:
+        assert np.all(a["ntiles"] > 0) and np.unique(a["depth"]).size == 1
+    assert np.array_equal(np.bincount(a["vals"], minlength=n), a["ntiles"])
+    key = (a["tile"].astype(np.int64) << 32) | a["vals"]  # by tile, and in a tile by record
+    assert np.all(key[1:] > key[:-1])
+    b = _table(ds, cams, R.Config(16, 64, flags=planes | L.MEGS_FLAG_ONE_STAGE_SORT), n)
+    for name in ("vals", "tile", "ranges"):
+        assert np.array_equal(a[name], b[name])
+    assert torch.equal(a["images"], b["images"])
+    ref = O.render(scene.widened(), scene.k, cams, 16)
+    ok = ref["views"][0]["flag"] == 0
+    img = a["images"].view(3, cams[0].height, cams[0].width).cpu().numpy()
+    assert np.abs(img - ref["images"][0])[:, ok].max() <= IMG_TOL
 
 
 def test_forwards_from_several_threads():
