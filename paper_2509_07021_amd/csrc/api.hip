@@ -377,11 +377,20 @@ size_t work_fwd_bytes(const Layout& L) {
            align256(radix_scratch_bytes(L.nr));
 }
 
+// Does the blend make a tile order? (The deterministic and the persistent launch make none.)
+bool orders_fwd(const Layout& L, const megs_config* cfg) {
+    return !(cfg->flags & (MEGS_FLAG_DETERMINISTIC | MEGS_FLAG_PERSISTENT)) && orders_tiles_fwd(L.tile, L.n_tiles);
+}
+bool orders_bwd(const Layout& L, const megs_config* cfg) {
+    return !(cfg->flags & (MEGS_FLAG_DETERMINISTIC | MEGS_FLAG_PERSISTENT)) && orders_tiles_bwd(L.tile, L.n_tiles);
+}
+
 // The backward's scratch: the per-record sums of the blend backward [NR][9] (grad2d_index), the
-// persistent launch's work counters, the blend's tile order, and in deterministic mode the per-pair slots [P][9].
+// persistent launch's work counters, the blend's tile order where it makes one (up to 256 KiB), and in
+// deterministic mode the per-pair slots [P][9].
 size_t backward_bytes(const Layout& L, const megs_config* cfg, int64_t cap) {
     size_t b = align256(sizeof(float) * 9 * nr1(L)) + align256(sizeof(uint32_t) * kQueueWords) +
-               align256(sizeof(uint32_t) * L.n_tiles);
+               (orders_bwd(L, cfg) ? align256(sizeof(uint32_t) * L.n_tiles) : 0);
     if (cfg->flags & MEGS_FLAG_DETERMINISTIC) b += align256(sizeof(float) * 9 * (cap > 0 ? cap : 1));
     return b;
 }
@@ -406,12 +415,13 @@ bool alt_in_work(const Layout& L, const megs_config* cfg, int64_t cap, size_t wo
 }
 
 // Size of the work space: the forward's own needs, and, where the frame is reusable, room for the
-// backward's scratch (when one may follow) and for the pair sort's alternate buffers (when the pair
+// backward's scratch and the forward's tile order (when a backward may follow) and for the pair sort's alternate buffers (when the pair
 // capacity is known here: cap > 0).
 size_t work_bytes(const Layout& L, const megs_config* cfg, int64_t cap, bool backward) {
     size_t w = work_fwd_bytes(L);
     if (!work_reusable(cfg)) return w;
     if (backward) w = std::max(w, backward_bytes(L, cfg, cap));
+    if (backward && orders_fwd(L, cfg)) w = std::max(w, sizeof(uint32_t) * (size_t)L.n_tiles);
     const bool one_stage = cfg->flags & MEGS_FLAG_ONE_STAGE_SORT;
     if (cap > 0 && alt_in_work(L, cfg, cap, (size_t)-1)) w = std::max(w, pairs_alt_bytes(cap, one_stage));
     return w;
@@ -636,9 +646,9 @@ megs_status enqueue_back(const megs_scene* sc, const Layout& L, const megs_confi
     a.vals = sorted_v; a.ranges = f.ranges;
     a.image = images; a.T_final = f.T_final; a.last = f.last;
     a.queue = f.queue;
-    // the tile order goes to the work space, which is free again here unless the deterministic mode keeps it
-    a.tile_order = !det && sizeof(uint32_t) * (size_t)L.n_tiles <= f.work_bytes ? reinterpret_cast<uint32_t*>(f.work)
-                                                                                 : nullptr;
+    // the tile order goes to the work space, which is free again here, where it fits
+    if (orders_fwd(L, cfg) && sizeof(uint32_t) * (size_t)L.n_tiles <= f.work_bytes)
+        a.tile_order = reinterpret_cast<uint32_t*>(f.work);
     a.stats = (cfg->flags & MEGS_FLAG_STATS) ? reinterpret_cast<unsigned long long*>(f.status + 4) : nullptr;
     a.importance = importance;
     a.n = L.n;
@@ -687,7 +697,7 @@ megs_status enqueue_backward(const megs_scene* sc, const Layout& L, const megs_c
     Carver c{static_cast<char*>(scratch), 0};
     float* grad2d = c.take<float>(9 * L.nr);
     uint32_t* queue = c.take<uint32_t>(kQueueWords);
-    uint32_t* tile_order = c.take<uint32_t>(L.n_tiles);
+    uint32_t* tile_order = orders_bwd(L, cfg) ? c.take<uint32_t>(L.n_tiles) : nullptr;
     float* grad_pair = nullptr;
     if (cfg->flags & MEGS_FLAG_DETERMINISTIC) {
         if (!st->det_inv) return fail(MEGS_ERR_ARG, "deterministic backward needs a deterministic forward state");

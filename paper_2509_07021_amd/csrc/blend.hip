@@ -561,14 +561,10 @@ __device__ __forceinline__ void wave_sync() {
 
 // Without the work queue a workgroup runs one item. Workgroups are handed out in order, each to the next
 // XCD in turn, and one whose XCD is full holds up all behind it; so the XCDs have to be equally busy at
-// every moment, and the longest items must not come last. From kOrderItemsFwd or kOrderItemsBwd sub-tiles
-// on, the tiles are run by falling length of their lists (k_tile_order), each XCD taking all sub-tiles of a
-// tile (forward) or of four tiles (backward) in turn, which share the list and the records in its L2.
-// Measured against each XCD running one contiguous eighth (forward) and the sub-tiles as numbered (backward):
-// eight 1080p views 0.96 -> 0.91 and 2.15 -> 1.97 ms, one 1080p view 0.25 -> 0.22 and 0.345 -> 0.335 ms, four
-// 720p views (importance) 0.39 -> 0.32 ms. With fewer sub-tiles all of them are resident at once and the
-// order costs its launch: then the eighths and the numbered order stand (8,928 sub-tiles: forward 0.352 and
-// 0.355 + 0.004 ms, backward 0.375 and 0.364 + 0.004 ms; 14,400 sub-tiles: forward 0.165 and 0.148 + 0.006 ms).
+// every moment, and the longest items must not come last. Where with_order says so, the tiles are run by falling
+// length of their lists (k_tile_order), each XCD taking all sub-tiles of a tile (forward) or of four tiles
+// (backward) in turn, which share the list and the records in its L2; elsewhere each XCD runs one contiguous
+// eighth (forward) or the sub-tiles run as numbered (backward).
 //
 // With the work queue (persistent launch) the items are split into kSlices contiguous slices, one per
 // XCD (the same eighths as above), with one counter each (queue[s * kQueueStride], one per 256 bytes).
@@ -586,21 +582,25 @@ constexpr int kSlices = kXcds;
 static_assert(kSlices % kXcds == 0 && kSlices <= 64 && kSlices * kQueueStride <= kQueueWords, "slice counters");
 
 // The tiles by falling list length (to an eighth of an octave), for next_item. One workgroup counts and
-// places them; each of the 256 lengths has eight counters, one per lane & 7, so that a wave of equally
-// short lists does not queue up at one (14.6 us for 16,320 tiles, 5.3 us for 2,040: two passes of latency).
+// places up to kOrderSlice of them; more tiles are ordered in slices of equal size, which run one after the
+// other. Each of the 256 lengths has eight counters, one per lane & 7, so that a wave of equally short lists
+// does not queue up at one (14.6 us for 16,320 tiles, 5.3 us for 2,040: two passes of latency; in one slice
+// a million tiles would take some 0.7 ms).
+constexpr int kOrderSlice = 16384;
 constexpr int kOrderThreads = 1024;
-__global__ __launch_bounds__(kOrderThreads) void k_tile_order(const uint2* __restrict__ ranges, uint32_t n,
-                                                              uint32_t* __restrict__ order) {
+__global__ __launch_bounds__(kOrderThreads) void k_tile_order(const uint2* __restrict__ ranges, uint32_t n_tiles,
+                                                              uint32_t slice, uint32_t* __restrict__ order) {
     constexpr int kCounters = 256 * 8, kEach = 8;  // 32 octaves of 8 lengths of 8 counters
     static_assert(kCounters == 2 * kOrderThreads, "two counters a thread");
     __shared__ uint32_t count[kCounters];
     __shared__ uint32_t wave_total[kOrderThreads / kWave];
     const int t = threadIdx.x;
+    const uint32_t first = blockIdx.x * slice, n = min(slice, n_tiles - first);
     auto for_tiles = [&](auto f) {
         for (uint32_t i0 = 0; i0 < n; i0 += kOrderThreads * kEach) {
             uint2 r[kEach];
 #pragma unroll
-            for (int j = 0; j < kEach; ++j) r[j] = ranges[min(i0 + j * kOrderThreads + t, n - 1u)];
+            for (int j = 0; j < kEach; ++j) r[j] = ranges[first + min(i0 + j * kOrderThreads + t, n - 1u)];
 #pragma unroll
             for (int j = 0; j < kEach; ++j) {
                 const uint32_t i = i0 + j * kOrderThreads + t;
@@ -627,7 +627,7 @@ __global__ __launch_bounds__(kOrderThreads) void k_tile_order(const uint2* __res
     count[2 * t] = inc - c0 - c1;
     count[2 * t + 1] = inc - c1;
     __syncthreads();
-    for_tiles([&](uint32_t i, uint32_t b) { order[atomicAdd(&count[b], 1u)] = i; });
+    for_tiles([&](uint32_t i, uint32_t b) { order[first + atomicAdd(&count[b], 1u)] = first + i; });
 }
 
 struct Pull {
@@ -1274,22 +1274,33 @@ void launch_fwd_sub_t(const BlendArgs& a, unsigned grid, int tile, SubMode mode,
         hipLaunchKernelGGL((k_blend_fwd_sub<false, IMP, kSubInTile>), dim3(grid), dim3(64), 0, stream, a, tile, (int)persistent);
 }
 
-// Sub-tiles from which a blend runs the tiles by falling list length (measured above next_item).
-constexpr int64_t kOrderItemsFwd = 12288, kOrderItemsBwd = 8192;
-
-// The arguments with the tile order made, or without it.
-BlendArgs with_order(const BlendArgs& a, int64_t items, int64_t from, bool persistent, hipStream_t stream) {
+// The arguments with the tile order made, or without it. It is made from kOrderItemsFwd (forward) or
+// kOrderItemsBwd (backward) sub-tiles on (orders_tiles_fwd, orders_tiles_bwd). Measured without and with it, its launch included:
+// at those sizes it gains about what its launch takes when lists are short (20,000 Gaussians over the image,
+// 640 x 480: forward 29 and 30 us, backward 38 and 41 us; 1024 x 768: 39 and 33 us, 69 and 64 us; gathered in
+// clusters, 960 x 640: 46 and 50 us, 71 and 69 us; 1280 x 1024: 49 and 44 us, 78 and 69 us). Long lists gain
+// below the limits too where they are even (1 M over 979 x 546: 95 and 76 us, 124 and 108 us) and forward lose a
+// little where they are clustered (445 and 449 us, 634 and 593 us). One 1080p view of 1 M 115 and 83 us, 165 and
+// 157 us, clustered 208 and 202 us, 392 and 335 us.
+// Upwards: with 16 x 16 tiles a forward of more than kOrderTilesFwd16 tiles mostly loses (8 x 1080p, 65,280 tiles: 1 M 575 and 616 us,
+// clustered 777 and 770 us, 0.2 M 376 and 437 us; 8 x 4K: 1.30 and 1.47 ms), with 32 x 32 tiles it gains or is even
+// (8 x 1080p 537 and 544 us, 740 and 672 us; 8 x 4K 1.23 and 1.23 ms, 1.47 and 1.42 ms; 16384 x 16384 7.3 and 6.2 ms). A
+// backward of more than kOrderTilesBwd tiles loses (65,536 tiles: 8 x 1080p 1653 and 1518 us, 1190 and 1209 us, 8 x 4K
+// 3.05 and 2.94 ms; 262,144 tiles of a 16384 x 16384 image 17.9 and 19.3 ms).
+BlendArgs with_order(const BlendArgs& a, bool use, hipStream_t stream) {
     BlendArgs r = a;
-    if (persistent || items <= from) r.tile_order = nullptr;
-    if (r.tile_order)
-        hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(kOrderThreads), 0, stream, a.ranges, (uint32_t)a.n_tiles,
-                           a.tile_order);
+    if (!use) r.tile_order = nullptr;
+    if (r.tile_order) {
+        const uint32_t n = (uint32_t)a.n_tiles, slices = (n + kOrderSlice - 1) / kOrderSlice;
+        const uint32_t slice = (n + slices - 1) / slices;  // (no slice is empty: n > slice * (slices - 1))
+        hipLaunchKernelGGL(k_tile_order, dim3(slices), dim3(kOrderThreads), 0, stream, a.ranges, n, slice, a.tile_order);
+    }
     return r;
 }
 
 hipError_t launch_fwd_sub(const BlendArgs& args, int tile, SubMode mode, bool persistent, hipStream_t stream) {
     const int64_t items = args.n_tiles * (int64_t)(tile / 8) * (tile / 8);
-    const BlendArgs a = with_order(args, items, kOrderItemsFwd, persistent, stream);
+    const BlendArgs a = with_order(args, !persistent && orders_tiles_fwd(tile, args.n_tiles), stream);
     const int64_t groups = persistent ? kPersistentGroups : items;
     const unsigned grid = (unsigned)(groups < items ? groups : items);
     if (a.importance)
@@ -1303,7 +1314,7 @@ hipError_t launch_fwd_sub(const BlendArgs& args, int tile, SubMode mode, bool pe
 
 hipError_t launch_bwd_sub(const BlendArgs& args, int tile, SubMode mode, bool persistent, hipStream_t stream) {
     const int64_t items = args.n_tiles * (int64_t)(tile / 8) * (tile / 8);
-    const BlendArgs a = with_order(args, items, kOrderItemsBwd, persistent, stream);
+    const BlendArgs a = with_order(args, !persistent && orders_tiles_bwd(tile, args.n_tiles), stream);
     const int64_t groups = persistent ? kPersistentGroups : items;
     const unsigned grid = (unsigned)(groups < items ? groups : items);
     if (mode == kSubFlags)

@@ -244,6 +244,18 @@ def test_state_bytes_sizes_the_forward_and_backward():
         == L.MEGS_ERR_ARG
 
 
+def test_state_bytes_of_the_tile_order():
+    """The order in which a backward runs its tiles costs memory only where it is made (16 x 16 and 32 x 32 tiles,
+    8,193 sub-tiles to 65,536 tiles, neither persistent nor deterministic): 4 bytes a tile beside the 36 bytes a
+    record and the work counters. (A 32 x 32 forward of more tiles orders them in the same memory.)"""
+    n, counters = 4096, 2048
+    for tile, w, h, flags, order in ((8, 4096, 4096, 0, 0), (16, 512, 512, 0, 0), (16, 1024, 1024, 0, 4096),
+                                     (16, 4096, 4096, 0, 65536), (16, 16384, 16384, 0, 0), (32, 4096, 4096, 0, 16384),
+                                     (32, 16384, 16384, 0, 262144 - 36 * n // 4 - counters // 4),
+                                     (16, 1024, 1024, L.MEGS_FLAG_PERSISTENT, 0)):
+        assert _sized(n, 1, w, h, tile, 0, flags, 0, 0).work == 36 * n + counters + 4 * order, (tile, w, flags)
+
+
 def test_stages_are_roctx_ranges():
     """Every stage's enqueue is a named ROCTX range (for rocprofv3 --marker-trace): the library imports
     the range calls and holds one name per stage."""

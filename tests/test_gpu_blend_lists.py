@@ -92,3 +92,28 @@ def test_long_lists_and_tile_order(tile, size, n):
         for p, g in out[0][1].items():
             if g is not None and g.numel():
                 assert float((g - out[1][1][p]).norm() / g.norm()) <= 1e-5, p
+
+
+@pytest.mark.parametrize("tile,sizes", [(16, [(2048, 2048)]), (16, [(2049, 2048)]), (16, [(2113, 2100), (65, 4000), (2048, 2100)]),
+                                        (16, [(4096, 4096)]), (16, [(4097, 4096)]), (32, [(4097, 4128)]), (32, [(8192, 8224)])])
+def test_tile_order_in_slices(tile, sizes):
+    """16,384 tiles (ordered in one piece), 16,512, 35,702 and 65,536 (two to four slices in the backward), 65,792
+    (none), and with 32 x 32 tiles 16,641 and 65,792 (two and five slices in the forward): the sub-tile blends run in
+    that order, with the two-stage and the one-stage sort, against the persistent launch, which runs the
+    sub-tiles as numbered: the same decisions over the same lists, so the same bits, and every tile was run."""
+    sc = S.random_scene(np.random.default_rng(5), 4000, 1, False, spread=1.5, logscale_mu=-3.5)
+    cams = [S.look_at((0.0, -4.0, 0.3 + 0.2 * i), w, h, bg=(0.3, 0.1, 0.2)) for i, (w, h) in enumerate(sizes)]
+    ds = R.DeviceScene.from_scene(sc)
+    npix = sum(c.width * c.height for c in cams)
+    dl = torch.rand(3 * npix, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    out = []
+    for flags in (L.MEGS_FLAG_PERSISTENT, 0, L.MEGS_FLAG_ONE_STAGE_SORT):
+        fr = R.forward(ds, cams, R.Config(tile, 64, subtile=8, flags=flags))
+        out.append(([fr.images.clone(), fr.buffer("T_final", npix, torch.float32).clone(),
+                     fr.buffer("last", npix, torch.int32).clone()], R.backward(ds, fr, dl)))
+    for other in out[1:]:
+        for x, y in zip(out[0][0], other[0]):
+            assert torch.equal(x, y)
+        for p, g in out[0][1].items():
+            if g is not None and g.numel():
+                assert float((g - other[1][p]).norm() / g.norm()) <= 1e-5, p
