@@ -833,6 +833,11 @@ __global__ void k_no_pairs(const uint32_t* total, int64_t capacity, uint32_t* co
     for (int64_t j = i; j < n_tiles; j += (int64_t)gridDim.x * blockDim.x) ranges[j] = make_uint2(0u, 0u);
 }
 
+// Tile ranges that a thread of the emission clears at most; more are a launch of their own: a step takes 31 ns, the
+// launch about 4 us. (One workgroup, 256 records, clearing the 4.2 M ranges of a 16384 x 16384 image in 8 x 8 tiles:
+// emission 511 us, with the launch 30 us.)
+constexpr int64_t kClearEach = 128;
+
 // S: sub-tiles per tile edge when the keys carry sub-tile flags (tile = 8 S), 0 without flags.
 template <int S>
 __global__ __launch_bounds__(kEmitThreads) void k_emit(Records rec, const ViewInfo* __restrict__ views, int64_t n,
@@ -1243,6 +1248,12 @@ hipError_t launch_emit(const Records& rec, const ViewInfo* views, int nv, int64_
     }
     if (sub && (sub != 8 || !tile_keys || (tile != 16 && tile != 32))) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((n_records + kEmitThreads - 1) / kEmitThreads));
+    // few records on many tiles: the emission's threads are too few to clear the ranges in passing
+    if (n_tiles > kClearEach * kEmitThreads * (int64_t)grid.x) {
+        const hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t*>(ranges), 0u, 2 * n_tiles, stream);
+        if (e != hipSuccess) return e;
+        n_tiles = 0;
+    }
     if (!sub)
         hipLaunchKernelGGL(k_emit<0>, grid, dim3(kEmitThreads), 0, stream, rec, views, n, tile, order, offsets,
                            total, n_records, tile_keys, keys64, vals, capacity, status, count, ranges, n_tiles);
