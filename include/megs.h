@@ -141,7 +141,7 @@ typedef struct {
                               library's choice (one wave per 8x8 tile; 16x16 and 32x32 tiles blend
                               per 8x8 sub-tile, one independent wave each, with the results of the
                               per-tile kernels) */
-    int64_t pair_capacity; /* 0: size the pair table from the counted pairs (one host sync per
+    int64_t pair_capacity; /* 0: size the pair table from the counted pairs (one host wait per
                               forward); > 0: fixed capacity, no host sync, overflow reported
                               as MEGS_ERR_CAPACITY by megs_state_status */
     int32_t subtile;       /* 0: blend per tile (waves as above); 8: blend per 8x8 sub-tile with one
@@ -218,8 +218,10 @@ typedef struct {
 /*
  * Forward render of n_views views (front-to-back compositing, Sec. 3.1; SG colour, Sec. 3.2).
  * images: device float[3 * NP], written. state: host struct, filled. Returns MEGS_OK or an
- * error status; with pair_capacity == 0 it synchronises the stream once to size the pair table,
- * and returns MEGS_ERR_CAPACITY when the records list more than 2^31 - 1 tile pairs.
+ * error status; with pair_capacity == 0 it waits once, for the count of the tile pairs (all earlier
+ * work of the stream is then done), to size the pair table, and returns MEGS_ERR_CAPACITY when the
+ * records list more than 2^31 - 1 tile pairs. What it enqueues runs on after the return, in stream
+ * order; a call that fails on the count or on the pair table's allocation leaves the stream idle.
  */
 megs_status megs_render_forward(const megs_scene *scene, const megs_camera *cams, int32_t n_views,
                                 const megs_config *cfg, megs_alloc_fn alloc, void *alloc_ctx,
@@ -236,11 +238,11 @@ megs_status megs_render_forward(const megs_scene *scene, const megs_camera *cams
  * (megs_render_backward accepts that state). The device current on the calling thread must be the
  * stream's device. All calls on one device share its array, so calls that overlap in time on one
  * device (other streams, other threads) race: the caller serialises them.
- * pair_capacity == 0 synchronises the stream once, as megs_render_forward does; pair_capacity > 0
+ * pair_capacity == 0 waits once for the count, as megs_render_forward does; pair_capacity > 0
  * does not (overflow is then reported by megs_state_status).
  * Errors: as megs_render_forward, and MEGS_ERR_CAPACITY, before anything is launched, when the frame
  * (plus a fixed pair table) needs more than MEGS_NOALLOC_SCRATCH_BYTES, or, after the one
- * synchronisation, when the counted pairs do not fit beside it.
+ * wait, when the counted pairs do not fit beside it.
  */
 #define MEGS_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 megs_status megs_render_forward_noalloc(const megs_scene *scene, const megs_camera *cams, int32_t n_views,
@@ -413,7 +415,9 @@ megs_status megs_penalty_grad(int64_t count, float delta, const float *x, const 
  *   kept      int32[scene.n]        source index of each kept Gaussian (ascending)
  *   lobe_src  int32[scene.n_lobes]  source element of each kept lobe in the input's sharp plane
  *                                   (dense input: l * n + i; compressed rows: the lobe index)
- * The call synchronises the stream once (to learn the output sizes). Thresholds must not be NaN.
+ * The call waits once for the output sizes (all earlier work of the stream is then done); what it
+ * enqueues after them runs on after the return, in stream order, and a call that fails after the
+ * wait leaves the stream idle. Thresholds must not be NaN.
  * Errors: MEGS_ERR_ARG for a bad scene or malformed lobe offsets, MEGS_ERR_ALLOC, MEGS_ERR_HIP.
  */
 typedef struct {

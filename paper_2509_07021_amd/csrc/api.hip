@@ -804,6 +804,12 @@ megs_status forward_impl(const megs_scene* sc, const megs_camera* cams, int32_t 
     if (bad_alloc(fm))
         return fail(MEGS_ERR_ALLOC, "allocation of %zu bytes failed or not 256-byte aligned", frame_bytes(L, work));
     Frame f = carve_frame(fm, L, work);
+    // The count is there before the kernel that forms it has ended: a call that ends on it waits for the
+    // stream, so that the caller may free or reuse the frame.
+    auto refused = [s](megs_status e) {
+        (void)hipStreamSynchronize(s);
+        return e;
+    };
     int64_t cap = cfg->pair_capacity;
     int64_t counted = -1;
     if (cap > 0) {
@@ -814,17 +820,20 @@ megs_status forward_impl(const megs_scene* sc, const megs_camera* cams, int32_t 
         int32_t bad_lobes = 0;
         st = front_and_count(sc, L, cfg, f, s, &total, &bad_lobes);
         if (st != MEGS_OK) return st;
-        if (bad_lobes) return fail(MEGS_ERR_ARG, "malformed lobe_off (compressed-row lobes)");
+        if (bad_lobes) return refused(fail(MEGS_ERR_ARG, "malformed lobe_off (compressed-row lobes)"));
         if (total > kMaxPairs)
-            return fail(MEGS_ERR_CAPACITY, "the records list %s%u tile pairs; a key table holds at most %u",
-                        total == 0xffffffffu ? "at least " : "", total, kMaxPairs);
+            return refused(fail(MEGS_ERR_CAPACITY, "the records list %s%u tile pairs; a key table holds at most %u",
+                                total == 0xffffffffu ? "at least " : "", total, kMaxPairs));
         counted = total;
         cap = total;
     }
     const bool alt = alt_in_work(L, cfg, cap, f.work_bytes);
     const size_t pbytes = pairs_bytes(cap, one_stage, det, alt);
     void* pm = alloc(ctx, pbytes);
-    if (bad_alloc(pm)) return fail(MEGS_ERR_ALLOC, "allocation of %zu bytes failed or not 256-byte aligned", pbytes);
+    if (bad_alloc(pm)) {
+        st = fail(MEGS_ERR_ALLOC, "allocation of %zu bytes failed or not 256-byte aligned", pbytes);
+        return counted >= 0 ? refused(st) : st;
+    }
     Pairs p = carve_pairs(pm, cap, one_stage, det, alt ? f.work : nullptr);
     st = enqueue_back(sc, L, cfg, f, p, images, state, s, importance);
     state->n_pairs = counted >= 0 ? counted : cap;
@@ -1111,7 +1120,11 @@ megs_status megs_compact(const megs_scene* scene, double opacity_min, double sha
         ht[0] = (uint32_t)hs[4];
         ht[1] = (uint32_t)hs[5];
     }
-    if (hs[kStatusBadLobes]) return fail(MEGS_ERR_ARG, "malformed lobe_off (compressed-row lobes)");
+    // (as in forward_impl: a call that ends here leaves the working block idle)
+    if (hs[kStatusBadLobes]) {
+        (void)hipStreamSynchronize(s);
+        return fail(MEGS_ERR_ARG, "malformed lobe_off (compressed-row lobes)");
+    }
     const int64_t no = ht[0], lo = ht[1];
     a.n_out = no;
     a.l_out = lo;
@@ -1122,7 +1135,10 @@ megs_status megs_compact(const megs_scene* scene, double opacity_min, double sha
                           align256(sizeof(int32_t) * (no + 1)) + align256(sizeof(int32_t) * no) +
                           align256(sizeof(int32_t) * lo) + 256 * 12;
     void* om = alloc(alloc_ctx, obytes);
-    if (bad_alloc(om)) return fail(MEGS_ERR_ALLOC, "allocation of %zu bytes failed or not 256-byte aligned", obytes);
+    if (bad_alloc(om)) {
+        (void)hipStreamSynchronize(s);
+        return fail(MEGS_ERR_ALLOC, "allocation of %zu bytes failed or not 256-byte aligned", obytes);
+    }
     Carver o{static_cast<char*>(om), 0};
     a.pos = o.take<char>((int64_t)(eg * 3 * no));
     a.logscale = o.take<char>((int64_t)(eg * 3 * no));
