@@ -6,7 +6,6 @@
 #include <string.h>
 
 #include <algorithm>
-#include <chrono>
 #include <mutex>
 #include <new>
 #include <utility>
@@ -105,84 +104,7 @@ __global__ void k_set_views(ViewInfo* dst, ViewChunk c) {
     if ((int)threadIdx.x < c.count) dst[threadIdx.x] = c.v[threadIdx.x];
 }
 
-// Slots of pinned host memory through which a kernel hands a counted total to the host that waits for it
-// (HostCount). One 4 KiB block for the process, portable over devices, its 64 slots lent to one call each;
-// a call that finds none, or whose stream is being captured, copies the words with the stream instead.
-// Measured on the eager forward of 2,000 Gaussians: two copies to pageable memory and the
-// synchronisation left the GPU idle for 100 us; the polled slot for 20 us.
-class HostSlots {
-public:
-    HostCount* take(uint32_t* seq) {
-        std::lock_guard<std::mutex> lock(mu_);
-        if (!base_ && !tried_) {
-            tried_ = true;
-            void* p = nullptr;
-            if (hipHostMalloc(&p, sizeof(HostCount) * kSlots, hipHostMallocPortable | hipHostMallocMapped |
-                                                                  hipHostMallocCoherent) == hipSuccess) {
-                memset(p, 0, sizeof(HostCount) * kSlots);
-                base_ = static_cast<HostCount*>(p);
-                for (int i = 0; i < kSlots; ++i) free_.push_back(i);
-            } else {
-                (void)hipGetLastError();
-            }
-        }
-        if (free_.empty()) return nullptr;
-        HostCount* s = base_ + free_.back();
-        free_.pop_back();
-        if (++seq_ == 0) ++seq_;
-        *seq = seq_;
-        return s;
-    }
-    void give(HostCount* s) {
-        std::lock_guard<std::mutex> lock(mu_);
-        free_.push_back((int)(s - base_));
-    }
-
-private:
-    static constexpr int kSlots = 64;
-    std::mutex mu_;
-    HostCount* base_ = nullptr;
-    bool tried_ = false;
-    std::vector<int> free_;
-    uint32_t seq_ = 0;
-};
 HostSlots g_slots;
-
-// One call's use of a slot: taken before the launches, waited for after them. A slot that was waited for
-// in vain is not lent again (a kernel might still write it).
-struct SlotUse {
-    HostCount* slot = nullptr;
-    uint32_t seq = 0;
-    hipStream_t stream;
-    explicit SlotUse(hipStream_t s) : stream(s) {
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
-            (void)hipGetLastError();
-            return;
-        }
-        if (cap == hipStreamCaptureStatusNone) slot = g_slots.take(&seq);
-    }
-    // Polls for a while (the wait is normally tens of microseconds), then waits for the stream.
-    hipError_t wait(uint32_t* total, int32_t* bad_lobes, uint32_t* total2 = nullptr) {
-        const auto t0 = std::chrono::steady_clock::now();
-        bool there = false;
-        while (!(there = __atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) == seq)) {
-            for (int i = 0; i < 32; ++i) __builtin_ia32_pause();
-            if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) break;
-        }
-        if (!there) {
-            const hipError_t e = hipStreamSynchronize(stream);
-            if (e != hipSuccess) return e;
-            if (__atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) != seq) return hipErrorUnknown;
-        }
-        *total = slot->total;
-        if (total2) *total2 = slot->total2;
-        *bad_lobes = slot->bad_lobes;
-        g_slots.give(slot);
-        slot = nullptr;
-        return hipSuccess;
-    }
-};
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -767,12 +689,8 @@ bool backward_reuses(const megs_config* cfg, const megs_state* st, size_t gbytes
 // enqueue_front, then the host's wait for what it counted.
 megs_status front_and_count(const megs_scene* sc, const Layout& L, const megs_config* cfg, Frame& f, hipStream_t s,
                             uint32_t* total, int32_t* bad_lobes) {
-    SlotUse slot(s);
+    SlotUse slot(g_slots, s);
     const bool polled = slot.slot && L.nr > 0;  // (without records no scan runs)
-    if (slot.slot && !polled) {
-        g_slots.give(slot.slot);
-        slot.slot = nullptr;
-    }
     const megs_status st = enqueue_front(sc, L, cfg, f, s, polled ? &slot : nullptr);
     if (st != MEGS_OK) return st;
     if (polled) {
@@ -1108,7 +1026,7 @@ megs_status megs_compact(const megs_scene* scene, double opacity_min, double sha
     uint32_t ht[2] = {0, 0};
     int32_t hs[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (n > 0) {
-        SlotUse slot(s);
+        SlotUse slot(g_slots, s);
         a.host = slot.slot;
         a.seq = slot.seq;
         HIP_TRY(launch_compact_mark(a, s));

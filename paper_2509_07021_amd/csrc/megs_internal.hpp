@@ -5,6 +5,7 @@
 #include <hip/hip_fp16.h>
 #include <stdint.h>
 
+#include "host_slots.hpp"
 #include "megs.h"
 
 namespace megs {
@@ -354,15 +355,7 @@ hipError_t launch_project_bwd(const SceneDev& sc, const ViewInfo* views, int nv,
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t count, hipStream_t stream);
 hipError_t launch_iota(uint32_t* p, int64_t count, hipStream_t stream);
 
-// A scan's grand total: to device memory, and, for a call that waits for it, to host memory as well
-// (pinned, coherent): a slot whose sequence number the host gives out, written last.
-struct HostCount {
-    uint32_t total;
-    int32_t bad_lobes;
-    uint32_t seq;
-    uint32_t total2;  // of a compaction: kept lobes
-    uint32_t pad[12];  // one slot per 64 bytes
-};
+// A scan's grand total: to device memory, and, for a call that waits for it, to host memory as well.
 struct ScanTotal {
     uint32_t* total = nullptr;
     HostCount* host = nullptr;  // null: no host copy
