@@ -41,8 +41,11 @@ public:
 private:
     static constexpr int kSlots = 64;
 
-    // A refused allocation is tried again by the next call.
+    // Another thread may be capturing a stream in global mode, where an allocation is refused unless this
+    // thread asks for the relaxed mode. A refused allocation is tried again by the next call.
     void allocate() {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
         void* p = nullptr;
         if (hipHostMalloc(&p, sizeof(HostCount) * kSlots,
                           hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
@@ -52,6 +55,7 @@ private:
         } else {
             (void)hipGetLastError();
         }
+        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
 
     std::mutex mu_;

@@ -1,4 +1,4 @@
-// The library's pinned slots (host_slots.hpp) with the four runtime calls they make replaced by stand-ins: no GPU, no
+// The library's pinned slots (host_slots.hpp) with the five runtime calls they make replaced by stand-ins: no GPU, no
 // HIP library. Ends with status 0, or prints the check that failed and ends with status 1.
 #include <stdio.h>
 #include <stdlib.h>
@@ -10,10 +10,12 @@ using namespace megs;
 static int g_syncs, g_mallocs;
 static hipError_t g_sync = hipSuccess, g_malloc = hipSuccess, g_capturing = hipSuccess;
 static hipStreamCaptureStatus g_status = hipStreamCaptureStatusNone;
+static hipStreamCaptureMode g_mode = hipStreamCaptureModeGlobal, g_mode_at_malloc;
 
 extern "C" {
 hipError_t hipHostMalloc(void** p, size_t bytes, unsigned int) {
     ++g_mallocs;
+    g_mode_at_malloc = g_mode;
     if (g_malloc == hipSuccess) *p = calloc(1, bytes);
     return g_malloc;
 }
@@ -25,6 +27,12 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
 hipError_t hipStreamSynchronize(hipStream_t) {
     ++g_syncs;
     return g_sync;
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) {
+    const hipStreamCaptureMode old = g_mode;
+    g_mode = *m;
+    *m = old;
+    return hipSuccess;
 }
 }
 
@@ -47,7 +55,7 @@ int main() {
     HostSlots pool;
     uint32_t total = 0, total2 = 0;
     int32_t bad = 0;
-    {  // a refused allocation: no slot, and the next call tries again
+    {  // a refused allocation: no slot, and the next call tries again, in the relaxed capture mode
         g_malloc = hipErrorOutOfMemory;
         SlotUse u(pool, nullptr);
         CHECK(!u.slot && g_mallocs == 1);
@@ -59,7 +67,7 @@ int main() {
         write_slot(u, 7 + i);
         CHECK(u.wait(&total, &bad, &total2) == hipSuccess && total == 7u + i && total2 == 8u + i && bad == 3 && !u.slot);
     }
-    CHECK(g_mallocs == 2);
+    CHECK(g_mallocs == 2 && g_mode_at_malloc == hipStreamCaptureModeRelaxed && g_mode == hipStreamCaptureModeGlobal);
     CHECK(g_syncs == 0);
     for (int i = 0; i < 200; ++i) {  // calls that end before they wait: the stream is waited for, the slot given back
         SlotUse u(pool, nullptr);
