@@ -167,10 +167,10 @@ struct TileCtx {
     float bg[3];
 };
 
-__device__ __forceinline__ TileCtx tile_ctx(const BlendArgs& a, int64_t t, int TILE) {
+__device__ __forceinline__ TileCtx tile_ctx(const BlendArgs& a, int view, int64_t t, int TILE) {
     TileCtx c;
     c.tile = t;
-    c.view = view_of_tile(a.views, a.nv, t);
+    c.view = view;
     const ViewInfo& vw = a.views[c.view];
     const int64_t lt = t - vw.tile_off;
     c.x0 = (int)(lt % vw.tiles_x) * TILE;
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_blend_fwd(BlendArgs a, int batch
     uint32_t n_blended = 0, n_evaluated = 0;
     for (int64_t t = next_tile(a, -1, persistent, &work_slot); t < a.n_tiles;
          t = next_tile(a, t, persistent, &work_slot)) {
-        const TileCtx c = tile_ctx(a, t, TILE);
+        const TileCtx c = tile_ctx(a, view_of_tile(a.views, a.nv, t), t, TILE);
         const uint2 rg = a.ranges[t];
         // T < 0 marks a pixel that has terminated (|T| is its final transmittance) or lies outside
         // the image; this keeps the per-pixel state in float registers.
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_blend_bwd(BlendArgs a, int batch
     const float px = lx + 0.5f;
     for (int64_t t = next_tile(a, -1, persistent, &work_slot); t < a.n_tiles;
          t = next_tile(a, t, persistent, &work_slot)) {
-        const TileCtx c = tile_ctx(a, t, TILE);
+        const TileCtx c = tile_ctx(a, view_of_tile(a.views, a.nv, t), t, TILE);
         const uint2 rg = a.ranges[t];
         const int64_t plane = (int64_t)c.width * c.height;
         float T[PPT], P[PPT], dl[PPT][3];  // P = S . dL/dC, as in the sub-tile backward
@@ -587,6 +587,7 @@ static_assert(kSlices % kXcds == 0 && kSlices <= 64 && kSlices * kQueueStride <=
 // does not queue up at one (14.6 us for 16,320 tiles, 5.3 us for 2,040: two passes of latency; in one slice
 // a million tiles would take some 0.7 ms).
 constexpr int kOrderSlice = 16384;
+constexpr uint32_t kEmptyTile = 1u << 31;  // set in the order beside a tile whose list is empty
 constexpr int kOrderThreads = 1024;
 __global__ __launch_bounds__(kOrderThreads) void k_tile_order(const uint2* __restrict__ ranges, uint32_t n_tiles,
                                                               uint32_t slice, uint32_t* __restrict__ order) {
@@ -627,7 +628,9 @@ __global__ __launch_bounds__(kOrderThreads) void k_tile_order(const uint2* __res
     count[2 * t] = inc - c0 - c1;
     count[2 * t + 1] = inc - c1;
     __syncthreads();
-    for_tiles([&](uint32_t i, uint32_t b) { order[first + atomicAdd(&count[b], 1u)] = first + i; });
+    for_tiles([&](uint32_t i, uint32_t b) {
+        order[first + atomicAdd(&count[b], 1u)] = first + i | (b >> 3 == 255u ? kEmptyTile : 0u);
+    });
 }
 
 struct Pull {
@@ -641,14 +644,16 @@ __device__ __forceinline__ void slice_of(int64_t n_items, int s, int64_t& base, 
 }
 
 __device__ __forceinline__ int64_t next_item(const BlendArgs& a, int64_t prev, bool persistent, int64_t n_items,
-                                             Pull& q, bool by_xcd, int sub_log2) {
+                                             Pull& q, bool by_xcd, int sub_log2, bool& empty) {
+    empty = false;  // (true: the item's tile has an empty list; false: it may have)
     if (!persistent) {
         if (prev >= 0) return n_items;
         if (!a.tile_order) return by_xcd ? xcd_item((int64_t)blockIdx.x, n_items) : (int64_t)blockIdx.x;
         const uint32_t b = blockIdx.x, run = sub_log2 + (by_xcd ? 0 : 2), rest = (uint32_t)n_items >> (run + 3) << (run + 3);
         uint32_t i = b;  // (past the last whole run of every XCD: as they come)
         if (b < rest) i = ((b >> 3 >> run) * kXcds + (b & 7u)) << run | (b >> 3 & ((1u << run) - 1u));
-        const uint32_t t = a.tile_order[i >> sub_log2];
+        const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.tile_order[i >> sub_log2]), t = e & ~kEmptyTile;
+        empty = e != t;
         return ((int64_t)t << sub_log2) + (i & ((1u << sub_log2) - 1u));
     }
     const int lane = __lane_id();
@@ -688,20 +693,27 @@ struct SubCtx {
     TileCtx c;
     int sx, sy;       // sub-tile origin inside the tile
     int sidx;         // sub-tile index r S + c (the bit of its flag in the tile keys)
-    int64_t t;
 };
 
-__device__ __forceinline__ SubCtx sub_ctx(const BlendArgs& a, int64_t w, int tile) {
+__device__ __forceinline__ SubCtx sub_ctx(const BlendArgs& a, int64_t t, int s, int tile) {
     constexpr int SUB = 8;
-    const int per_row = tile / SUB, nsub = per_row * per_row;
+    const int per_row = tile / SUB;
     SubCtx q;
-    q.t = w / nsub;
-    const int s = (int)(w - q.t * nsub);
     q.sidx = s;
     q.sx = (s % per_row) * SUB;
     q.sy = (s / per_row) * SUB;
-    q.c = tile_ctx(a, q.t, tile);
+    // the last view whose first tile is not behind t: one load, by as many lanes as there are views
+    static_assert(MEGS_MAX_VIEWS <= kWave, "a lane for each view");
+    const int lane = __lane_id();
+    const int view = __popcll(__ballot(lane < a.nv && a.views[min(lane, a.nv - 1)].tile_off <= t)) - 1;
+    q.c = tile_ctx(a, view, t, tile);
     return q;
+}
+
+// The tile's list, in scalar registers, so that branches on it are branches of the wave.
+__device__ __forceinline__ uint2 range_of(const BlendArgs& a, int64_t t) {
+    const uint2 r = a.ranges[t];
+    return make_uint2((uint32_t)__builtin_amdgcn_readfirstlane((int)r.x), (uint32_t)__builtin_amdgcn_readfirstlane((int)r.y));
 }
 
 // How a sub-tile kernel frames its entries and chooses the ones it keeps; a template argument, so each
@@ -857,10 +869,24 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kSub
     const int sub_log2 = tile == 32 ? 4 : 2;  // (sub-tiles of a 32 x 32 or a 16 x 16 tile)
     const int64_t n_items = a.n_tiles << sub_log2;
     uint64_t n_blended = 0, n_evaluated = 0;  // of the wave
+    const int n_sub = 1 << sub_log2;
     Pull pull;
-    for (int64_t w = next_item(a, -1, persistent, n_items, pull, true, sub_log2); w < n_items;
-         w = next_item(a, w, persistent, n_items, pull, true, sub_log2)) {
-        const SubCtx q = sub_ctx(a, w, tile);
+    bool empty;
+    for (int64_t w = next_item(a, -1, persistent, n_items, pull, true, sub_log2, empty); w < n_items;
+         w = next_item(a, w, persistent, n_items, pull, true, sub_log2, empty)) {
+        const int64_t t = w >> sub_log2;
+        int sub = (int)w & (n_sub - 1);
+        // A tile with an empty list is one wave's (in turn one of the tile's, so that the waves with work are spread
+        // over the CUs): it writes all of the tile's pixels, and the others end before they look for their view. (Each writing its own 8 x 8 pixels, a forward of a few records on a 16384 x 16384 image
+        // in 32 x 32 tiles took 2.6 ms, per tile 1.2 ms.)
+        const bool writer = sub == ((int)t & (n_sub - 1));
+        if (empty && !writer) continue;
+        const uint2 rg = range_of(a, t);
+        if (rg.x == rg.y) {
+            if (!writer) continue;
+            sub = 0;
+        }
+        const SubCtx q = sub_ctx(a, t, sub, tile);
         const TileCtx& c = q.c;
         const int lx = q.sx + (lane & 7), ly = q.sy + (lane >> 3);
         const bool inside = c.x0 + lx < c.width && c.y0 + ly < c.height;
@@ -870,7 +896,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kSub
         if (!alive) continue;  // a sub-tile past the image edge has no pixel
         float T = 1.0f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
         uint32_t last = 0;
-        const uint2 rg = a.ranges[q.t];
         // the frame the entries are staged in (the tile or the sub-tile): its corner, the sub-tile's corner
         // in it, and the pixel centre in it
         const int bx = MODE == kSubInTile ? q.sx : 0, by = MODE == kSubInTile ? q.sy : 0;
@@ -976,16 +1001,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kSub
                 wave_sync();
             }
         }
-        if (inside) {
-            const int x = c.x0 + lx, y = c.y0 + ly;
-            const int64_t p = (int64_t)y * c.width + x;
-            const int64_t plane = (int64_t)c.width * c.height;
-            float* img = a.image + 3 * c.pix_off;
-            img[p] = __fmaf_rn(T, c.bg[0], C0);
-            img[plane + p] = __fmaf_rn(T, c.bg[1], C1);
-            img[2 * plane + p] = __fmaf_rn(T, c.bg[2], C2);
-            a.T_final[c.pix_off + p] = T;
-            a.last[c.pix_off + p] = last;
+        int x = c.x0 + lx, y = c.y0 + ly;
+        for (int s = sub;;) {  // (of an empty list: every sub-tile of the tile)
+            if (x < c.width && y < c.height) {
+                const int64_t p = (int64_t)y * c.width + x;
+                const int64_t plane = (int64_t)c.width * c.height;
+                float* img = a.image + 3 * c.pix_off;
+                img[p] = __fmaf_rn(T, c.bg[0], C0);
+                img[plane + p] = __fmaf_rn(T, c.bg[1], C1);
+                img[2 * plane + p] = __fmaf_rn(T, c.bg[2], C2);
+                a.T_final[c.pix_off + p] = T;
+                a.last[c.pix_off + p] = last;
+            }
+            if (rg.x != rg.y || ++s == n_sub) break;
+            const bool row_end = (s & ((tile >> 3) - 1)) == 0;
+            x += row_end ? 8 - tile : 8;
+            y += row_end ? 8 : 0;
         }
     }
     if (STATS) {
@@ -1042,9 +1073,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     const int sub_log2 = tile == 32 ? 4 : 2;
     const int64_t n_items = a.n_tiles << sub_log2;
     Pull pull;
-    for (int64_t w = next_item(a, -1, persistent, n_items, pull, false, sub_log2); w < n_items;
-         w = next_item(a, w, persistent, n_items, pull, false, sub_log2)) {
-        const SubCtx q = sub_ctx(a, w, tile);
+    bool empty;
+    for (int64_t w = next_item(a, -1, persistent, n_items, pull, false, sub_log2, empty); w < n_items;
+         w = next_item(a, w, persistent, n_items, pull, false, sub_log2, empty)) {
+        if (empty) continue;
+        const int64_t t = w >> sub_log2;
+        const uint2 rg = range_of(a, t);
+        if (rg.x == rg.y) continue;  // (before any pixel is read)
+        const SubCtx q = sub_ctx(a, t, (int)(w & ((1 << sub_log2) - 1)), tile);
         const TileCtx& c = q.c;
         const int lx = q.sx + (lane & 7), ly = q.sy + (lane >> 3);
         const int x = c.x0 + lx, y = c.y0 + ly;
@@ -1074,7 +1110,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         dlr[0][lane] = dl0;
         dlr[1][lane] = dl1;
         dlr[2][lane] = dl2;
-        const uint2 rg = a.ranges[q.t];
         // the frame, as in the forward; the summing lane's pixel row in it
         const int bx = MODE == kSubInTile ? q.sx : 0, by = MODE == kSubInTile ? q.sy : 0;
         const double fx0 = (double)(c.x0 + q.sx - bx), fy0 = (double)(c.y0 + q.sy - by);

@@ -117,3 +117,38 @@ def test_tile_order_in_slices(tile, sizes):
         for p, g in out[0][1].items():
             if g is not None and g.numel():
                 assert float((g - other[1][p]).norm() / g.norm()) <= 1e-5, p
+
+
+@pytest.mark.parametrize("tile,subtile", [(16, 0), (32, 0), (16, 8), (32, 8)])
+@pytest.mark.parametrize("sizes", [[(1003, 803)], [(121, 77)], [(33, 31)] * 63 + [(200, 17)]])
+def test_tiles_with_empty_lists(tile, subtile, sizes):
+    """A few small Gaussians on images whose tiles are mostly empty, ragged at both edges, one view and as many as there
+    can be: every stage of the one view against the oracle, images and gradients against the per-tile kernels', and the
+    background exact where nothing is included."""
+    sc = S.random_scene(np.random.default_rng(11), 40, 1, False, spread=0.3, logscale_mu=-5.0)
+    cams = [S.look_at((0.0, -4.0, 0.3 + 0.01 * i), w, h, bg=(0.3, 0.1 + 0.01 * i, 0.2)) for i, (w, h) in enumerate(sizes)]
+    cfg = R.Config(tile, 64, subtile=subtile)
+    if len(cams) == 1:
+        _run_all_stages(sc, cams, cfg)
+    ds = R.DeviceScene.from_scene(sc)
+    npix = sum(c.width * c.height for c in cams)
+    dl = torch.rand(3 * npix, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    out = []
+    for c in (cfg, R.Config(tile, 64, waves=4)):
+        torch.full((64 << 20,), float("nan"), device="cuda")  # what the allocator hands out next holds NaN
+        fr = R.forward(ds, cams, c)
+        out.append((fr.images.clone(), fr.buffer("T_final", npix, torch.float32).clone(),
+                    fr.buffer("last", npix, torch.int32).clone(), R.backward(ds, fr, dl)))
+    off = 0
+    for c in cams:
+        n = c.width * c.height
+        none = out[0][2][off:off + n] == 0
+        assert bool(none.any()) and bool(torch.equal(out[0][1][off:off + n][none], torch.ones_like(out[0][1][off:off + n][none])))
+        for ch in range(3):
+            plane = out[0][0][3 * off + ch * n:3 * off + (ch + 1) * n]
+            assert bool((plane[none] == float(np.float32(c.bg[ch]))).all())
+        off += n
+    assert float((out[0][0] - out[1][0]).abs().max()) <= 1e-5
+    for p, g in out[1][3].items():
+        if g is not None and g.numel():
+            assert float((g - out[0][3][p]).norm() / g.norm()) <= 1e-4, p
