@@ -574,6 +574,7 @@ megs_status enqueue_back(const megs_scene* sc, const Layout& L, const megs_confi
     a.stats = (cfg->flags & MEGS_FLAG_STATS) ? reinterpret_cast<unsigned long long*>(f.status + 4) : nullptr;
     a.importance = importance;
     a.n = L.n;
+    a.records = L.nr; a.pairs = p.capacity;
     if (persistent) HIP_TRY(launch_fill_u32(f.queue, 0u, kQueueWords, s));
     {
         StageTimer t(MEGS_STAGE_BLEND_FWD, s);
@@ -631,6 +632,7 @@ megs_status enqueue_backward(const megs_scene* sc, const Layout& L, const megs_c
     a.views = static_cast<const ViewInfo*>(st->internal);
     a.nv = L.nv; a.n_tiles = L.n_tiles;
     a.n = L.n;
+    a.records = L.nr; a.pairs = st->pair_capacity;
     a.rec = static_cast<const PackedRec*>(st->packed);
     a.tkeys = sub_masks(cfg, L) ? static_cast<const uint32_t*>(st->tile_keys) : nullptr;
     a.vals = static_cast<const uint32_t*>(st->vals);

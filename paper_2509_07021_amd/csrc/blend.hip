@@ -1365,9 +1365,11 @@ hipError_t launch_bwd_sub(const BlendArgs& args, int tile, SubMode mode, bool pe
 // tile's frame, so that their results are those of the per-tile kernels (the forward's bit for bit): a wave
 // then walks only the entries that reach its 8 x 8 pixels, and no wave waits for another. The per-tile
 // kernels serve the wave counts a caller names, 8 x 8 tiles, the fragment statistics (they count tested
-// fragments) and the deterministic backward (one slot of sums per tile and entry).
-bool sub_in_tile(const BlendArgs& a, int tile, int waves) {
-    return waves == 0 && tile > 8 && !a.stats && !a.grad_pair;
+// fragments), the deterministic backward (one slot of sums per tile and entry), and the sizes at which they
+// are faster (blends_by_sub_tile).
+bool sub_in_tile(const BlendArgs& a, BlendKind kind, int tile, int waves) {
+    return waves == 0 && tile > 8 && !a.stats && !a.grad_pair &&
+           blends_by_sub_tile(kind, tile, a.n_tiles, a.records, a.pairs);
 }
 
 int waves_or_default(int waves, int tile) { return waves ? waves : (tile == 8 ? 1 : 4); }
@@ -1379,7 +1381,8 @@ hipError_t launch_blend_fwd(const BlendArgs& a, int tile, int waves, int batch, 
     if (a.n_tiles <= 0) return hipSuccess;
     if (subtile == 8 && tile > 8)
         return launch_fwd_sub(a, tile, a.tkeys ? kSubFlags : kSubReach, persistent, stream);
-    if (sub_in_tile(a, tile, waves)) return launch_fwd_sub(a, tile, kSubInTile, persistent, stream);
+    if (sub_in_tile(a, a.importance ? kBlendImportance : kBlendForward, tile, waves))
+        return launch_fwd_sub(a, tile, kSubInTile, persistent, stream);
     waves = waves_or_default(waves, tile);
     if (tile == 8 && waves == 1) return launch_fwd_t<8, 1>(a, batch, persistent, stream);
     if (tile == 16 && waves == 1) return launch_fwd_t<16, 1>(a, batch, persistent, stream);
@@ -1396,7 +1399,7 @@ hipError_t launch_blend_bwd(const BlendArgs& a, int tile, int waves, int batch, 
     if (a.n_tiles <= 0) return hipSuccess;
     if (subtile == 8 && tile > 8 && !a.grad_pair)
         return launch_bwd_sub(a, tile, a.tkeys ? kSubFlags : kSubReach, persistent, stream);
-    if (sub_in_tile(a, tile, waves)) return launch_bwd_sub(a, tile, kSubInTile, persistent, stream);
+    if (sub_in_tile(a, kBlendBackward, tile, waves)) return launch_bwd_sub(a, tile, kSubInTile, persistent, stream);
     waves = waves_or_default(waves, tile);
     if (tile == 8 && waves == 1) return launch_bwd_t<8, 1>(a, batch, persistent, stream);
     if (tile == 16 && waves == 1) return launch_bwd_t<16, 1>(a, batch, persistent, stream);

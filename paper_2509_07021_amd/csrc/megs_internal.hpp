@@ -5,6 +5,7 @@
 #include <hip/hip_fp16.h>
 #include <stdint.h>
 
+#include "blend_rules.hpp"
 #include "host_slots.hpp"
 #include "megs.h"
 
@@ -429,18 +430,9 @@ struct BlendArgs {
     unsigned long long* stats;  // forward fragment counters [blended, evaluated] (null: not counted)
     float* importance;          // forward: per-Gaussian sum of blending weights (null: not computed)
     int64_t n;                  // Gaussians per view (record r of view v is Gaussian r - v n)
+    int64_t records, pairs;     // records of all views, and the pair table's capacity (blends_by_sub_tile)
     uint32_t* tile_order;       // [n_tiles] room for the order in which the tiles are run (null: as numbered)
 };
-// Does a sub-tile blend (unless persistent) run its tiles by list length, given memory for the order? The limits
-// are measured where the order is made (with_order, blend.hip).
-constexpr int64_t kOrderItemsFwd = 12288, kOrderTilesFwd16 = 16384;
-constexpr int64_t kOrderItemsBwd = 8192, kOrderTilesBwd = 65536;
-constexpr bool orders_tiles_fwd(int tile, int64_t n_tiles) {
-    return tile > 8 && (tile == 32 || n_tiles <= kOrderTilesFwd16) && n_tiles * (tile / 8) * (tile / 8) > kOrderItemsFwd;
-}
-constexpr bool orders_tiles_bwd(int tile, int64_t n_tiles) {
-    return tile > 8 && n_tiles <= kOrderTilesBwd && n_tiles * (tile / 8) * (tile / 8) > kOrderItemsBwd;
-}
 // subtile 8 (with 16 x 16 or 32 x 32 tiles): one independent wave per 8 x 8 sub-tile walking its
 // tile's list (the deterministic backward keeps the per-tile kernels). waves 0: the library's choice.
 hipError_t launch_blend_fwd(const BlendArgs& a, int tile, int waves, int batch, bool persistent, hipStream_t stream,

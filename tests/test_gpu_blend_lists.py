@@ -152,3 +152,31 @@ def test_tiles_with_empty_lists(tile, subtile, sizes):
     for p, g in out[1][3].items():
         if g is not None and g.numel():
             assert float((g - out[0][3][p]).norm() / g.norm()) <= 1e-4, p
+
+
+@pytest.mark.parametrize("tile,size,n,mu", [(32, (1311, 1311), 400, -5.5), (32, (1311, 1311), 4000, -3.5), (16, (1003, 803), 60, 0.3),
+                                            (32, (1003, 803), 60, 0.3), (16, (1003, 803), 3000, -1.0), (32, (1003, 803), 3000, -1.0)])
+def test_default_launch_where_it_runs_the_per_tile_kernels(tile, size, n, mu):
+    """Short lists of 32 x 32 tiles, and few records that cover most of the image (the library's choice is then the
+    per-tile kernels, in the forward, the importance or the backward), and sizes on the other side of that choice: images,
+    transmittances and last indices as with waves = 4, sums and gradients to the rounding of their order."""
+    sc = S.random_scene(np.random.default_rng(n), n, 1, False, spread=0.7, logscale_mu=mu)
+    sc = dataclasses.replace(sc, op_logit=(sc.op_logit - 3.0).astype(np.float32))
+    cams = [S.look_at((0.0, -4.0, 0.3), *size, bg=(0.3, 0.1, 0.2))]
+    ds = R.DeviceScene.from_scene(sc)
+    npix = size[0] * size[1]
+    dl = torch.rand(3 * npix, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    out = []
+    for cfg in (R.Config(tile, 64), R.Config(tile, 64, waves=4)):
+        fr = R.forward(ds, cams, cfg)
+        images, imp = P.importance(ds, cams, cfg)
+        out.append(([fr.images.clone(), fr.buffer("T_final", npix, torch.float32).clone(),
+                     fr.buffer("last", npix, torch.int32).clone(), images], imp, R.backward(ds, fr, dl)))
+    for x, y in zip(out[0][0], out[1][0]):
+        assert torch.equal(x, y)
+    # a score sums at most 805,409 weights, first in partial sums of 64 or 256 and those one by one, of which
+    # there are at most 12,585: in any order that errs by less than 12,585 x 2^-24 of the (positive) sum
+    assert torch.allclose(out[0][1], out[1][1], rtol=7.5e-4, atol=1e-7)
+    for p, g in out[1][2].items():
+        if g is not None and g.numel():
+            assert float((g - out[0][2][p]).norm() / g.norm()) <= 1e-4, p
