@@ -1105,7 +1105,7 @@ megs_status megs_photometric_loss(const float* images, const float* targets, int
         vs.v[i].pix_off = pix;
         pix += (int64_t)w * h;
     }
-    const int rows = loss_rows(pix);
+    const int rows = loss_rows(vs, n_views);
     for (int i = 0; i < n_views; ++i) {
         vs.v[i].rows = rows;
         vs.v[i].part_off = parts;

@@ -21,7 +21,8 @@
 // written and read. One 1080p image takes 74 + 62 us, where 16 x 16 tiles of FP64 patches in LDS took
 // 138 + 116 us; four take 248 + 254 us (the maps then exceed the last-level cache). Both passes in one, with
 // the maps kept in LDS, saves their traffic but needs 236 registers for one wave and measured 157 us (183 us
-// as two waves handing rows over).
+// as two waves handing rows over). Small and narrow images, whose strips are few or leave lanes idle, go by such
+// tiles (loss_rows).
 #include "megs_internal.hpp"
 
 namespace megs {
@@ -227,6 +228,14 @@ __device__ __forceinline__ void loss_by_wave(const double* __restrict__ partial,
     if (lane == 0) loss[0] = sum;
 }
 
+// A pixel's gradient from the windowed derivative maps; n: values of the view (3 per pixel).
+__device__ __forceinline__ float gradient_of(float x, float y, const double (&b)[3], double n, double lam) {
+    const double cl = (1.0 - lam) / n, cs = lam / n, xv = x, yv = y;
+    const double sgn = x > y ? cl : (x < y ? -cl : 0.0);
+    const double dssim = fma(yv, b[2], fma(2.0 * xv, b[1], b[0]));
+    return (float)fma(-cs, dssim, sgn);
+}
+
 // The gradient. With `loss` given, one more workgroup than strips reduces the loss beside them.
 __global__ __launch_bounds__(64) void k_ssim_bwd(LossViews vs, int nv, const float* __restrict__ x,
                                                  const float* __restrict__ y, const double* __restrict__ maps,
@@ -243,7 +252,7 @@ __global__ __launch_bounds__(64) void k_ssim_bwd(LossViews vs, int nv, const flo
     const Strip s = strip_of(vs, nv, item);
     const double* mc = maps + s.off * 3;
     const bool col = s.x0 + lane < s.v.width;
-    const double n = 3.0 * (double)s.plane, cl = (1.0 - lam) / n, cs = lam / n;
+    const double n = 3.0 * (double)s.plane;
     double acc[3][10] = {};
     RowPair<double> even[3], odd[3];
     auto load = [&](RowPair<double> (&v)[3], int r) {
@@ -270,10 +279,7 @@ __global__ __launch_bounds__(64) void k_ssim_bwd(LossViews vs, int nv, const flo
         }
         wave_sync();
         if (q >= s.y0 && col) {
-            const double xv = xf, yv = yf;
-            const double sgn = xf > yf ? cl : (xf < yf ? -cl : 0.0);
-            const double dssim = fma(yv, b[2], fma(2.0 * xv, b[1], b[0]));
-            dl[p] = (float)fma(-cs, dssim, sgn);
+            dl[p] = gradient_of(xf, yf, b, n, lam);
         }
     };
     const int r1 = s.y1 + kR;
@@ -283,6 +289,126 @@ __global__ __launch_bounds__(64) void k_ssim_bwd(LossViews vs, int nv, const flo
         step(even, r);
         if (r + 1 < r1) step(odd, r + 1);
     }
+}
+
+// The same two passes by 16 x 16 tiles, one workgroup each, for images so small or narrow that strips leave the
+// chip idle or their waves' lanes (loss_rows): a tile and its 5-pixel halo in LDS, the window as a row pass and
+// a column pass over all of it at once, where a strip's wave takes its rows one after the other.
+constexpr int kT = 16, kP = kT + 2 * kR;
+
+struct Tile {
+    LossView v;
+    int x0, y0;
+    int64_t plane, off;  // as in Strip
+};
+
+__device__ __forceinline__ Tile tile_of(const LossViews& vs, int nv, int64_t item) {
+    int i = 0;
+    while (i + 1 < nv && vs.v[i + 1].part_off <= item) ++i;
+    Tile t;
+    t.v = vs.v[i];
+    const int k = (int)(item - t.v.part_off), tx = (t.v.width + kT - 1) / kT, per_c = tx * ((t.v.height + kT - 1) / kT);
+    const int c = k / per_c, q = k - c * per_c;
+    t.x0 = q % tx * kT;
+    t.y0 = q / tx * kT;
+    t.plane = (int64_t)t.v.width * t.v.height;
+    t.off = t.v.pix_off * 3 + c * t.plane;
+    return t;
+}
+
+// Element i of the patch: is it in the image, and where.
+__device__ __forceinline__ bool patch_pixel(const Tile& t, int i, int64_t& p) {
+    const int y = t.y0 - kR + i / kP, x = t.x0 - kR + i % kP;
+    p = (int64_t)y * t.v.width + x;
+    return x >= 0 && y >= 0 && x < t.v.width && y < t.v.height;
+}
+
+template <bool MAPS>
+__global__ __launch_bounds__(kT * kT) void k_ssim_fwd_tile(LossViews vs, int nv, const float* __restrict__ x,
+                                                           const float* __restrict__ y, double* __restrict__ maps,
+                                                           double* __restrict__ partial, Window11 g) {
+    __shared__ double sx[kP * kP], sy[kP * kP], row[4][kP * kT], red[2][kT * kT / kWave];
+    const int tid = threadIdx.x, tx = tid % kT, ty = tid / kT;
+    const Tile t = tile_of(vs, nv, blockIdx.x);
+    for (int i = tid; i < kP * kP; i += kT * kT) {
+        int64_t p;
+        const bool in = patch_pixel(t, i, p);
+        sx[i] = in ? x[t.off + p] : 0.0f;
+        sy[i] = in ? y[t.off + p] : 0.0f;
+    }
+    __syncthreads();
+    for (int i = tid; i < kP * kT; i += kT * kT) {
+        double h[4];
+        row_moments(sx + i / kT * kP, sy + i / kT * kP, i % kT, g, h);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) row[m][i] = h[m];
+    }
+    __syncthreads();
+    double mo[4] = {};
+#pragma unroll
+    for (int k = 0; k < 11; ++k)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) mo[m] = fma(g.w[k], row[m][(ty + k) * kT + tx], mo[m]);
+    double ssim = 0.0, l1 = 0.0;
+    if (t.x0 + tx < t.v.width && t.y0 + ty < t.v.height) {
+        const Ssim s = ssim_of(mo);
+        const int c = (ty + kR) * kP + tx + kR;
+        ssim = s.S;
+        l1 = fabs(sx[c] - sy[c]);
+        if (MAPS) {
+            double* const mc = maps + t.off * 3 + (int64_t)(t.y0 + ty) * t.v.width + t.x0 + tx;
+#pragma unroll
+            for (int m = 0; m < 3; ++m) mc[m * t.plane] = s.d[m];
+        }
+    }
+    ssim = wave_sum_f64(ssim);
+    l1 = wave_sum_f64(l1);
+    if (tid % kWave == 0) {
+        red[0][tid / kWave] = ssim;
+        red[1][tid / kWave] = l1;
+    }
+    __syncthreads();
+    if (tid < 2) partial[2 * (int64_t)blockIdx.x + tid] = (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
+}
+
+__global__ __launch_bounds__(kT * kT) void k_ssim_bwd_tile(LossViews vs, int nv, const float* __restrict__ x,
+                                                           const float* __restrict__ y, const double* __restrict__ maps,
+                                                           float* __restrict__ dl, Window11 g, double lam,
+                                                           const double* __restrict__ partial, double* __restrict__ loss) {
+    __shared__ double sm[3][kP * kP], row[3][kP * kT];
+    const int tid = threadIdx.x, tx = tid % kT, ty = tid / kT;
+    if (loss && blockIdx.x == 0) {
+        if (tid < kWave) loss_by_wave(partial, vs, nv, lam, loss, tid);
+        return;
+    }
+    const Tile t = tile_of(vs, nv, blockIdx.x - (loss ? 1 : 0));
+    const double* const mc = maps + t.off * 3;
+    for (int i = tid; i < kP * kP; i += kT * kT) {
+        int64_t p;
+        const bool in = patch_pixel(t, i, p);
+#pragma unroll
+        for (int m = 0; m < 3; ++m) sm[m][i] = in ? mc[m * t.plane + p] : 0.0;
+    }
+    const bool inside = t.x0 + tx < t.v.width && t.y0 + ty < t.v.height;
+    const int64_t p = t.off + (int64_t)(t.y0 + ty) * t.v.width + t.x0 + tx;
+    const float xf = inside ? x[p] : 0.0f, yf = inside ? y[p] : 0.0f;
+    __syncthreads();
+    for (int i = tid; i < kP * kT; i += kT * kT)
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            double h = 0.0;
+#pragma unroll
+            for (int k = 0; k < 11; ++k) h = fma(g.w[k], sm[m][i / kT * kP + i % kT + k], h);
+            row[m][i] = h;
+        }
+    __syncthreads();
+    if (!inside) return;
+    double b[3] = {};
+#pragma unroll
+    for (int k = 0; k < 11; ++k)
+#pragma unroll
+        for (int m = 0; m < 3; ++m) b[m] = fma(g.w[k], row[m][(ty + k) * kT + tx], b[m]);
+    dl[p] = gradient_of(xf, yf, b, 3.0 * (double)t.plane, lam);
 }
 
 // The loss by a workgroup of its own, in the same order (the same bits): 256 threads per view, thread
@@ -340,42 +466,46 @@ __global__ __launch_bounds__(256) void k_adam(int64_t count, void* __restrict__ 
 
 hipError_t launch_loss(const LossViews& vs, int nv, const float* x, const float* y, double* maps, double* partial,
                        double* loss, float* dl, const Window11& g, double lam, hipStream_t stream) {
-    const int64_t strips = vs.v[nv - 1].part_off + vs.v[nv - 1].n_part;
-    const bool few = strips <= kWaveSums;
-    const dim3 grid((unsigned)strips), wave(kWave);
-    if (dl)
-        hipLaunchKernelGGL(k_ssim_fwd<true>, grid, wave, 0, stream, vs, nv, x, y, maps, partial, g);
-    else
-        hipLaunchKernelGGL(k_ssim_fwd<false>, grid, wave, 0, stream, vs, nv, x, y, maps, partial, g);
+    const int64_t items = vs.v[nv - 1].part_off + vs.v[nv - 1].n_part;  // strips, or tiles
+    const bool tiles = vs.v[0].rows == 0, few = items <= kWaveSums;
+    const dim3 grid((unsigned)items), block(tiles ? kT * kT : kWave);
+    const auto fwd = tiles ? (dl ? k_ssim_fwd_tile<true> : k_ssim_fwd_tile<false>) : (dl ? k_ssim_fwd<true> : k_ssim_fwd<false>);
+    hipLaunchKernelGGL(fwd, grid, block, 0, stream, vs, nv, x, y, maps, partial, g);
     if (!few || !dl)
         hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(nv > 1 ? 1024 : 256), 0, stream, partial, vs, nv, lam, loss);
     if (dl)
-        hipLaunchKernelGGL(k_ssim_bwd, dim3((unsigned)strips + (few ? 1 : 0)), wave, 0, stream, vs, nv, x, y, maps, dl, g,
-                           lam, partial, few ? loss : static_cast<double*>(nullptr));
+        hipLaunchKernelGGL(tiles ? k_ssim_bwd_tile : k_ssim_bwd, dim3((unsigned)items + (few ? 1 : 0)), block, 0, stream, vs,
+                           nv, x, y, maps, dl, g, lam, partial, few ? loss : static_cast<double*>(nullptr));
     return hipGetLastError();
 }
 
-// Rows of a strip: the strips above and below sum its 10 rows of halo again, so tall strips cost least, but a
-// strip is one wave's serial walk, and the chip's 1,024 SIMDs want waves: the rows that make (rows + 10)
-// times (1 + strips per SIMD) least. Measured (forward + backward) in strips of 64 / 32 / 16 rows for a 1080p
+// Rows of a strip, or 0 for tiles. The strips above and below sum a strip's 10 rows of halo again, so tall strips
+// cost least, but a strip is one wave's serial walk, and the chip's 1,024 SIMDs want waves: the rows that make
+// (rows + 10) times (1 + strips per SIMD) least. Measured (forward + backward) in strips of 64 / 32 / 16 rows for a 1080p
 // image 84 + 68, 74 + 62 and 74 + 63 us, in strips of 16 / 8 / 4 rows for one of 979 x 546 29 + 24, 35 + 28
 // and 43 + 38 us, the whole loss with its gradient in strips of 4 / 2 / 1 rows for one of 240 x 180 23, 25
-// and 30 us.
-int loss_rows(int64_t pixels) {
+// and 30 us. That measure is some 1.2 times the strips' time in us where images are wide; tiles take 8 us and 0.0108 us
+// each. The loss with its gradient in strips and in tiles: 64 x 64 16.9 and 10.0 us, 240 x 180 21.9 and 14.2, 480 x 270 29.6
+// and 24.8, 640 x 360 38.8 and 37.0, 800 x 600 54 and 70, 16384 x 1 17.6 and 27.1; narrow images leave lanes of a
+// strip's wave without a column: 1 x 16384 66 and 32 us, 16 x 16384 67 and 36, 48 x 16384 78 and 106.
+int loss_rows(const LossViews& vs, int nv) {
     int best = 64;
-    double least = 1e300;
+    double least = 1e300, tiles = 0.0;
+    for (int i = 0; i < nv; ++i) tiles += (double)loss_partials(vs.v[i].width, vs.v[i].height, 0);
     for (int rows = 64; rows >= 2; rows /= 2) {
-        const double per_simd = 3.0 * (double)pixels / (kWave * rows) / 1024.0;
-        const double t = (rows + 2 * kR) * (1.0 + per_simd);
+        double strips = 0.0;
+        for (int i = 0; i < nv; ++i) strips += (double)loss_partials(vs.v[i].width, vs.v[i].height, rows);
+        const double t = (rows + 2 * kR) * (1.0 + strips / 1024.0);
         if (t < least) {
             least = t;
             best = rows;
         }
     }
-    return best;
+    return 8.0 + 0.0108 * tiles < 0.85 * least ? 0 : best;
 }
 
 int64_t loss_partials(int width, int height, int rows) {
+    if (rows == 0) return 3ll * ((width + kT - 1) / kT) * ((height + kT - 1) / kT);
     return 3ll * ((width + kWave - 1) / kWave) * ((height + rows - 1) / rows);
 }
 

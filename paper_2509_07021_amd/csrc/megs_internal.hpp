@@ -476,11 +476,11 @@ hipError_t launch_compact_write(const CompactArgs& a, hipStream_t stream);
 // training-step pieces (loss.hip)
 struct LossView {
     int32_t width, height;
-    int32_t rows;      // rows of a strip (loss_rows)
+    int32_t rows;      // rows of a strip, or 0: tiles (loss_rows)
     int32_t pad;
     int64_t pix_off;   // first pixel of the view in the concatenated image layout
-    int64_t part_off;  // first strip (and loss partial) of the view
-    int64_t n_part;    // strips of the view (3 channels x blocks of columns x blocks of rows)
+    int64_t part_off;  // first strip or tile (and loss partial) of the view
+    int64_t n_part;    // strips or tiles of the view, over its 3 channels
 };
 struct LossViews {
     LossView v[MEGS_MAX_VIEWS];
@@ -488,7 +488,7 @@ struct LossViews {
 struct Window11 {
     double w[11];
 };
-int loss_rows(int64_t pixels);  // rows of a strip, for the pixels of all views
+int loss_rows(const LossViews& vs, int nv);  // rows of a strip for these views' sizes, or 0: 16 x 16 tiles
 int64_t loss_partials(int width, int height, int rows);
 // dl null: the loss alone, which uses no maps
 hipError_t launch_loss(const LossViews& vs, int nv, const float* x, const float* y, double* maps, double* partial,

@@ -45,3 +45,13 @@ def test_loss_without_gradient_and_repeated():
     b, none = T.photometric_loss(x, y, sizes, with_grad=False)
     c, dl2 = T.photometric_loss(x, y, sizes)
     assert none is None and float(a) == float(b) == float(c) and torch.equal(dl, dl2)
+
+
+@pytest.mark.parametrize("sizes", [
+    # 16 x 16 tiles: edges of a tile and of its halo, several views, the narrowest and tallest
+    [(16, 16)], [(17, 15), (15, 17), (32, 33)], [(21, 22), (26, 27), (5, 48)], [(1, 700), (2, 65)], [(640, 350)], [(33, 18)] * 64,
+    # strips of 2 to 64 rows on wide images: edges of a strip's columns and halo
+    [(4096, 1)], [(4097, 2)], [(4159, 3), (4160, 5)], [(4101, 9), (4155, 17)], [(703, 517)], [(961, 603), (64, 7)],
+], ids=lambda s: f"{len(s)} of {s[0][0]}x{s[0][1]}")
+def test_loss_in_tiles_and_in_strips(sizes):
+    _small(sizes)
