@@ -990,7 +990,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kSub
                 Staged st;
                 if (idx < rg.y) {
                     st = staged_of(raw, fx0, fy0, true);
-                    hit = reaches(st, bx, by);
+                    // (the fragment statistics count the entries whose box meets the sub-tile as tested)
+                    hit = STATS ? box_meets(st.box, bx, bx + 7, by, by + 7) : reaches(st, bx, by);
                 }
                 const uint64_t m = __ballot(hit);
                 if (hit) keep(lane_rank(m), st, idx - rg.x + 1u, g);
@@ -1300,13 +1301,16 @@ hipError_t launch_bwd_t(const BlendArgs& a, int batch, bool persistent, hipStrea
 }
 
 template <bool STATS, bool IMP>
-void launch_fwd_sub_t(const BlendArgs& a, unsigned grid, int tile, SubMode mode, bool persistent, hipStream_t stream) {
+hipError_t launch_fwd_sub_t(const BlendArgs& a, unsigned grid, int tile, SubMode mode, bool persistent, hipStream_t stream) {
     if (mode == kSubFlags)
         hipLaunchKernelGGL((k_blend_fwd_sub<STATS, IMP, kSubFlags>), dim3(grid), dim3(64), 0, stream, a, tile, (int)persistent);
     else if (mode == kSubReach)
         hipLaunchKernelGGL((k_blend_fwd_sub<STATS, IMP, kSubReach>), dim3(grid), dim3(64), 0, stream, a, tile, (int)persistent);
     else if constexpr (!STATS)
         hipLaunchKernelGGL((k_blend_fwd_sub<false, IMP, kSubInTile>), dim3(grid), dim3(64), 0, stream, a, tile, (int)persistent);
+    else
+        return hipErrorInvalidValue;  // (the statistics count the per-tile kernels' fragments there: sub_in_tile)
+    return hipGetLastError();
 }
 
 // The arguments with the tile order made, or without it. It is made from kOrderItemsFwd (forward) or
@@ -1338,13 +1342,9 @@ hipError_t launch_fwd_sub(const BlendArgs& args, int tile, SubMode mode, bool pe
     const BlendArgs a = with_order(args, !persistent && orders_tiles_fwd(tile, args.n_tiles), stream);
     const int64_t groups = persistent ? kPersistentGroups : items;
     const unsigned grid = (unsigned)(groups < items ? groups : items);
-    if (a.importance)
-        launch_fwd_sub_t<false, true>(a, grid, tile, mode, persistent, stream);
-    else if (a.stats)
-        launch_fwd_sub_t<true, false>(a, grid, tile, mode, persistent, stream);
-    else
-        launch_fwd_sub_t<false, false>(a, grid, tile, mode, persistent, stream);
-    return hipGetLastError();
+    if (a.importance) return launch_fwd_sub_t<false, true>(a, grid, tile, mode, persistent, stream);
+    if (a.stats) return launch_fwd_sub_t<true, false>(a, grid, tile, mode, persistent, stream);
+    return launch_fwd_sub_t<false, false>(a, grid, tile, mode, persistent, stream);
 }
 
 hipError_t launch_bwd_sub(const BlendArgs& args, int tile, SubMode mode, bool persistent, hipStream_t stream) {

@@ -180,3 +180,16 @@ def test_default_launch_where_it_runs_the_per_tile_kernels(tile, size, n, mu):
     for p, g in out[1][2].items():
         if g is not None and g.numel():
             assert float((g - out[0][2][p]).norm() / g.norm()) <= 1e-4, p
+
+
+@pytest.mark.parametrize("tile,subtile,flags,evaluated", [
+    (8, 0, 0, 379_840), (16, 8, 0, 392_000), (32, 8, 0, 397_056), (16, 8, L.MEGS_FLAG_ONE_STAGE_SORT, 403_968),
+    (32, 8, L.MEGS_FLAG_ONE_STAGE_SORT, 410_304), (32, 8, L.MEGS_FLAG_PERSISTENT, 397_056)])
+def test_fragment_counts(tile, subtile, flags, evaluated):
+    """The statistics' whole numbers on a fixed scene: the blended fragments are the same for every launch; those tested are
+    the live pixels of the entries that the sub-tile flags, or without flags the footprint boxes, leave."""
+    scene, cams = S.make_workload("small_2k_128px")
+    fr = R.forward(R.DeviceScene.from_scene(scene), cams, R.Config(tile, 64, flags | L.MEGS_FLAG_STATS, subtile=subtile))
+    torch.cuda.synchronize()
+    st = fr.alloc.view(fr.state.device_status, 8, torch.int32).cpu().numpy()
+    assert (int(st[4:6].view("uint64")[0]), int(st[6:8].view("uint64")[0])) == (80_458, evaluated)
