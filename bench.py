@@ -52,9 +52,9 @@ FLOP_TEST, FLOP_FWD_BLEND, FLOP_BWD_BLEND = 15, 10, 30
 # when the counters were taken; a changed source reports traffic as null.
 TRAFFIC = {
     # 1M masked Gaussians, FP16, 8 x 1920x1080, 32x32 tiles, 8x8 sub-tile blending: FETCH_SIZE
-    # 675,771 KiB x 1.9998 (a 512 MiB copy read 262,167 KiB) + WRITE_SIZE 1,187,045 KiB x 1.0000
-    "blend_bwd": {"bytes": 2599390042,
-                  "source_sha256": "79d6e9cd7abe409ce413e67349e204f663ff71b01cf9864acb754ab05d8d814f"},
+    # 611,034 KiB x 1.9998 (a 512 MiB copy read 262,167 KiB) + WRITE_SIZE 1,187,045 KiB x 1.0000
+    "blend_bwd": {"bytes": 2466821771,
+                  "source_sha256": "ce52c0b5e0b6f6af640650dbc0165ca0b2e074312a96eec6c7547cd9a684c4df"},
 }
 # VALU instructions per launch of the blend kernels on the same workload, from a rocprofv3 --pmc
 # SQ_INSTS_VALU run (per dispatch, averaged), with the SHA-256 of the source they were taken on (a
@@ -62,10 +62,10 @@ TRAFFIC = {
 # 1024 SIMDs at 2.4 GHz they give the issue time; set against the measured time it is the kernel's
 # VALU utilisation.
 VALU = {
-    "blend_fwd": {"instructions": 460027223,
-                  "source_sha256": "79d6e9cd7abe409ce413e67349e204f663ff71b01cf9864acb754ab05d8d814f"},
-    "blend_bwd": {"instructions": 841467483,
-                  "source_sha256": "79d6e9cd7abe409ce413e67349e204f663ff71b01cf9864acb754ab05d8d814f"},
+    "blend_fwd": {"instructions": 456103146,
+                  "source_sha256": "ce52c0b5e0b6f6af640650dbc0165ca0b2e074312a96eec6c7547cd9a684c4df"},
+    "blend_bwd": {"instructions": 835268315,
+                  "source_sha256": "ce52c0b5e0b6f6af640650dbc0165ca0b2e074312a96eec6c7547cd9a684c4df"},
 }
 SIMDS, CLOCK_HZ, VALU_CYCLES = 1024, 2.4e9, 4
 STAGE_SOURCE = {"project": "project.hip", "project_bwd": "project.hip", "blend_fwd": "blend.hip",

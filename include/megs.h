@@ -140,7 +140,7 @@ typedef struct {
     int32_t waves;         /* wave64s per tile workgroup: 1, 2 or 4 (1 for 8x8 tiles); 0: the
                               library's choice (one wave per 8x8 tile; 16x16 and 32x32 tiles blend
                               per 8x8 sub-tile, one independent wave each, with the results of the
-                              per-tile kernels) */
+                              per-tile kernels, or by those where sizes make them faster) */
     int64_t pair_capacity; /* 0: size the pair table from the counted pairs (one host wait per
                               forward); > 0: fixed capacity, no host sync, overflow reported
                               as MEGS_ERR_CAPACITY by megs_state_status */
@@ -339,7 +339,8 @@ megs_status megs_autotune(const megs_scene *scene, const megs_camera *cams, int3
  * megs_profile_begin starts recording on the calling thread: every following
  * megs_render_forward / megs_render_backward on this thread brackets each stage's launches with
  * events on its stream. megs_profile_end waits for the recorded events, writes the summed
- * milliseconds and launch counts per stage, and stops recording.
+ * milliseconds and launch counts per stage, and stops recording. (Up to 8,192 records the depth
+ * sort's launch does the scan too, and the scan stage has no launch of its own.)
  */
 typedef enum {
     MEGS_STAGE_PROJECT = 0,   /* EWA projection and SG colour */

@@ -23,8 +23,8 @@
 // its moments e w1, e w2, e w1^2, e w1 w2, e w2^2 in the exponent's factors (Staged; the exponent's
 // gradient is o_eff e, so the projection backward turns them into the mean and conic gradients once
 // per record), and the colour gradient. They are summed over the wave's pixels (the per-tile kernels with a
-// transposed butterfly of permlane swaps and DPP adds, the sub-tile kernel through LDS rows) and added to the record's slot with nine lanes of one hardware
-// float atomic, only when some lane of the wave contributed.
+// transposed butterfly of permlane swaps and DPP adds, the sub-tile kernel through LDS rows) and added to the
+// record's slot with nine lanes of one hardware float atomic, only when some lane of the wave contributed.
 #include "megs_internal.hpp"
 
 #include <utility>
@@ -571,8 +571,8 @@ __device__ __forceinline__ void wave_sync() {
 // A wave pulls one item at a time from the slice of the XCD it runs on (the XCC_ID hardware register),
 // so a tile's sub-tiles and its list stay in one L2. Once its slice is drained it reads all the
 // counters at once (one lane each) and moves to the first slice with items left, its own XCD's first. Every
-// pull advances a counter, so every item is handed out exactly once, and a wave ends when every counter has passed its slice's end. The register only steers locality: any value in
-// it gives the same result. Measured on the 8-view 1080p workload (forward / backward blend): with the
+// pull advances a counter, so every item is handed out exactly once, and a wave ends when every counter has
+// passed its slice's end. The register only steers locality: any value in it gives the same result. Measured on the 8-view 1080p workload (forward / backward blend): with the
 // eight counters in one cache line, pulls serialised on it and the blends took 3.7 / 4.3 ms instead of
 // 0.99 / 2.24 ms for one workgroup per item; a line per counter brings them to 1.35 / 2.48 ms. More
 // slices per XCD (32, 64) lost L2 locality, and several items per pull lost balance (both slower).
@@ -1036,12 +1036,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kSub
 // forms the moments in registers (an entry's second factor w2 is constant along a row), and the eight rows'
 // partial sums go through LDS to the lane that adds them: lane 9 k + c ends with sum c of entry k, so the
 // kGroup records leave through one atomic instruction, nine consecutive lanes per record (kGroup = 7: 63
-// lanes). That is about 12 VALU instructions an entry: on eight 1080p views of 1 M Gaussians, 937 M VALU
-// instructions per launch instead of 1,369 M, and 2.17 ms instead of 2.42 ms (one 1080p view of 0.96 M:
-// 0.35 instead of 0.42 ms; with the list queue and the tile order 1.94 and 0.288 ms). VALU issue is then 82%
-// of the time; the rest is the float atomics' completion and latency at four waves per SIMD. (The same sums
+// lanes). That is about 12 VALU instructions an entry. Where it replaced the butterfly, eight 1080p views of 1 M
+// Gaussians went from 1,369 M VALU instructions per launch and 2.42 ms to 937 M and 2.17 ms, one 1080p view of 0.96 M from
+// 0.42 to 0.35 ms. With the list queue and the tile order the launch has 835 M and takes 1.62 ms: VALU issue is 84% of
+// it, the rest is the float atomics' completion and latency at four waves per SIMD. (The same sums
 // as FP32 matrix products, the entries as rows and 1, x, y, x^2, x y, y^2 and the colour gradients as columns,
-// took 2.30 ms: seven entries keep the matrix pipe busy for 512 cycles.) The kernel is
+// took 2.30 ms where this took 1.93: seven entries keep the matrix pipe busy for 512 cycles.) The kernel is
 // compiled for four: at five (96 registers) it spills, and since memory operations complete in order, each
 // reload from scratch memory waits for the atomics before it (2.69 ms).
 constexpr int kGroup = 7;

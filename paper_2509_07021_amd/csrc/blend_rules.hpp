@@ -39,7 +39,7 @@ constexpr int64_t kSubTileLaunch = (int64_t)1 << 26;  // sub-tiles, one wave64 e
 constexpr bool blends_by_sub_tile(BlendKind kind, int tile, int64_t n_tiles, int64_t records, int64_t pairs) {
     const int64_t items = sub_tiles(tile, n_tiles), per_tile = items / (n_tiles > 0 ? n_tiles : 1);
     if (items >= kSubTileLaunch) return false;
-    if (items <= 8192) return true;  // all resident at once, or nearly
+    if (items <= 8192) return true;  // small launches: sub-tiles win, or lose a few us
     const int64_t sparse = items / 16384 < 40 ? items / 16384 : 40;
     if (kind != kBlendBackward && tile == 32 && pairs < sparse * n_tiles) return false;
     const int64_t cover = kind == kBlendImportance && items > 65536 ? 200 : 800;  // sub-tiles a record covers

@@ -4,8 +4,9 @@
 // The radix sort is reduce-then-scan with a fixed grid: each workgroup owns a contiguous chunk of
 // the input, so the per-pass digit counts form a [256][G] table whose digit-major exclusive scan
 // gives every workgroup its scatter base per digit. Ranks inside a workgroup are stable: each
-// wave64 owns a contiguous segment of a 4096-item tile, equal digits within a 64-item step are
-// found with one 64-bit ballot per digit bit, and per-wave running counts live in LDS. There are no
+// wave64 owns a contiguous segment of a tile of 1,024, 2,048 or 4,096 items (by the table's length), equal
+// digits within a 64-item step are found with one 64-bit ballot per digit bit, and per-wave running
+// counts live in LDS. There are no
 // inter-workgroup waits, so no pass depends on forward progress of other workgroups. The element
 // count is read on device, which lets the same launches run inside a captured graph.
 //
