@@ -52,9 +52,9 @@ FLOP_TEST, FLOP_FWD_BLEND, FLOP_BWD_BLEND = 15, 10, 30
 # when the counters were taken; a changed source reports traffic as null.
 TRAFFIC = {
     # 1M masked Gaussians, FP16, 8 x 1920x1080, 32x32 tiles, 8x8 sub-tile blending: FETCH_SIZE
-    # 611,034 KiB x 1.9998 (a 512 MiB copy read 262,167 KiB) + WRITE_SIZE 1,187,045 KiB x 1.0000
-    "blend_bwd": {"bytes": 2466821771,
-                  "source_sha256": "ce52c0b5e0b6f6af640650dbc0165ca0b2e074312a96eec6c7547cd9a684c4df"},
+    # 611,097 KiB x 1.9998 (a 512 MiB copy read 262,167 KiB) + WRITE_SIZE 1,187,045 KiB x 1.0000
+    "blend_bwd": {"bytes": 2466951638,
+                  "source_sha256": "3cae8e215573a0a999d36e8be4d96003c91f67f5f2ceaf7fb2016532201aaabe"},
 }
 # VALU instructions per launch of the blend kernels on the same workload, from a rocprofv3 --pmc
 # SQ_INSTS_VALU run (per dispatch, averaged), with the SHA-256 of the source they were taken on (a
@@ -63,9 +63,9 @@ TRAFFIC = {
 # VALU utilisation.
 VALU = {
     "blend_fwd": {"instructions": 456103146,
-                  "source_sha256": "ce52c0b5e0b6f6af640650dbc0165ca0b2e074312a96eec6c7547cd9a684c4df"},
+                  "source_sha256": "3cae8e215573a0a999d36e8be4d96003c91f67f5f2ceaf7fb2016532201aaabe"},
     "blend_bwd": {"instructions": 835268315,
-                  "source_sha256": "ce52c0b5e0b6f6af640650dbc0165ca0b2e074312a96eec6c7547cd9a684c4df"},
+                  "source_sha256": "3cae8e215573a0a999d36e8be4d96003c91f67f5f2ceaf7fb2016532201aaabe"},
 }
 SIMDS, CLOCK_HZ, VALU_CYCLES = 1024, 2.4e9, 4
 STAGE_SOURCE = {"project": "project.hip", "project_bwd": "project.hip", "blend_fwd": "blend.hip",

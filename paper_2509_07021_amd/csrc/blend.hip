@@ -1339,7 +1339,7 @@ BlendArgs with_order(const BlendArgs& a, bool use, hipStream_t stream) {
 
 hipError_t launch_fwd_sub(const BlendArgs& args, int tile, SubMode mode, bool persistent, hipStream_t stream) {
     const int64_t items = args.n_tiles * (int64_t)(tile / 8) * (tile / 8);
-    const BlendArgs a = with_order(args, !persistent && orders_tiles_fwd(tile, args.n_tiles), stream);
+    const BlendArgs a = with_order(args, !persistent && orders_tiles_fwd(tile, args.n_tiles, args.pairs), stream);
     const int64_t groups = persistent ? kPersistentGroups : items;
     const unsigned grid = (unsigned)(groups < items ? groups : items);
     if (a.importance) return launch_fwd_sub_t<false, true>(a, grid, tile, mode, persistent, stream);

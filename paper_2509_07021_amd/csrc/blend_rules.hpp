@@ -14,6 +14,12 @@ constexpr int64_t kOrderItemsBwd = 8192, kOrderTilesBwd = 65536;
 constexpr bool orders_tiles_fwd(int tile, int64_t n_tiles) {
     return tile > 8 && (tile == 32 || n_tiles <= kOrderTilesFwd16) && sub_tiles(tile, n_tiles) > kOrderItemsFwd;
 }
+// `pairs` is the pair table's capacity. Above 65,536 tiles, where most of them are empty or nearly, the waves only pay
+// for looking up the order: a 16384 x 16384 image in 32 x 32 tiles with 0.04 / 0.7 pairs a tile 1.56 and 2.45 / 2.07 and
+// 2.59 ms without and with it.
+constexpr bool orders_tiles_fwd(int tile, int64_t n_tiles, int64_t pairs) {
+    return orders_tiles_fwd(tile, n_tiles) && (n_tiles <= 65536 || pairs >= 8 * n_tiles);
+}
 constexpr bool orders_tiles_bwd(int tile, int64_t n_tiles) {
     return tile > 8 && n_tiles <= kOrderTilesBwd && sub_tiles(tile, n_tiles) > kOrderItemsBwd;
 }

@@ -14,6 +14,10 @@ int main() {
     int tile;
     long long n_tiles, records, pairs;
     while (scanf("%15s %d %lld %lld %lld", kind, &tile, &n_tiles, &records, &pairs) == 5) {
+        if (!strcmp(kind, "order")) {
+            printf("%d\\n", (int)orders_tiles_fwd(tile, n_tiles, pairs));
+            continue;
+        }
         const BlendKind k = !strcmp(kind, "fwd") ? kBlendForward : !strcmp(kind, "imp") ? kBlendImportance : kBlendBackward;
         printf("%d\\n", (int)blends_by_sub_tile(k, tile, n_tiles, records, pairs));
     }
@@ -39,6 +43,11 @@ CASES = [
     ("imp", 32, 2040, 3000, 50 * 3000 - 1, True), ("imp", 32, 2040, 3000, 50 * 3000, False),
     ("imp", 32, 16320, 24_000, 34 * 24_000, False), ("bwd", 32, 16320, 24_000, 34 * 24_000, True),
     ("fwd", 16, 1, 0, 0, True), ("bwd", 16, 100_000, 0, 0, False),
+    # the forward's tile order: from 12,289 sub-tiles on, to 16,384 tiles of 16 x 16; of 32 x 32 beyond 65,536 with long lists
+    ("order", 8, 20_000, 0, 1 << 20, False), ("order", 16, 3072, 0, 0, False), ("order", 16, 3073, 0, 0, True),
+    ("order", 16, 16384, 0, 0, True), ("order", 16, 16385, 0, 1 << 30, False), ("order", 32, 768, 0, 0, False),
+    ("order", 32, 769, 0, 0, True), ("order", 32, 65536, 0, 0, True), ("order", 32, 65537, 0, 8 * 65537 - 1, False),
+    ("order", 32, 65537, 0, 8 * 65537, True),
 ]
 
 

@@ -101,7 +101,7 @@ def test_tile_order_in_slices(tile, sizes):
     (none), and with 32 x 32 tiles 16,641 and 65,792 (two and five slices in the forward): the sub-tile blends run in
     that order, with the two-stage and the one-stage sort, against the persistent launch, which runs the
     sub-tiles as numbered: the same decisions over the same lists, so the same bits, and every tile was run."""
-    sc = S.random_scene(np.random.default_rng(5), 4000, 1, False, spread=1.5, logscale_mu=-3.5)
+    sc = S.random_scene(np.random.default_rng(5), 4000, 1, False, spread=1.5, logscale_mu=-3.0)
     cams = [S.look_at((0.0, -4.0, 0.3 + 0.2 * i), w, h, bg=(0.3, 0.1, 0.2)) for i, (w, h) in enumerate(sizes)]
     ds = R.DeviceScene.from_scene(sc)
     npix = sum(c.width * c.height for c in cams)
@@ -109,6 +109,7 @@ def test_tile_order_in_slices(tile, sizes):
     out = []
     for flags in (L.MEGS_FLAG_PERSISTENT, 0, L.MEGS_FLAG_ONE_STAGE_SORT):
         fr = R.forward(ds, cams, R.Config(tile, 64, subtile=8, flags=flags))
+        assert int(fr.state.n_pairs) >= 8 * int(fr.state.n_tiles)  # (above 65,536 tiles only long lists are ordered)
         out.append(([fr.images.clone(), fr.buffer("T_final", npix, torch.float32).clone(),
                      fr.buffer("last", npix, torch.int32).clone()], R.backward(ds, fr, dl)))
     for other in out[1:]:
